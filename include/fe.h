@@ -592,9 +592,10 @@ fe_status fe_spmv_tuning_reset(void);
  * reports the longest row), for the Q1 scalar pattern 4 (the values of 32
  * rows and the runs of x they touch staged in LDS with wide loads; two lanes
  * per row in the order of mode 3, so modes 3 and 4 give bitwise the same
- * products), and for every other pattern 6 (rows_per_wave 8: x over the
- * column box of 32 consecutive rows of a line of nodes staged in LDS per
- * workgroup; bitwise the same products as mode 2 with 8 rows per wave),
+ * products), and for every other pattern 6 (x over the column box of a chunk
+ * of rows of neighbouring lines of nodes staged in LDS per workgroup;
+ * rows_per_wave 8: row by row, bitwise the same products as mode 2 with 8
+ * rows per wave; vector problems also 4: the rows of a node together),
  * timed on A assembled on (mesh, order, coeff); the fastest
  * becomes the plan of every mesh system with the same longest row and
  * component count.  ws: fe_spmv_autotune_query(A->n_rows) bytes.

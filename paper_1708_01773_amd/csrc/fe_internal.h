@@ -393,8 +393,17 @@ struct AxisClosed {
     int32_t lo, hi, N, swlo;
 };
 
-__device__ __forceinline__ void axis_row(const AxisClosed &A, int32_t k, double kinv, int32_t i, int32_t &w,
-                                         int32_t &cl, int32_t &P)
+// floor(a / k) for 0 <= a < 2^31 and an order k in 1..4, in integers (a shift,
+// or a multiplication by ceil(2^32 / 3)): exact, and uniform arguments stay
+// on the scalar unit, which a division through doubles does not.
+__device__ __forceinline__ int32_t div_order(int32_t a, int32_t k)
+{
+    const int32_t third = int32_t((uint64_t(uint32_t(a)) * 0x55555556u) >> 32);
+    return k == 3 ? third : a >> (k >> 1);
+}
+
+__device__ __forceinline__ void axis_row(const AxisClosed &A, int32_t k, int32_t i, int32_t &w, int32_t &cl,
+                                         int32_t &P)
 {
     if (A.N == 0) {  // the third axis of a 2D mesh
         w = 1;
@@ -402,13 +411,13 @@ __device__ __forceinline__ void axis_row(const AxisClosed &A, int32_t k, double 
         P = 0;
         return;
     }
-    const int32_t m = i - div_exact(i, k, kinv) * k;
+    const int32_t m = i - div_order(i, k) * k;
     const int32_t low = A.lo == 0 ? (i == 0 ? k : 0) : ((i >= 1 && i <= k) ? 1 : 0);
     const int32_t high = A.hi == A.N ? (i == A.N ? k : 0) : ((i >= A.N - k && i <= A.N - 1) ? 1 : 0);
     w = (m == 0 ? 2 * k + 1 : k + 1) - low - high;
     cl = (m == 0 ? i - k : i - m) + low;
     // unclipped widths of nodes 0..i-1: i (k + 1) + k ceil(i / k)
-    P = i * (k + 1) + k * div_exact(i + k - 1, k, kinv) - A.swlo;
+    P = i * (k + 1) + k * div_order(i + k - 1, k) - A.swlo;
     P -= A.lo == 0 ? (i >= 1 ? k : 0) : max(0, min(i - 1, k));
     if (A.hi != A.N) P -= max(0, i - max(A.lo, A.N - k));
 }

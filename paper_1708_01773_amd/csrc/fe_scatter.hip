@@ -347,7 +347,7 @@ __device__ __forceinline__ double entry_from_tables(const RowTables &t, const ET
 // Row geometry from the closed forms of the axis tables (no table loads);
 // the fields of row_geom.
 template <int NC>
-__device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const AxisClosed (&A)[3], double kinv,
+__device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const AxisClosed (&A)[3],
                                                    int64_t row)
 {
     RowGeom g;
@@ -359,9 +359,9 @@ __device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const Axi
     const int32_t q = div_exact(R, f0, s.ax[0].finv), t0 = R - q * f0;
     const int32_t t2 = div_exact(q, f1, s.ax[1].finv), t1 = q - t2 * f1;
     int32_t w0, w1, w2, cl0, cl1, cl2, P0, P1, P2;
-    axis_row(A[0], k, kinv, A[0].lo + t0, w0, cl0, P0);
-    axis_row(A[1], k, kinv, A[1].lo + t1, w1, cl1, P1);
-    axis_row(A[2], k, kinv, A[2].lo + t2, w2, cl2, P2);
+    axis_row(A[0], k, A[0].lo + t0, w0, cl0, P0);
+    axis_row(A[1], k, A[1].lo + t1, w1, cl1, P1);
+    axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
     g.I0 = A[0].lo + t0;
     g.I1 = A[1].lo + t1;
     g.I2 = A[2].lo + t2;
@@ -371,9 +371,9 @@ __device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const Axi
     g.cl0 = cl0;
     g.cl1 = cl1;
     g.cl2 = cl2;
-    g.v0 = div_exact(int32_t(g.I0), k, kinv);
-    g.v1 = div_exact(int32_t(g.I1), k, kinv);
-    g.v2 = div_exact(int32_t(g.I2), k, kinv);
+    g.v0 = div_order(int32_t(g.I0), k);
+    g.v1 = div_order(int32_t(g.I1), k);
+    g.v2 = div_order(int32_t(g.I2), k);
     g.m0 = int32_t(g.I0) - g.v0 * k;
     g.m1 = int32_t(g.I1) - g.v1 * k;
     g.m2 = int32_t(g.I2) - g.v2 * k;
@@ -395,7 +395,6 @@ __device__ __forceinline__ void k5_entries_body(const SpaceArgs &s, const ET *__
     const int64_t nw = nb * 4;
     const int64_t lw = lb * 4 + threadIdx.x / 64;
     const int32_t k = s.k, k1 = k + 1;
-    const double kinv = 1.0 / double(k);
     AxisClosed A[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -410,7 +409,7 @@ __device__ __forceinline__ void k5_entries_body(const SpaceArgs &s, const ET *__
     const int64_t n_nodes = s.n_rows / NC;
     for (int64_t node = lw; node < n_nodes; node += nw) {
         const int64_t row0 = node * NC;
-        const RowGeom g = row_geom_closed<NC>(s, A, kinv, row0);
+        const RowGeom g = row_geom_closed<NC>(s, A, row0);
         build_row_tables(s, g, NC, t, lane);
         int32_t e0lo, e0hi, e1lo, e1hi, e2lo, e2hi;  // the node's cells along each axis
         axis_cells(g.I0, g.v0, g.m0, g.I0, s.ax[0].n, e0lo, e0hi);

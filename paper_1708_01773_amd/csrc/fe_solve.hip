@@ -97,6 +97,13 @@ struct PcgWs {
     double *r, *p, *q;
 };
 
+// How the block-staged traversal (plan mode 6) cuts a system into chunks.
+struct XbShape {
+    int32_t rc = 1, m = 1, pcs = 1, yb = 1;  // groups per line stretch, lines per chunk, stretches per line, y blocks
+    int32_t nchunks = 0;
+    int32_t lds = 0;  // bytes of the staged box
+};
+
 // One problem of a (possibly batched) solve, as the kernels see it.
 struct PcgProb {
     int64_t n, nnz;
@@ -110,6 +117,7 @@ struct PcgProb {
     int32_t maxit;
     int32_t nbr, nbe;  // blocks of the row kernels / of the vector kernels
     SpaceArgs sa;      // pattern of a system assembled on a structured brick (mode 2)
+    XbShape xb;        // its chunks (mode 6)
 };
 
 // How a CSR matrix is traversed.
@@ -615,7 +623,6 @@ __device__ __forceinline__ void for_rows_struct(const SpaceArgs &s, const double
     const int64_t nw = nb * kWaves, lw = lb * kWaves + threadIdx.x / 64;
     const int64_t runs = (n + RPW - 1) / RPW;
     const int32_t k = s.k;
-    const double kinv = 1.0 / double(k);
     AxisClosed A[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -639,9 +646,9 @@ __device__ __forceinline__ void for_rows_struct(const SpaceArgs &s, const double
                 const int32_t q = div_exact(R, f0, f0inv), t0 = R - q * f0;
                 const int32_t t2 = div_exact(q, f1, f1inv), t1 = q - t2 * f1;
                 int32_t w0, w1, w2, cl0, cl1, cl2, P0, P1, P2;
-                axis_row(A[0], k, kinv, A[0].lo + t0, w0, cl0, P0);
-                axis_row(A[1], k, kinv, A[1].lo + t1, w1, cl1, P1);
-                axis_row(A[2], k, kinv, A[2].lo + t2, w2, cl2, P2);
+                axis_row(A[0], k, A[0].lo + t0, w0, cl0, P0);
+                axis_row(A[1], k, A[1].lo + t1, w1, cl1, P1);
+                axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
                 const int64_t S = int64_t(P2) * T1 * T0 + int64_t(w2) * P1 * T0 + int64_t(w2 * w1) * P0;
                 const int32_t wx = w0 * NC;
                 glen = wx * w1 * w2;
@@ -740,7 +747,6 @@ __device__ __forceinline__ void for_rows_short(const SpaceArgs &s, const double 
     const int64_t nw = nb * kWaves, lw = lb * kWaves + threadIdx.x / 64;
     const int64_t runs = (n + RW - 1) / RW;
     const int32_t k = s.k;
-    const double kinv = 1.0 / double(k);
     AxisClosed A[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -764,9 +770,9 @@ __device__ __forceinline__ void for_rows_short(const SpaceArgs &s, const double 
             const int32_t q = div_exact(R, f0, f0inv), t0 = R - q * f0;
             const int32_t t2 = div_exact(q, f1, f1inv), t1 = q - t2 * f1;
             int32_t w0, w2, cl0, cl1, cl2, P0, P1, P2;
-            axis_row(A[0], k, kinv, A[0].lo + t0, w0, cl0, P0);
-            axis_row(A[1], k, kinv, A[1].lo + t1, w1, cl1, P1);
-            axis_row(A[2], k, kinv, A[2].lo + t2, w2, cl2, P2);
+            axis_row(A[0], k, A[0].lo + t0, w0, cl0, P0);
+            axis_row(A[1], k, A[1].lo + t1, w1, cl1, P1);
+            axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
             const int64_t S = int64_t(P2) * T1 * T0 + int64_t(w2) * P1 * T0 + int64_t(w2 * w1) * P0;
             wx = w0 * NC;
             len = wx * w1 * w2;
@@ -882,9 +888,9 @@ __device__ __forceinline__ void for_rows_q1(const SpaceArgs &s, const double *__
             const int32_t q = div_exact(r32, f0, f0inv), t0 = r32 - q * f0;
             const int32_t t2 = div_exact(q, f1, f1inv), t1 = q - t2 * f1;
             int32_t w0, w2, cl0, cl1, cl2, P0, P1, P2;
-            axis_row(A[0], 1, 1.0, A[0].lo + t0, w0, cl0, P0);
-            axis_row(A[1], 1, 1.0, A[1].lo + t1, w1, cl1, P1);
-            axis_row(A[2], 1, 1.0, A[2].lo + t2, w2, cl2, P2);
+            axis_row(A[0], 1, A[0].lo + t0, w0, cl0, P0);
+            axis_row(A[1], 1, A[1].lo + t1, w1, cl1, P1);
+            axis_row(A[2], 1, A[2].lo + t2, w2, cl2, P2);
             start = int64_t(P2) * T1 * T0 + int64_t(w2) * P1 * T0 + int64_t(w2 * w1) * P0;
             wx = w0;
             len = w0 * w1 * w2;
@@ -1032,9 +1038,9 @@ __device__ __forceinline__ void for_rows_q1sym(const SpaceArgs &s, const VT *__r
             const int32_t q = div_exact(r32, f0, f0inv), t0 = r32 - q * f0;
             const int32_t t2 = div_exact(q, f1, f1inv), t1 = q - t2 * f1;
             int32_t w0, w1, w2, cl0, cl1, cl2, P0, P1, P2;
-            axis_row(A[0], 1, 1.0, A[0].lo + t0, w0, cl0, P0);
-            axis_row(A[1], 1, 1.0, A[1].lo + t1, w1, cl1, P1);
-            axis_row(A[2], 1, 1.0, A[2].lo + t2, w2, cl2, P2);
+            axis_row(A[0], 1, A[0].lo + t0, w0, cl0, P0);
+            axis_row(A[1], 1, A[1].lo + t1, w1, cl1, P1);
+            axis_row(A[2], 1, A[2].lo + t2, w2, cl2, P2);
             mk0 = ((1u << w0) - 1u) << (cl0 - (A[0].lo + t0) + 1);
             mk1 = ((1u << w1) - 1u) << (cl1 - (A[1].lo + t1) + 1);
             mk2 = DIM == 3 ? ((1u << w2) - 1u) << (cl2 - (A[2].lo + t2) + 1) : 2u;
@@ -1200,9 +1206,9 @@ __global__ __launch_bounds__(kQ1Block) void sym_fill_kernel(SpaceArgs s, const d
         const int32_t q = r32 / f0, t0 = r32 - q * f0;
         const int32_t t2 = q / f1, t1 = q - t2 * f1;
         int32_t cl[3], P[3];
-        axis_row(A[0], 1, 1.0, A[0].lo + t0, w[0], cl[0], P[0]);
-        axis_row(A[1], 1, 1.0, A[1].lo + t1, w[1], cl[1], P[1]);
-        axis_row(A[2], 1, 1.0, A[2].lo + t2, w[2], cl[2], P[2]);
+        axis_row(A[0], 1, A[0].lo + t0, w[0], cl[0], P[0]);
+        axis_row(A[1], 1, A[1].lo + t1, w[1], cl[1], P[1]);
+        axis_row(A[2], 1, A[2].lo + t2, w[2], cl[2], P[2]);
         start = int64_t(P[2]) * T1 * T0 + int64_t(w[2]) * P[1] * T0 + int64_t(w[2] * w[1]) * P[0];
         len = w[0] * w[1] * w[2];
         e[0] = cl[0] - (A[0].lo + t0) + 1;
@@ -1236,37 +1242,99 @@ __global__ __launch_bounds__(kQ1Block) void sym_fill_kernel(SpaceArgs s, const d
 }
 
 // Rows of any evaluated pattern, x staged per block (plan mode 6).  A block
-// takes a chunk of kXbRows consecutive rows of one line of nodes (t1, t2
-// fixed): their column boxes share the y and z ranges, and their x ranges lie
-// in the union [cl0(first node), cl0(last node) + w0(last node)).  The block
-// loads x over that box -- w1 w2 runs of NC (xb - xa) consecutive unknowns,
-// coalesced -- into LDS once; then each wave sums eight rows, eight lanes per
-// row, values read from memory and x from LDS, in the order of the
-// lanes-per-row traversal with eight rows per wave (bitwise the same
-// products).  Chunks never cross a line of nodes.
-constexpr int kXbRows = 32;   // rows per chunk: 4 waves x 8 rows
-constexpr int kXbCap = 4864;  // staged doubles: (2k+1)^2 runs of NC (nodes of a chunk + 2k), k <= 4
+// takes a chunk: a stretch of rc groups of rows along x of m neighbouring
+// lines of nodes (t1 .. t1 + m - 1, one t2).  A group is one row (shape 8)
+// or the NC rows of a node, which have the same columns (shape 4).  The
+// rows' column boxes lie in the union box of the chunk, run x W1 x w2
+// unknowns (run consecutive ones along x); the block stages x over it in LDS
+// once, coalesced, and a position p of a row reads slot
+//   xoff + p + (p / wx) (run - wx) + (p / (wx w1)) (W1 - w1) run
+// (wx, w1: the row's own box), so a column costs two multiply-shift divisions
+// and no load.  L lanes stream a group's values, two consecutive ones per
+// 16-byte load (8-byte aligned: the rows start anywhere), U loads per row in
+// flight; the first U are issued before x is staged, so the two round trips
+// overlap.
+// What bounds it: the values, from HBM (x is 12-40% of them, from L2); with
+// 8-byte loads of eight lanes per row it was bound by the loads it could keep
+// in flight (the texture addresser 0.93 busy at 3.6-4.3 TB/s).
+//   shape 8: L = 4, one row per group.  Lane l holds the partial sums of the
+//     positions 2 l and 2 l + 1 mod 8, in position order, added in the tree of
+//     the lanes-per-row traversal with eight rows per wave: bitwise the same
+//     products.
+//   shape 4: L = 16, the NC rows of a node together, so that x and the slot
+//     arithmetic serve NC values each, in an order of its own.
+// Chunks are dealt XCD-contiguously (nb is a multiple of 8).
+constexpr int kXbRows = 64;   // most rows per chunk
+constexpr int kXbCap = 7536;  // most staged doubles: (2k+1)^2 runs of NC (nodes of a chunk + 2k), k <= 4
 
-// The staged box of a chunk: its kXbRows rows cover at most (kXbRows - 1) / NC + 2
-// nodes of the line (a chunk may start inside a node's components), whose
-// column boxes along x reach k nodes beyond each end, and (2k + 1)^2 node
-// lines across; every supported component count and order must fit.
+// The staged box of a chunk of one line: its kXbRows rows cover at most
+// (kXbRows - 1) / NC + 2 nodes of the line (a chunk may start inside a node's
+// components), whose column boxes along x reach k nodes beyond each end, and
+// (2k + 1)^2 node lines across; every supported component count and order
+// must fit.  A chunk of m lines holds at most kXbRows / m rows of each and
+// m + 2k lines across in y, which is less.
 constexpr int xblock_staged_max(int nc, int k) { return nc * ((kXbRows - 1) / nc + 2 + 2 * k) * (2 * k + 1) * (2 * k + 1); }
 static_assert(xblock_staged_max(1, 4) <= kXbCap && xblock_staged_max(2, 4) <= kXbCap &&
                   xblock_staged_max(3, 4) <= kXbCap,
               "the staged x box of a mode-6 chunk exceeds its LDS buffer");
 
-template <int NC, typename VT, typename Fn>
-__device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const VT *__restrict__ gval,
+constexpr int xb_lanes(int shape) { return shape == 8 ? 4 : 16; }
+constexpr int xb_group_rows(int shape, int nc) { return shape == 8 ? 1 : nc; }
+
+// The cut with the least work: every chunk streams up to G groups whatever it
+// holds (idle lanes cost what busy ones do) and stages its box, so short lines
+// of nodes are taken several to a chunk and long ones in equal stretches.
+static XbShape xb_shape(const SpaceArgs &sa, int shape)
+{
+    const int nc = sa.ncomp, k = sa.k, G = kQ1Block / xb_lanes(shape), gr = xb_group_rows(shape, nc);
+    const int64_t f0 = sa.ax[0].f, f1 = sa.ax[1].f, f2 = sa.ax[2].f;
+    XbShape best{};
+    if (f0 == 0 || f1 == 0 || f2 == 0) return best;
+    const int64_t gpl = f0 * nc / gr;  // groups per line
+    double row = nc;                   // values per row, average over the vertex and interior nodes of an axis
+    for (int r = 0; r < sa.dim; r++) row *= double(2 * k + 1 + (k - 1) * (k + 1)) / k;
+    double cost = 0.0;
+    const int64_t p0 = (gpl + G - 1) / G;
+    for (int64_t pcs = p0; pcs < p0 + 4 && pcs <= gpl; pcs++) {
+        const int64_t rc = (gpl + pcs - 1) / pcs;
+        const int64_t m = std::max<int64_t>(1, std::min<int64_t>(f1, G / rc));
+        const int64_t yb = (f1 + m - 1) / m;
+        const int64_t nodes = std::min<int64_t>(f0, (rc * gr - 1) / nc + 2 + 2 * k);
+        const int64_t wy = std::min<int64_t>(f1, m + 2 * k), wz = sa.dim == 3 ? std::min<int64_t>(f2, 2 * k + 1) : 1;
+        const int64_t staged = nc * nodes * wy * wz;
+        const double c = double(yb * pcs) * (G * gr * row + 2.0 * double(staged));
+        if (best.nchunks == 0 || c < cost) {
+            cost = c;
+            best = XbShape{int32_t(rc), int32_t(m), int32_t((gpl + rc - 1) / rc), int32_t(yb), 0, int32_t(8 * staged)};
+            best.nchunks = int32_t(f2 * yb * best.pcs);
+        }
+    }
+    return best;
+}
+
+extern __shared__ double fe_xb_lds[];                                       // the staged box (XbShape::lds bytes)
+typedef double fe_dpair8 __attribute__((ext_vector_type(2), aligned(8)));  // two doubles at an 8-byte boundary
+typedef float fe_fpair4 __attribute__((ext_vector_type(2), aligned(4)));   // two floats at a 4-byte boundary
+
+template <int SHAPE, int NC, typename VT, typename Fn>
+__device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const XbShape &xb, const VT *__restrict__ gval,
                                                 const double *__restrict__ gx, int64_t lb, int64_t nb, Fn f)
 {
-    constexpr int RPW = 8, LW = 64 / RPW;
-    __shared__ double sx[kXbCap];
+    constexpr int L = xb_lanes(SHAPE), GR = xb_group_rows(SHAPE, NC);
+    constexpr int U = SHAPE == 8 ? 4 : 2;  // loads per row in flight
+    using Pair = std::conditional_t<sizeof(VT) == 8, fe_dpair8, fe_fpair4>;
+    double *sx = fe_xb_lds;
     const FE_GLOBAL VT *__restrict__ val = as_global(gval);
     const FE_GLOBAL double *__restrict__ x = as_global(gx);
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, g = lane / LW, sub = lane % LW;
+    const int tid = threadIdx.x, g = tid / L, sub = tid % L;
+    if (s.n_rows == 1) {  // no pair to load
+        if (lb == 0 && tid == 0) {
+            if constexpr (std::is_invocable_v<Fn, int64_t, double, double>) f(0, double(val[0]) * x[0], x[0]);
+            else f(0, double(val[0]) * x[0]);
+        }
+        return;
+    }
     const int32_t k = s.k;
-    const double kinv = 1.0 / double(k);
     AxisClosed A[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -1277,68 +1345,124 @@ __device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const VT *__
     }
     const int32_t f0 = int32_t(s.ax[0].f), f1 = int32_t(s.ax[1].f);
     const int64_t T0 = s.ax[0].T, T1 = s.ax[1].T;
-    const int64_t rpl = int64_t(NC) * f0;                      // rows per line of nodes
-    const int64_t cpl = (rpl + kXbRows - 1) / kXbRows;         // chunks per line
-    const int64_t nchunks = int64_t(f1) * s.ax[2].f * cpl;
-    for (int64_t ch = lb; ch < nchunks; ch += nb) {
-        const int64_t line = ch / cpl, q = ch - line * cpl;
-        const int32_t t1 = int32_t(line % f1), t2 = int32_t(line / f1);
-        const int64_t lr0 = q * kXbRows;                        // first row of the chunk within its line
-        const int64_t lr1 = lr0 + kXbRows < rpl ? lr0 + kXbRows : rpl;
-        int32_t wa, cla, Pa, wb, clb, Pb, w1, cl1, P1, w2, cl2, P2;
-        axis_row(A[0], k, kinv, A[0].lo + int32_t(lr0 / NC), wa, cla, Pa);
-        axis_row(A[0], k, kinv, A[0].lo + int32_t((lr1 - 1) / NC), wb, clb, Pb);
-        axis_row(A[1], k, kinv, A[1].lo + t1, w1, cl1, P1);
-        axis_row(A[2], k, kinv, A[2].lo + t2, w2, cl2, P2);
-        const int32_t xa = cla, run = NC * (clb + wb - cla);    // staged nodes [xa, xb) along x
-        const int32_t nst = run * w1 * w2;
+    const int32_t rpl = NC * f0;  // rows per line of nodes
+    const int32_t rc = xb.rc, m = xb.m;
+    // this thread's group: line gj of the chunk, group gr of its stretch (g < 64)
+    const int gj = int((uint32_t(g) * (65536u / uint32_t(rc) + 1u)) >> 16), gr = g - gj * rc;
+    const int32_t xcd = int32_t(lb % 8), per = int32_t(nb / 8);
+    const int32_t c_hi = int32_t(int64_t(xcd + 1) * xb.nchunks / 8);
+    for (int32_t ch = int32_t(int64_t(xcd) * xb.nchunks / 8) + int32_t(lb / 8); ch < c_hi; ch += per) {
+        const int32_t q = ch / xb.pcs, pc = ch - q * xb.pcs;
+        const int32_t t2 = q / xb.yb, ya = (q - t2 * xb.yb) * m;   // plane and first line of the chunk
+        const int32_t ny = ya + m < f1 ? m : f1 - ya;               // lines of the chunk
+        const int32_t lr0 = pc * rc * GR;                           // its rows along a line: [lr0, lr1)
+        const int32_t lr1 = lr0 + rc * GR < rpl ? lr0 + rc * GR : rpl;
+        int32_t wa, cla, Pa, wb, clb, Pb, wya, cya, Pya, wyb, cyb, Pyb, w2, cl2, P2;
+        axis_row(A[0], k, A[0].lo + lr0 / NC, wa, cla, Pa);
+        axis_row(A[0], k, A[0].lo + (lr1 - 1) / NC, wb, clb, Pb);
+        axis_row(A[1], k, A[1].lo + ya, wya, cya, Pya);
+        axis_row(A[1], k, A[1].lo + ya + ny - 1, wyb, cyb, Pyb);
+        axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
+        const int32_t run = NC * (clb + wb - cla), W1 = cyb + wyb - cya;
         __syncthreads();  // the previous chunk's reads of sx are done
-        for (int e = threadIdx.x; e < nst; e += 256) {
-            const int rr = e / run, i = e - rr * run;
-            const int jz = rr / w1, jy = rr - jz * w1;
-            const int64_t col = int64_t(NC) * ((xa - A[0].lo) + int64_t(f0) * ((cl1 + jy - A[1].lo) +
-                                                                               int64_t(f1) * (cl2 + jz - A[2].lo))) + i;
-            sx[e] = x[col];
-        }
-        __syncthreads();
-        const int64_t lrow = lr0 + RPW * wave + g;
-        const bool live = lrow < lr1;
-        const int64_t row = line * rpl + lrow;
-        double sum = 0.0;
-        if (live) {
-            const int32_t t0 = int32_t(lrow / NC), c = int32_t(lrow - int64_t(t0) * NC);
-            int32_t w0, cl0, P0;
-            axis_row(A[0], k, kinv, A[0].lo + t0, w0, cl0, P0);
-            const int64_t S = int64_t(P2) * T1 * T0 + int64_t(w2) * P1 * T0 + int64_t(w2 * w1) * P0;
-            const int32_t wx = w0 * NC, len = wx * w1 * w2;
-            const int64_t start = int64_t(NC) * NC * S + int64_t(c) * len;
-            const int32_t xoff = NC * (cl0 - xa);
-            // floor(p / d) = (p m) >> 20 for m in [2^20 / d, 2^20 / d + 8] (p < 2^12, d <= 27)
-            const uint32_t mx = uint32_t(1048576.0f * __builtin_amdgcn_rcpf(float(wx))) + 2u;
-            const uint32_t my = uint32_t(1048576.0f * __builtin_amdgcn_rcpf(float(w1))) + 2u;
-            for (int32_t p0 = 0; p0 < len; p0 += 4 * LW) {
-                double a4[4], x4[4];
+        {
+            // element e of the box: run rr = e / run, (jy, jz) = rr mod, div W1; exact
+            // (the quotient's error is below e / 2^32 < 1 / run); four loads in flight
+            const uint32_t mr = 0xffffffffu / uint32_t(run) + 1u, mw = 0xffffffffu / uint32_t(W1) + 1u;
+            const int32_t nst = run * W1 * w2, sy = NC * f0;
+            const int64_t sz = int64_t(sy) * f1;
+            const FE_GLOBAL double *__restrict__ xo =
+                x + int64_t(NC) * ((cla - A[0].lo) + int64_t(f0) * ((cya - A[1].lo) + int64_t(f1) * (cl2 - A[2].lo)));
+            for (int32_t e0 = tid; e0 < nst; e0 += 4 * kQ1Block) {
+                double t[4];
 #pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    const int32_t pos = p0 + sub + t * LW;
-                    const bool ok = pos < len;
-                    const int32_t pc = ok ? pos : 0;
-                    const int32_t qy = int32_t((uint32_t(pc) * mx) >> 20);
-                    const int32_t xx = pc - qy * wx;
-                    const int32_t j2 = int32_t((uint32_t(qy) * my) >> 20);
-                    const int32_t j1 = qy - j2 * w1;
-                    // pc = 0 is in the row: an unconditional load, so an FP32 value's widening
-                    // does not make each load wait for the one before
-                    const VT raw = val[start + pc];
-                    a4[t] = ok ? double(raw) : 0.0;
-                    x4[t] = sx[(j2 * w1 + j1) * run + xoff + xx];
+                for (int u = 0; u < 4; u++) {
+                    const int32_t e = min(e0 + u * kQ1Block, nst - 1);
+                    const int32_t rr = run == 1 ? e : int32_t(__umulhi(uint32_t(e), mr));
+                    const int32_t jz = W1 == 1 ? rr : int32_t(__umulhi(uint32_t(rr), mw)), jy = rr - jz * W1;
+                    t[u] = xo[jz * sz + (e - rr * run + jy * sy)];
                 }
 #pragma unroll
-                for (int t = 0; t < 4; t++) sum += a4[t] * x4[t];
+                for (int u = 0; u < 4; u++)
+                    if (e0 + u * kQ1Block < nst) sx[e0 + u * kQ1Block] = t[u];
             }
         }
-        const double t = butterfly<LW>(sum);
-        if (live && sub == 0) f(row, t);
+        // this thread's group
+        const int32_t lrow = lr0 + gr * GR, t0 = lrow / NC, c0 = lrow - t0 * NC, t1 = ya + gj;
+        const bool live = gj < ny && lrow < lr1;
+        int32_t w0, cl0, P0, w1, cl1, P1;
+        axis_row(A[0], k, A[0].lo + t0, w0, cl0, P0);
+        axis_row(A[1], k, A[1].lo + t1, w1, cl1, P1);
+        const int32_t wx = w0 * NC, len = live ? wx * w1 * w2 : 0;
+        const int64_t S = int64_t(P2) * T1 * T0 + int64_t(w2) * P1 * T0 + int64_t(w2 * w1) * P0;
+        const FE_GLOBAL VT *__restrict__ row = val + (live ? int64_t(NC) * NC * S + int64_t(c0) * len : 0);
+        // positions p and p + 1 of the group's rows, one load each; the last
+        // position of a row of odd length comes as the second of its pair
+        // (a system of two or more rows has at least two entries in each);
+        // lanes past the end load the row's first pair and use neither
+        auto load = [&](int32_t p0, Pair (&v)[U][GR]) {
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int32_t p = p0 + 2 * L * u;
+                const int32_t pl = p < len ? (p == len - 1 ? p - 1 : p) : 0;
+#pragma unroll
+                for (int c = 0; c < GR; c++) v[u][c] = *reinterpret_cast<const FE_GLOBAL Pair *>(row + (c * len + pl));
+            }
+        };
+        Pair v[U][GR];
+        __syncthreads();
+        double acc[GR][2];
+#pragma unroll
+        for (int c = 0; c < GR; c++) acc[c][0] = acc[c][1] = 0.0;
+        const int32_t xoff = (cl1 - cya) * run + NC * (cl0 - cla);
+        // floor(p / d) = (p m) >> 20 for m in [2^20 / d, 2^20 / d + 8] (p < 2^12, d <= 27)
+        const uint32_t mx = uint32_t(1048576.0f * __builtin_amdgcn_rcpf(float(wx))) + 2u;
+        const uint32_t my = uint32_t(1048576.0f * __builtin_amdgcn_rcpf(float(w1))) + 2u;
+        const int32_t gx1 = run - wx, gx2 = (W1 - w1) * run;
+        auto slot = [&](int32_t p) {
+            const int32_t qy = int32_t((uint32_t(p) * mx) >> 20), jz = int32_t((uint32_t(qy) * my) >> 20);
+            return xoff + p + qy * gx1 + jz * gx2;
+        };
+        for (int32_t p0 = 2 * sub; p0 < len; p0 += 2 * L * U) {
+            load(p0, v);
+            double xv[U][2];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int32_t p = p0 + 2 * L * u;
+                const bool ok = p < len, odd = p == len - 1;
+                xv[u][0] = sx[slot(ok ? p : 0)];
+                xv[u][1] = sx[slot(ok && !odd ? p + 1 : 0)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int32_t p = p0 + 2 * L * u;
+                const bool ok = p < len, odd = p == len - 1;
+#pragma unroll
+                for (int c = 0; c < GR; c++) {
+                    const double a0 = ok ? double(odd ? v[u][c].y : v[u][c].x) : 0.0, a1 = ok && !odd ? double(v[u][c].y) : 0.0;
+                    acc[c][0] = fma(a0, xv[u][0], acc[c][0]);
+                    acc[c][1] = fma(a1, xv[u][1], acc[c][1]);
+                }
+            }
+        }
+        double out = 0.0;
+#pragma unroll
+        for (int c = 0; c < GR; c++) {
+            double v0 = acc[c][0], v1 = acc[c][1];
+#pragma unroll
+            for (int off = L / 2; off > 0; off >>= 1) {
+                v0 += __shfl_xor(v0, off, L);
+                v1 += __shfl_xor(v1, off, L);
+            }
+            if (sub == c) out = v0 + v1;
+        }
+        // x of the row itself (its diagonal column), for the caller's p . q
+        const int32_t sd = ((A[2].lo + t2 - cl2) * W1 + (A[1].lo + t1 - cya)) * run + NC * (A[0].lo + t0 - cla) + c0;
+        if (live && sub < GR) {
+            const int64_t r = (int64_t(t2) * f1 + t1) * rpl + lrow + sub;
+            if constexpr (std::is_invocable_v<Fn, int64_t, double, double>) f(r, out, sx[sd + sub]);
+            else f(r, out);
+        }
     }
 }
 
@@ -1354,6 +1478,8 @@ __device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const VT *__
         case 6108: FE_PLAN_CASE(6, 8, 1, BODY)                                                 \
         case 6208: FE_PLAN_CASE(6, 8, 2, BODY)                                                 \
         case 6308: FE_PLAN_CASE(6, 8, 3, BODY)                                                 \
+        case 6204: FE_PLAN_CASE(6, 4, 2, BODY)                                                 \
+        case 6304: FE_PLAN_CASE(6, 4, 3, BODY)                                                 \
         case 5127: FE_PLAN_CASE(5, 27, 1, BODY)                                                \
         case 5109: FE_PLAN_CASE(5, 9, 1, BODY)                                                 \
         case 4127: FE_PLAN_CASE(4, 27, 1, BODY)                                                \
@@ -1389,10 +1515,12 @@ __device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const VT *__
         if ((PL).mode == 7 || (PL).mode == 8) {                                                \
             FE_SYM_DISPATCH(PL, BODY)                                                          \
         } else if ((PL).mode == 6) {                                                           \
-            switch ((PL).nc) {                                                                 \
-                case 1: FE_PLAN_CASE(6, 8, 1, BODY)                                            \
-                case 2: FE_PLAN_CASE(6, 8, 2, BODY)                                            \
-                default: FE_PLAN_CASE(6, 8, 3, BODY)                                           \
+            switch ((PL).nc * 10 + (PL).rpb) {                                                 \
+                case 18: FE_PLAN_CASE(6, 8, 1, BODY)                                           \
+                case 28: FE_PLAN_CASE(6, 8, 2, BODY)                                           \
+                case 38: FE_PLAN_CASE(6, 8, 3, BODY)                                           \
+                case 24: FE_PLAN_CASE(6, 4, 2, BODY)                                           \
+                default: FE_PLAN_CASE(6, 4, 3, BODY)                                           \
             }                                                                                  \
         } else {                                                                               \
             FE_PLAN_DISPATCH(PL, BODY);                                                        \
@@ -1459,22 +1587,24 @@ static SpmvPlan struct_plan_of_class(const SpaceArgs &sa)
         pl.lanes = 2;
         return pl;
     }
-    // vector patterns and order 4: x of each 32-row chunk staged per block
-    // (measured on 2.6-4.0 M-row systems: elasticity Q2 / Q3 / Q4 996 / 1769 /
-    // 2889 us against 1033 / 1850 / 3080 us for the best lanes-per-row plan,
-    // scalar Q4 1910 against 2073 us)
-    if (sa.ncomp >= 2 || sa.k >= 4) {
-        pl.mode = 6;
+    // 2D patterns and Q1 vector rows: lanes per row, eight rows per wave (the
+    // staged box of short rows costs what it saves: 2D Q3 300^2 44 us against
+    // 53 block-staged, 2D Q2 elasticity 300 x 200 30 against 34, 3D Q1
+    // elasticity 40^3 25 against 25)
+    if (sa.dim == 2 || (sa.ncomp >= 2 && sa.k == 1)) {
+        pl.mode = 2;
         pl.rpb = 8;
         pl.lanes = 8;
         return pl;
     }
-    // scalar Q2-Q3: eight rows per wave step (8 lanes per row, the rest of a
-    // long row in further steps of 32 positions), measured fastest (the
-    // block-staged plan: 415 / 925 us against 358 / 862 us)
-    pl.mode = 2;
-    pl.rpb = 8;
-    pl.lanes = 8;
+    // 3D orders >= 2: x staged per block, the rows of a node together for
+    // vector problems (Q2 64^3 233 us against 357 with lanes per row, Q3 40^3
+    // 370 against 508, Q4 30^3 573 against 880; elasticity Q2 48^3 / Q3 32^3 /
+    // Q4 24^3 786 / 1298 / 2133 us with the rows of a node together, 864 /
+    // 1404 / 2853 row by row, 1106 / 2062 / 3413 with lanes per row)
+    pl.mode = 6;
+    pl.rpb = sa.ncomp >= 2 ? 4 : 8;
+    pl.lanes = xb_lanes(pl.rpb);
     return pl;
 }
 
@@ -1628,7 +1758,7 @@ __device__ __forceinline__ void for_rows_p(const PcgProb &P, const double *x, in
     else if constexpr (MODE == 7 || MODE == 8)
         for_rows_q1sym<RPB == 27 ? 3 : 2, MODE == 8>(P.sa, static_cast<const VT *>(P.val), x, lb, nb, f);
     else if constexpr (MODE == 6)
-        for_rows_xblock<NC, VT>(P.sa, static_cast<const VT *>(P.val), x, lb, nb, f);
+        for_rows_xblock<RPB, NC, VT>(P.sa, P.xb, static_cast<const VT *>(P.val), x, lb, nb, f);
     else if constexpr (MODE == 4 || MODE == 5)
         for_rows_q1<RPB == 27 ? 3 : 2, MODE == 5>(P.sa, static_cast<const double *>(P.val), x, lb, nb, f);
     else if constexpr (MODE == 3)
@@ -1759,7 +1889,8 @@ __global__ __launch_bounds__(rows_block(MODE)) void spmv_kernel(int64_t n, int64
 }
 
 template <int MODE, int RPB, int NC>
-__global__ __launch_bounds__(rows_block(MODE)) void spmv_struct_kernel(SpaceArgs sa, const double *__restrict__ val,
+__global__ __launch_bounds__(rows_block(MODE)) void spmv_struct_kernel(SpaceArgs sa, XbShape xb,
+                                                                        const double *__restrict__ val,
                                                                         const double *__restrict__ x,
                                                                         double *__restrict__ y)
 {
@@ -1770,7 +1901,7 @@ __global__ __launch_bounds__(rows_block(MODE)) void spmv_struct_kernel(SpaceArgs
         for_rows_q1sym<RPB == 27 ? 3 : 2, MODE == 8>(sa, val, x, xcd_block<MODE>(blockIdx.x, gridDim.x), gridDim.x,
                                                      [&](int64_t row, double s) { y[row] = s; });
     else if constexpr (MODE == 6)
-        for_rows_xblock<NC, double>(sa, val, x, blockIdx.x, gridDim.x, [&](int64_t row, double s) { y[row] = s; });
+        for_rows_xblock<RPB, NC, double>(sa, xb, val, x, blockIdx.x, gridDim.x, [&](int64_t row, double s) { y[row] = s; });
     else if constexpr (MODE == 4 || MODE == 5)
         for_rows_q1<RPB == 27 ? 3 : 2, MODE == 5>(sa, val, x, blockIdx.x, gridDim.x,
                                                   [&](int64_t row, double s) { y[row] = s; });
@@ -1846,10 +1977,10 @@ __global__ __launch_bounds__(rows_block(MODE)) void pcg_spmv_kernel(const PcgPro
     double v = 0.0;
     const FE_GLOBAL double *__restrict__ p = as_global(P.w.p);
     FE_GLOBAL double *__restrict__ q = as_global(P.w.q);
-    // the Q1 traversals (modes 4, 5, 7, 8) hand over p[row] from their LDS copy of p
+    // the traversals that stage x (modes 4 to 8) hand over p[row] from their LDS copy of p
     for_rows_p<MODE, RPB, NC, VT>(P, P.w.p, lb, nb, [&](int64_t row, double s, double prow = 0.0) {
                                 q[row] = s;
-                                v += (MODE == 4 || MODE == 5 || MODE == 7 || MODE == 8 ? prow : p[row]) * s;
+                                v += (MODE >= 4 && MODE <= 8 ? prow : p[row]) * s;
                             });
     // block partial: wave sums, then wave 0's lane 0 adds them in wave order
     __shared__ double wsum[rows_block(MODE) / 64];
@@ -2027,8 +2158,12 @@ __global__ __launch_bounds__(kBlock) void resid_finish_kernel(const PcgProb *__r
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-static int grid_rows(int64_t n, const SpmvPlan &pl)
+static int grid_rows(int64_t n, const SpmvPlan &pl, const XbShape &xb = XbShape{})
 {
+    if (pl.mode == 6) {  // a block per chunk, at most one per partial slot; a multiple of 8 (XCD-contiguous chunks)
+        const int64_t cap = part_slots(n) / 8 * 8;
+        return int((std::max<int64_t>(1, std::min<int64_t>(cap, xb.nchunks)) + 7) / 8 * 8);
+    }
     if (pl.mode == 10) {  // DG: a block per cell, at most one per partial slot; a multiple of 8 (XCD-contiguous cells)
         const int64_t ncells = n / pl.rpb;
         const int64_t cap = part_slots(n) / 8 * 8;
@@ -2039,8 +2174,8 @@ static int grid_rows(int64_t n, const SpmvPlan &pl)
         const int64_t cap = part_slots(n) / 8 * 8;
         return int((std::max<int64_t>(1, std::min<int64_t>(cap, tiles)) + 7) / 8 * 8);
     }
-    const int rows_per_run = pl.mode >= 7 ? 64 : pl.mode >= 3 ? 32 : pl.rpb;  // mode 6: a block per 32-row chunk
-    const int waves = pl.mode == 6 ? 1 : rows_block(pl.mode) / 64;
+    const int rows_per_run = pl.mode >= 7 ? 64 : pl.mode >= 3 ? 32 : pl.rpb;
+    const int waves = rows_block(pl.mode) / 64;
     const int64_t runs = (n + rows_per_run - 1) / rows_per_run;
     // the Q1 traversals: up to one block per partial slot (modes 5 and 8:
     // exactly one wave per step); the others: at most kGrid blocks
@@ -2222,7 +2357,8 @@ static std::vector<SpmvPlan> struct_candidates(const SpaceArgs &sa)
     for (int r : rpws) c.push_back(SpmvPlan{2, nc, r, 64 / r});
     if ((nc == 1 && (L == 27 || L == 9 || L == 25)) || (nc == 2 && L == 18)) c.push_back(SpmvPlan{3, nc, L, 2});
     if (nc == 1 && sa.k == 1) c.push_back(SpmvPlan{4, nc, L, 2});
-    else c.push_back(SpmvPlan{6, nc, 8, 8});
+    else c.push_back(SpmvPlan{6, nc, 8, xb_lanes(8)});
+    if (nc >= 2) c.push_back(SpmvPlan{6, nc, 4, xb_lanes(4)});
     return c;
 }
 
@@ -2246,10 +2382,11 @@ fe_status spmv_autotune_struct(const SpaceArgs &sa, const double *values, int re
     fe_status st = FE_OK;
     for (size_t c = 0; c < cand.size() && st == FE_OK; c++) {
         const SpmvPlan pl = aligned_form(launch_form(cand[c], n), values);
-        const int g = grid_rows(n, pl);
+        const XbShape xb = pl.mode == 6 ? xb_shape(sa, pl.rpb) : XbShape{};
+        const int g = grid_rows(n, pl, xb);
         for (int r = -1; r < reps; r++) {
             if (r == 0 && hipEventRecord(e0, s) != hipSuccess) st = set_error(FE_EDEVICE, "event record failed");
-            FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, values, x, y)));
+            FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), xb.lds, s>>>(sa, xb, values, x, y)));
         }
         float ms = 0.0f;
         if (hipGetLastError() != hipSuccess || hipEventRecord(e1, s) != hipSuccess ||
@@ -2334,6 +2471,7 @@ struct Group {
     int first, count;  // problems [first, first + count) of the sorted table
     int32_t *d_boff;   // count + 1 block offsets of the row kernels
     int grid;
+    int lds;           // bytes of dynamic LDS (mode 6: the largest staged box of the group)
 };
 
 // A set of problems launched together: the device table is sorted by (SpMV
@@ -2360,13 +2498,13 @@ const PcgJob &engine_job(const EngineSet &E, int t) { return E.jobs[t]; }
 #define FE_ROWS_KERNELS(DISPATCH, VT)                                                                                \
     switch (which) {                                                                                                  \
         case 0:                                                                                                       \
-            DISPATCH(g.pl, (pcg_init_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), 0, s>>>(tp, g.d_boff, g.count))); \
+            DISPATCH(g.pl, (pcg_init_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), g.lds, s>>>(tp, g.d_boff, g.count))); \
             break;                                                                                                    \
         case 1:                                                                                                       \
-            DISPATCH(g.pl, (pcg_spmv_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), 0, s>>>(tp, g.d_boff, g.count))); \
+            DISPATCH(g.pl, (pcg_spmv_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), g.lds, s>>>(tp, g.d_boff, g.count))); \
             break;                                                                                                    \
         default:                                                                                                      \
-            DISPATCH(g.pl, (resid_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), 0, s>>>(tp, g.d_boff, g.count))); \
+            DISPATCH(g.pl, (resid_kernel<kMode, kRpb, kNc, VT><<<dim3(g.grid), dim3(rows_block(kMode)), g.lds, s>>>(tp, g.d_boff, g.count))); \
             break;                                                                                                    \
     }
 
@@ -2388,7 +2526,7 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         if (jobs[i].dg)  // DG: the cell-block traversal
             plans[i] = SpmvPlan{10, jobs[i].sa->dim, jobs[i].sa->nn, 0};
         else if (jobs[i].sa && jobs[i].fp32 && !jobs[i].sym)  // FP32 values: the block-staged traversal
-            plans[i] = SpmvPlan{6, jobs[i].sa->ncomp, 8, 8};
+            plans[i] = SpmvPlan{6, jobs[i].sa->ncomp, jobs[i].sa->ncomp >= 2 ? 4 : 8, 0};
         else if (jobs[i].sym)
             plans[i] = launch_form(SpmvPlan{7, 1, jobs[i].sa->dim == 3 ? 27 : 9, 2}, jobs[i].n);
         else
@@ -2435,7 +2573,8 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         P.maxit = jb.maxit;
         if (jb.sa) P.sa = *jb.sa;
         const SpmvPlan &pl = plans[order[t]];
-        P.nbr = grid_rows(jb.n, pl);
+        if (pl.mode == 6) P.xb = xb_shape(*jb.sa, pl.rpb);
+        P.nbr = grid_rows(jb.n, pl, P.xb);
         P.nbe = grid_elems(jb.n);
         E.hi[t] = eoff;
         eoff += P.nbe;
@@ -2448,6 +2587,7 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
             E.groups.push_back(g);
         }
         E.groups.back().count++;
+        E.groups.back().lds = std::max(E.groups.back().lds, int(P.xb.lds));
     }
     E.hi[np] = eoff;
     E.ge = eoff;
@@ -2776,7 +2916,7 @@ fe_status launch_spmv_sym(const SpaceArgs &sa, const double *sym, const double *
     if (sa.n_rows == 0) return FE_OK;
     const SpmvPlan pl = launch_form(SpmvPlan{7, 1, sa.dim == 3 ? 27 : 9, 2}, sa.n_rows);
     const int g = grid_rows(sa.n_rows, pl);
-    FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, sym, x, y)));
+    FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, XbShape{}, sym, x, y)));
     FE_HIP(hipGetLastError());
     return FE_OK;
 }
@@ -2792,8 +2932,9 @@ fe_status launch_spmv_struct(const SpaceArgs &sa, const double *val, const doubl
 {
     if (sa.n_rows == 0) return FE_OK;
     const SpmvPlan pl = aligned_form(struct_plan(sa), val);
-    const int g = grid_rows(sa.n_rows, pl);
-    FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, val, x, y)));
+    const XbShape xb = pl.mode == 6 ? xb_shape(sa, pl.rpb) : XbShape{};
+    const int g = grid_rows(sa.n_rows, pl, xb);
+    FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), xb.lds, s>>>(sa, xb, val, x, y)));
     FE_HIP(hipGetLastError());
     return FE_OK;
 }
@@ -2803,7 +2944,7 @@ fe_status launch_spmv_dg(const SpaceArgs &sa, const double *val, const double *x
     if (sa.n_rows == 0) return FE_OK;
     const SpmvPlan pl{10, sa.dim, sa.nn, 0};
     const int g = grid_rows(sa.n_rows, pl);
-    FE_DG_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, val, x, y)));
+    FE_DG_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(sa, XbShape{}, val, x, y)));
     FE_HIP(hipGetLastError());
     return FE_OK;
 }

@@ -341,3 +341,50 @@ def test_mesh_traversals_accept_values_off_16_byte_boundaries(dim, n, k, prob):
     assert iw["status"] == F.FE_OK and iw["iters"] == ia["iters"] and torch.equal(ua, uw)
     with pytest.raises(F.FeError, match="8-byte"):
         F.pcg_solve_mesh(pair.mesh, k, pair.coeff, A.csr, A.rhs, uw, 1e-10, 20000, wb[4 : 4 + ws.numel()])
+
+
+# The block-staged traversal that takes the rows of a node together (mode 6
+# with four nodes per wave): lines of fewer, exactly and more than its 16 nodes
+# per chunk, several lines per chunk, free and clamped ends, odd and even row
+# lengths, two and three components.
+@pytest.mark.parametrize("dim,n,k,prob,faces", [(3, [9, 3, 2], 2, "elasticity", None), (3, [8, 2, 2], 2, "elasticity", 0b000001),
+                                                (3, [2, 5, 3], 3, "elasticity", 0), (3, [5, 2, 3], 4, "elasticity", 0b111101),
+                                                (3, [1, 1, 1], 2, "elasticity", None), (3, [4, 4, 3], 1, "elasticity", None),
+                                                (2, [21, 3], 2, "elasticity", None), (2, [2, 9], 4, "elasticity", 0b0001)])
+def test_node_grouped_traversal_matches_oracle(dim, n, k, prob, faces):
+    pair = Pair(dim, n, k, prob, faces=faces, seed=71)
+    A = pair.gpu_assembly()
+    say(f"[node groups] dim {dim} n {n} k {k} faces {faces} rows {A.n_rows}")
+    x = np.random.Generator(np.random.PCG64(72)).standard_normal(A.n_rows)
+    xd = torch.from_numpy(x).cuda()
+    y = torch.empty_like(xd)
+    F.spmv_tuning_reset()
+    try:
+        F.spmv_plan_set_mesh(pair.mesh, k, pair.coeff, 6, 4)
+        F.spmv_mesh(pair.mesh, k, pair.coeff, A.csr, xd, y)
+        u = torch.zeros_like(xd)
+        if faces != 0:
+            ws = torch.empty(F.pcg_query(A.n_rows), dtype=torch.uint8, device="cuda")
+            info = A.solve(u, 1e-10, 20000, ws)
+            assert info["status"] == F.FE_OK
+        torch.cuda.synchronize()
+    finally:
+        F.spmv_tuning_reset()
+    S = pair.system
+    yo = O.spmv(S.rowptr, S.colind, S.values, x)
+    scale = O.spmv(S.rowptr, S.colind, np.abs(S.values), np.abs(x))
+    assert np.all(np.abs(y.cpu().numpy() - yo) <= 1e-12 * scale + 1e-300)
+    if faces != 0:
+        assert rel(u.cpu().numpy(), spla.spsolve(S.scipy().tocsc(), S.rhs)) <= 1e-8
+
+
+def test_block_staged_traversal_of_a_single_row():
+    """One unknown: no pair of values to load."""
+    pair = Pair(3, [1, 1, 1], 2, seed=73)
+    A = pair.gpu_assembly()
+    assert A.n_rows == 1 and A.nnz == 1
+    x = torch.full((1,), 3.0, dtype=torch.float64, device="cuda")
+    y = torch.empty_like(x)
+    F.spmv_mesh(pair.mesh, 2, pair.coeff, A.csr, x, y)
+    torch.cuda.synchronize()
+    assert float(y) == 3.0 * float(A.values[0])
