@@ -2251,6 +2251,39 @@ struct PinnedState {
     }
 };
 
+// Two stop counters in pinned memory and an event for each, per thread: the
+// engine reads a chunk's counter while the next chunk runs.  Events belong to
+// the device they were made on and are made anew when the thread changes it.
+struct StopSlots {
+    int32_t *h = nullptr;  // counters at h[0] and h[16]
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    int dev = -1;
+    void drop()
+    {
+        for (hipEvent_t &e : ev) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
+        }
+    }
+    fe_status ready()
+    {
+        int d = 0;
+        FE_HIP(hipGetDevice(&d));
+        if (!h) FE_HIP(hipHostMalloc(reinterpret_cast<void **>(&h), 32 * sizeof(int32_t), hipHostMallocDefault));
+        if (d != dev || !ev[0] || !ev[1]) {
+            drop();
+            for (hipEvent_t &e : ev) FE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            dev = d;
+        }
+        return FE_OK;
+    }
+    ~StopSlots()
+    {
+        drop();
+        if (h) (void)hipHostFree(h);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // SpMV autotuner: times every plan on a matrix and keeps the fastest for the
 // matrix's row-length class.
@@ -2437,19 +2470,14 @@ void spmv_plan_of_struct(const SpaceArgs &sa, fe_spmv_plan *plan, int32_t *cls)
 // vector kernels serve all problems in one launch.  Chunks of iterations are
 // launched directly or replayed from a captured HIP graph.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void count_active_kernel(const PcgProb *__restrict__ probs, int nprob,
-                                                               int32_t *active)
+__global__ __launch_bounds__(64) void count_active_kernel(const PcgProb *__restrict__ probs, int nprob,
+                                                           int32_t *active)
 {
-    __shared__ int32_t cnt[kBlock];
     int32_t c = 0;
-    for (int i = threadIdx.x; i < nprob; i += kBlock) c += pcg_stopped(*probs[i].w.st, probs[i].w.st->iter) ? 0 : 1;
-    cnt[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int32_t t = 0;
-        for (int i = 0; i < kBlock; i++) t += cnt[i];
-        *active = t;
-    }
+    for (int i = threadIdx.x; i < nprob; i += 64) c += pcg_stopped(*probs[i].w.st, probs[i].w.st->iter) ? 0 : 1;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+    if (threadIdx.x == 0) *active = c;
 }
 
 __global__ __launch_bounds__(kBlock) void gather_states_kernel(const PcgProb *__restrict__ probs, int nprob,
@@ -2710,15 +2738,12 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
     int maxit = 0;
     for (const PcgJob &jb : E.jobs) maxit = std::max(maxit, jb.maxit);
 
-    static thread_local PinnedState pin;
-    int32_t pageable_active = 0;
-    int32_t *h_active = &pageable_active;
-    if (no_alloc) {
-        use_graph = false;
-    } else {
-        if (!pin.h) FE_HIP(hipHostMalloc(reinterpret_cast<void **>(&pin.h), sizeof(PcgState), hipHostMallocDefault));
-        h_active = reinterpret_cast<int32_t *>(pin.h);
-    }
+    // The stop counter is written by the device into pinned memory and read
+    // one chunk behind, so the device never waits for the host; a solve that
+    // may not allocate reads it after every chunk into pageable memory.
+    static thread_local StopSlots slots;
+    if (no_alloc) use_graph = false;
+    else if ((st = slots.ready()) != FE_OK) return st;
     const bool timed = timing_on() && !use_graph && !no_alloc && np == 1;
     // SpMV launches timed: every kTimeEvery-th iteration (an event pair costs a
     // few microseconds of device time, which around every launch lengthened
@@ -2742,29 +2767,43 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         if (st != FE_OK) return st;
         FE_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
         for (int i = 0; i < gchunk; i++) engine_iteration(E, cs, nullptr);
-        hipLaunchKernelGGL(count_active_kernel, dim3(1), dim3(kBlock), 0, cs, E.d_probs, np, E.d_active);
         if (hipStreamEndCapture(cs, &hold.g) != hipSuccess) return set_error(FE_EDEVICE, "graph capture failed");
         if (hipGraphInstantiate(&hold.e, hold.g, nullptr, nullptr, 0) != hipSuccess)
             return set_error(FE_EDEVICE, "graph instantiation failed");
     }
     int j = 0, chunk = 8;
-    while (j < maxit) {
-        if (hold.e) {
-            FE_HIP(hipGraphLaunch(hold.e, s));
-            j += gchunk;
-        } else {
-            for (int i = 0; i < chunk && j < maxit; i++, j++) {
-                const bool mark = timed && j % kTimeEvery == 0;
-                engine_iteration(E, s, mark ? &marks : nullptr);
-                mark_iter.resize(marks.size(), j);
+    for (int c = 0;; c++) {
+        const bool more = j < maxit;
+        if (more) {
+            if (hold.e) {
+                FE_HIP(hipGraphLaunch(hold.e, s));
+                j += gchunk;
+            } else {
+                for (int i = 0; i < chunk && j < maxit; i++, j++) {
+                    const bool mark = timed && j % kTimeEvery == 0;
+                    engine_iteration(E, s, mark ? &marks : nullptr);
+                    mark_iter.resize(marks.size(), j);
+                }
+                if (no_alloc && chunk < 128) chunk *= 2;
             }
-            hipLaunchKernelGGL(count_active_kernel, dim3(1), dim3(kBlock), 0, s, E.d_probs, np, E.d_active);
-            if (chunk < 128) chunk *= 2;
+            int32_t *out = no_alloc ? E.d_active : slots.h + 16 * (c & 1);
+            hipLaunchKernelGGL(count_active_kernel, dim3(1), dim3(64), 0, s, E.d_probs, np, out);
+            FE_HIP(hipGetLastError());
+            if (!no_alloc) FE_HIP(hipEventRecord(slots.ev[c & 1], s));
         }
-        FE_HIP(hipGetLastError());
-        FE_HIP(hipMemcpyAsync(h_active, E.d_active, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        FE_HIP(hipStreamSynchronize(s));
-        if (*h_active == 0) break;
+        if (no_alloc) {
+            int32_t active = 0;
+            if (!more) break;
+            FE_HIP(hipMemcpyAsync(&active, E.d_active, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            FE_HIP(hipStreamSynchronize(s));
+            if (active == 0) break;
+        } else {  // the chunk before this one
+            if (c > 0) {
+                FE_HIP(hipEventSynchronize(slots.ev[(c - 1) & 1]));
+                if (*static_cast<volatile int32_t *>(slots.h + 16 * ((c - 1) & 1)) == 0) break;
+            }
+            if (!more) break;
+        }
     }
     st = engine_finish(E, s);
     if (st != FE_OK) return st;
@@ -2814,9 +2853,7 @@ static fe_status pcg_run(int64_t n, int64_t nnz, const int64_t *rowptr, const in
     jobs[0] = PcgJob{n, nnz, rowptr, colind, val, std::is_same<VT, float>::value, dinv, b, x, ws, info, rtol, maxit, sa,
                      sym, dg};
     void *table = static_cast<char *>(ws) + pcg_ws_bytes(n);
-    // small systems are launch-bound: replay the iterations from a HIP graph
-    const bool graph = n < (int64_t(1) << 18);
-    return pcg_engine(jobs, table, graph, s);
+    return pcg_engine(jobs, table, false, s);
 }
 
 fe_status pcg_solve(const fe_csr *A, const double *b, double *x, double rtol, int maxit, void *ws, size_t ws_bytes,
