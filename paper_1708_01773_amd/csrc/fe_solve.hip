@@ -104,6 +104,16 @@ struct XbShape {
     int32_t lds = 0;  // bytes of the staged box
 };
 
+// How a small system is held by the one-workgroup solver (pcg_small_kernel).
+enum SmallKind { kSmallNone = 0, kSmallCsr = 1, kSmallStruct = 2, kSmallSym = 3 };
+struct SmallPlan {
+    int32_t kind = kSmallNone;  // where values and columns come from
+    int32_t lanes = 1;          // lanes per row
+    int32_t resident = 0;       // the values stay in LDS too
+    int32_t regs = 0;           // a row per lane group: the matrix may be held in registers
+    int32_t lds = 0;            // bytes of LDS
+};
+
 // One problem of a (possibly batched) solve, as the kernels see it.
 struct PcgProb {
     int64_t n, nnz;
@@ -118,6 +128,8 @@ struct PcgProb {
     int32_t nbr, nbe;  // blocks of the row kernels / of the vector kernels
     SpaceArgs sa;      // pattern of a system assembled on a structured brick (mode 2)
     XbShape xb;        // its chunks (mode 6)
+    SmallPlan small;   // one-workgroup iterations, if the system takes them
+    int32_t turn;      // every other iteration takes the row blocks in the reverse order (see alternates)
 };
 
 // How a CSR matrix is traversed.
@@ -1973,6 +1985,8 @@ __global__ __launch_bounds__(rows_block(MODE)) void pcg_spmv_kernel(const PcgPro
     int64_t lb, nb;
     const PcgProb &P = probs[find_problem(boff, nprob, lb, nb)];
     if (pcg_stopped(*P.w.st, P.w.st->iter)) return;
+    if constexpr (MODE >= 5 && MODE <= 8)  // in reverse, each block on its XCD where the mode deals them by XCD
+        if (P.turn && (P.w.st->iter & 1)) lb = MODE >= 6 ? (nb / 8 - 1 - lb / 8) * 8 + lb % 8 : nb - 1 - lb;
     lb = xcd_block<MODE>(lb, nb);
     double v = 0.0;
     const FE_GLOBAL double *__restrict__ p = as_global(P.w.p);
@@ -2129,6 +2143,314 @@ __global__ __launch_bounds__(kBlock) void pcg_dir_kernel(const PcgProb *__restri
     });
 }
 
+// ---------------------------------------------------------------------------
+// Small systems: all iterations in one workgroup.
+// An iteration of the three kernels takes 14-16 us whatever the size (three
+// launches, and in each a chain of dependent loads: table, state, partials,
+// vectors).  A system whose pattern fits LDS runs in one workgroup of 1024
+// threads instead: the direction p, the product q and the columns (16 bits
+// each) stay in LDS, with the values where they fit too, r, x and the Jacobi
+// diagonal in registers, and the barriers of the workgroup take the place of
+// the kernel boundaries.  A system that gives every thread at most one row (or
+// a lane's share of one) of at most 16 entries holds its matrix in registers
+// (REGS), so that a product reads nothing but the gathered p from LDS.  What bounds it is LDS and barrier
+// latency, or the values from L2 at the rate one CU reads.  Scalars, stop test and state
+// are those of the three kernels, so a launch may take any number of
+// iterations and the next go on from the state.
+// The matrix comes from the CSR arrays, from the values in CSR order with the
+// columns evaluated, or from the symmetric storage of a Q1 scalar system.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallElems = 4;  // elements of each vector per thread
+constexpr int kSmallRegs = 16;  // matrix entries per thread held in registers
+constexpr int64_t kSmallMaxRows = kSmallThreads * kSmallElems;
+constexpr int64_t kSmallLds = 156 * 1024;  // of the 160 KB of a CU; the rest for the static part
+
+__host__ __device__ constexpr int64_t align16(int64_t b) { return (b + 15) / 16 * 16; }
+
+// p, q | row starts | columns | values (when resident)
+__host__ __device__ constexpr int64_t small_bytes(int64_t n, int64_t nnz, int64_t resident_value)
+{
+    return align16(16 * n) + align16(4 * (n + 1)) + align16(2 * nnz) + align16(resident_value * nnz);
+}
+
+// Sum over the wave, the same in every lane, without LDS: quads, then halves
+// and rows of 16 by mirrored moves, then the four rows through scalar
+// registers (a butterfly of lane exchanges through LDS has six dependent
+// round trips).
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v)
+{
+    const uint64_t u = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(int(uint32_t(u)), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(int(uint32_t(u >> 32)), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((uint64_t(uint32_t(hi)) << 32) | uint32_t(lo));
+}
+__device__ __forceinline__ double lane_read(double v, int lane)
+{
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u)), lane));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(u >> 32)), lane));
+    return __longlong_as_double((uint64_t(hi) << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v += lane_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v += lane_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v += lane_move<0x141>(v);  // row_half_mirror
+    v += lane_move<0x140>(v);  // row_mirror
+    return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
+}
+
+// Sums over the workgroup, the same in every thread; slots of alternating
+// calls differ, so one barrier per call is enough.
+template <int NV>
+__device__ __forceinline__ void small_sum(double (&v)[NV], double (&sh)[2][NV][kSmallThreads / 64], int flip)
+{
+#pragma unroll
+    for (int t = 0; t < NV; t++) {
+        const double w = wave_sum(v[t]);
+        if (threadIdx.x % 64 == 0) sh[flip][t][threadIdx.x / 64] = w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NV; t++) {
+        const double *h = sh[flip][t];
+        double a[4];
+#pragma unroll
+        for (int w = 0; w < 4; w++) a[w] = (h[w] + h[4 + w]) + (h[8 + w] + h[12 + w]);
+        v[t] = (a[0] + a[1]) + (a[2] + a[3]);
+    }
+}
+
+template <typename VT, bool REGS>
+__global__ __launch_bounds__(kSmallThreads) void pcg_small_kernel(const PcgProb *__restrict__ probs, int iters)
+{
+    constexpr int kElems = REGS ? 1 : kSmallElems;  // REGS: at most one row per thread
+    extern __shared__ double fe_small_lds[];
+    __shared__ int longest;
+    __shared__ double sh1[2][1][kSmallThreads / 64], sh2[2][2][kSmallThreads / 64];
+    const PcgProb &P = probs[blockIdx.x];
+    PcgState *st = P.w.st;
+    int j = st->iter;
+    if (pcg_stopped(*st, j)) return;
+    const int tid = threadIdx.x, n = int(P.n), nnz = int(P.nnz);
+    const SmallPlan sm = P.small;
+    char *lds = reinterpret_cast<char *>(fe_small_lds);
+    double *sp = fe_small_lds, *sq = sp + n;
+    lds += align16(16 * int64_t(n));
+    uint32_t *sstart = reinterpret_cast<uint32_t *>(lds);
+    lds += align16(4 * int64_t(n + 1));
+    uint16_t *scol = reinterpret_cast<uint16_t *>(lds);
+    lds += align16(2 * int64_t(nnz));
+    VT *sval = reinterpret_cast<VT *>(lds);
+    const FE_GLOBAL VT *__restrict__ gval = as_global(static_cast<const VT *>(P.val));
+    const int LW = sm.lanes, sub = tid % LW, rpp = kSmallThreads / LW;
+    // the pattern (and the resident values), a row per lane group
+    if (sm.kind == kSmallCsr) {
+        const FE_GLOBAL int64_t *__restrict__ rowptr = as_global(P.rowptr);
+        const FE_GLOBAL int32_t *__restrict__ colind = as_global(P.colind);
+        for (int i = tid; i <= n; i += kSmallThreads) sstart[i] = uint32_t(rowptr[i]);
+        for (int e = tid; e < nnz; e += kSmallThreads) {
+            scol[e] = uint16_t(colind[e]);
+            if (sm.resident) sval[e] = gval[e];
+        }
+    } else {
+        const SpaceArgs &s = P.sa;
+        const int32_t k = s.k, nc = s.ncomp;
+        AxisClosed A[3];
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            A[r].lo = int32_t(s.ax[r].lo);
+            A[r].hi = int32_t(s.ax[r].lo + s.ax[r].f - 1);
+            A[r].N = int32_t(s.ax[r].N);
+            A[r].swlo = A[r].lo * (k + 1) + k * ((A[r].lo + k - 1) / k);
+        }
+        const int32_t f0 = int32_t(s.ax[0].f), f1 = int32_t(s.ax[1].f);
+        const int32_t T0 = int32_t(s.ax[0].T), T1 = int32_t(s.ax[1].T), ns = int32_t(sym_stride(n));
+        for (int row = tid / LW; row < n; row += rpp) {
+            const int32_t R = row / nc, c = row - R * nc;
+            const int32_t q = R / f0, t0 = R - q * f0, t2 = q / f1, t1 = q - t2 * f1;
+            int32_t w0, w1, w2, cl0, cl1, cl2, P0, P1, P2;
+            axis_row(A[0], k, A[0].lo + t0, w0, cl0, P0);
+            axis_row(A[1], k, A[1].lo + t1, w1, cl1, P1);
+            axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
+            const int32_t S = P2 * T1 * T0 + w2 * P1 * T0 + w2 * w1 * P0;
+            const int32_t wx = w0 * nc, len = wx * w1 * w2, start = nc * nc * S + c * len;
+            if (sub == 0) {
+                sstart[row] = uint32_t(start);
+                if (row == n - 1) sstart[n] = uint32_t(start + len);
+            }
+            for (int e = sub; e < len; e += LW) {
+                const int32_t qy = e / wx, j2 = qy / w1, j1 = qy - j2 * w1;
+                const int32_t col = nc * ((cl0 - A[0].lo) + f0 * ((cl1 + j1 - A[1].lo) + f1 * (cl2 + j2 - A[2].lo))) +
+                                    (e - qy * wx);
+                scol[start + e] = uint16_t(col);
+                if (sm.kind == kSmallSym) {  // entry (row, col) is slot |code - centre| of the lower of the two rows
+                    const int32_t d0 = cl0 + (e - qy * wx) - A[0].lo - t0, d1 = cl1 + j1 - A[1].lo - t1;
+                    const int32_t d2 = cl2 + j2 - A[2].lo - t2, g = 9 * d2 + 3 * d1 + d0;
+                    sval[start + e] = gval[g >= 0 ? g * ns + row : -g * ns + col];
+                } else if (sm.resident) {
+                    sval[start + e] = gval[start + e];
+                }
+            }
+        }
+    }
+    // the vectors
+    double r[kElems], x[kElems], d[kElems];
+    const FE_GLOBAL double *__restrict__ gr = as_global(P.w.r);
+    const FE_GLOBAL double *__restrict__ gp = as_global(P.w.p);
+    const FE_GLOBAL double *__restrict__ gd = as_global(P.dinv);
+    const FE_GLOBAL double *__restrict__ gx = as_global(P.x);
+#pragma unroll
+    for (int u = 0; u < kElems; u++) {
+        const int e = tid + u * kSmallThreads;
+        r[u] = x[u] = d[u] = 0.0;
+        if (e < n) {
+            r[u] = gr[e];
+            x[u] = gx[e];
+            d[u] = gd[e];
+            sp[e] = gp[e];
+        }
+    }
+    double rho = st->rho[j & 1], rr = st->rr, alpha = 0.0;
+    const double bound = P.rtol2 * st->bb;
+    const int maxit = P.maxit;
+    __syncthreads();
+    // this thread's part of its row (REGS: one row per lane group); an unused
+    // slot is a zero times the row's own p
+    double rm[REGS ? kSmallRegs : 1];
+    uint16_t rcol[REGS ? kSmallRegs : 1];
+    const int myrow = min(tid / LW, n - 1);
+    int per = 0;  // slots used; 0: a row is longer than the registers hold
+    if constexpr (REGS) {
+        const int b = int(sstart[myrow]) + sub, e = tid / LW < n ? int(sstart[myrow + 1]) : 0;
+        if (tid == 0) longest = 0;
+        __syncthreads();
+        if (sub == 0 && e > b) atomicMax(&longest, e - b);
+        __syncthreads();
+        per = (longest + LW - 1) / LW;
+        if (per > kSmallRegs) per = 0;
+#pragma unroll
+        for (int u = 0; u < kSmallRegs; u++) {
+            const int t = b + u * LW;
+            rm[u] = t < e ? double(sval[t]) : 0.0;
+            rcol[u] = t < e ? scol[t] : uint16_t(myrow);
+        }
+    }
+    int stop = 0, status = FE_OK;
+    for (int it = 0; it < iters && !stop; it++) {
+        const int flip = it & 1;
+        // q = A p, p . q
+        double v1[1] = {0.0};
+        auto rows = [&](const auto *val) {
+            for (int r0 = 0; r0 < n; r0 += rpp) {
+                const int row = r0 + tid / LW;
+                double a = 0.0;
+                if (row < n) {
+                    const int b = int(sstart[row]), e = int(sstart[row + 1]);
+                    int t = b + sub;
+                    for (; t + 3 * LW < e; t += 4 * LW) {
+                        double m[4], xx[4];
+#pragma unroll
+                        for (int u = 0; u < 4; u++) {
+                            m[u] = double(val[t + u * LW]);
+                            xx[u] = sp[scol[t + u * LW]];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; u++) a = fma(m[u], xx[u], a);
+                    }
+                    for (; t < e; t += LW) a = fma(double(val[t]), sp[scol[t]], a);
+                }
+                for (int off = LW / 2; off > 0; off >>= 1) a += __shfl_xor(a, off);
+                if (row < n && sub == 0) {
+                    sq[row] = a;
+                    v1[0] = fma(sp[row], a, v1[0]);
+                }
+            }
+        };
+        bool done = false;
+        if constexpr (REGS) if (per > 0) {
+            done = true;
+            double a[2] = {0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < kSmallRegs; u++)
+                if (u < per) a[u & 1] = fma(rm[u], sp[rcol[u]], a[u & 1]);
+            a[0] += a[1];
+            for (int off = LW / 2; off > 0; off >>= 1) a[0] += __shfl_xor(a[0], off);
+            if (tid / LW < n && sub == 0) {
+                sq[myrow] = a[0];
+                v1[0] = sp[myrow] * a[0];
+            }
+        }
+        if (!done) {
+            if (REGS || sm.resident) rows(sval);
+            else rows(gval);
+        }
+        small_sum<1>(v1, sh1, flip);  // its barrier also makes q visible
+        if (!(v1[0] > 0.0) || !isfinite(v1[0])) {
+            stop = 2;
+            status = FE_EBREAKDOWN;
+            break;
+        }
+        alpha = rho / v1[0];
+        double v2[2] = {0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < kElems; u++) {
+            const int e = tid + u * kSmallThreads;
+            if (e < n) {
+                r[u] = fma(-alpha, sq[e], r[u]);
+                v2[0] = fma(r[u], d[u] * r[u], v2[0]);
+                v2[1] = fma(r[u], r[u], v2[1]);
+            }
+        }
+        small_sum<2>(v2, sh2, flip);
+        const double beta = v2[0] / rho;
+        const bool conv = v2[1] <= bound;
+        rho = v2[0];
+        rr = v2[1];
+        if (tid == 0 && j < kHist) {
+            P.w.hist[j] = alpha;
+            P.w.hist[kHist + j] = beta;
+        }
+#pragma unroll
+        for (int u = 0; u < kElems; u++) {
+            const int e = tid + u * kSmallThreads;
+            if (e < n) {
+                const double pe = sp[e];
+                x[u] = fma(alpha, pe, x[u]);
+                if (!conv) sp[e] = fma(beta, pe, d[u] * r[u]);
+            }
+        }
+        if (conv) stop = 1;
+        else if (j + 1 >= maxit) {
+            stop = 1;
+            status = FE_ENOTCONV;
+        }
+        j++;
+        __syncthreads();  // p for the next product
+    }
+#pragma unroll
+    for (int u = 0; u < kElems; u++) {
+        const int e = tid + u * kSmallThreads;
+        if (e < n) {
+            P.w.r[e] = r[u];
+            P.w.p[e] = sp[e];
+            P.x[e] = x[u];
+        }
+    }
+    if (tid == 0) {
+        st->rho[j & 1] = rho;
+        st->rr = rr;
+        st->iter = j;
+        st->iter_upd = j;
+        st->alpha = alpha;
+        st->status = status;
+        if (stop == 1) st->stop_at = j - 1;
+        if (stop == 2) st->done = 1;
+    }
+}
+
 // partials of (b - A x)^2
 template <int MODE, int RPB, int NC, typename VT>
 __global__ __launch_bounds__(rows_block(MODE)) void resid_kernel(const PcgProb *__restrict__ probs,
@@ -2208,39 +2530,40 @@ fe_status launch_spmv(int64_t n, const int64_t *rowptr, const int32_t *colind, c
 
 // Smallest / largest eigenvalue of the symmetric tridiagonal (d, e) by
 // bisection on Sturm sequence counts.
-static int sturm_count(const std::vector<double> &d, const std::vector<double> &e, double x)
-{
-    int cnt = 0;
-    double q = 1.0;
-    for (size_t i = 0; i < d.size(); i++) {
-        const double off = i > 0 ? e[i - 1] * e[i - 1] : 0.0;
-        q = d[i] - x - (i > 0 ? off / q : 0.0);
-        if (q == 0.0) q = -1e-300;
-        if (q < 0) cnt++;
-    }
-    return cnt;
-}
-
+// Extremal eigenvalues of the symmetric tridiagonal matrix (d, e) by bisection
+// on the signs of its pivots: an eigenvalue lies below x if a pivot of
+// T - x is negative, none at or above x if all are.  Both ends are bisected
+// together, one pass over the pivots a step, left as soon as both are decided.
 static void tridiag_extremes(const std::vector<double> &d, const std::vector<double> &e, double &lmin, double &lmax)
 {
     const size_t m = d.size();
     double lo = d[0], hi = d[0];
+    std::vector<double> off(m, 0.0);
     for (size_t i = 0; i < m; i++) {
         const double r = (i > 0 ? std::fabs(e[i - 1]) : 0.0) + (i + 1 < m ? std::fabs(e[i]) : 0.0);
         lo = std::fmin(lo, d[i] - r);
         hi = std::fmax(hi, d[i] + r);
+        if (i > 0) off[i] = e[i - 1] * e[i - 1];
     }
-    auto kth = [&](int k) {
-        double a = lo, b = hi;
-        for (int it = 0; it < 200 && b - a > 1e-14 * std::fmax(std::fabs(a), std::fabs(b)); it++) {
-            const double mid = 0.5 * (a + b);
-            if (sturm_count(d, e, mid) >= k) b = mid;
-            else a = mid;
+    double a[2] = {lo, lo}, b[2] = {hi, hi};  // brackets of the smallest and the largest
+    auto open = [&](int k) { return b[k] - a[k] > 1e-14 * std::fmax(std::fabs(a[k]), std::fabs(b[k])); };
+    for (int it = 0; it < 200 && (open(0) || open(1)); it++) {
+        const double x0 = 0.5 * (a[0] + b[0]), x1 = 0.5 * (a[1] + b[1]);
+        double q0 = 1.0, q1 = 1.0;
+        bool any = false, all = true;  // a negative pivot at x0; only negative pivots at x1
+        for (size_t i = 0; i < m && (!any || all); i++) {
+            q0 = d[i] - x0 - off[i] / q0;
+            q1 = d[i] - x1 - off[i] / q1;
+            if (q0 == 0.0) q0 = -1e-300;
+            if (q1 == 0.0) q1 = -1e-300;
+            any = any || q0 < 0;
+            all = all && q1 < 0;
         }
-        return 0.5 * (a + b);
-    };
-    lmin = kth(1);
-    lmax = kth(int(m));
+        if (open(0)) (any ? b[0] : a[0]) = x0;
+        if (open(1)) (all ? b[1] : a[1]) = x1;
+    }
+    lmin = 0.5 * (a[0] + b[0]);
+    lmax = 0.5 * (a[1] + b[1]);
 }
 
 struct PinnedState {
@@ -2251,11 +2574,16 @@ struct PinnedState {
     }
 };
 
-// Two stop counters in pinned memory and an event for each, per thread: the
-// engine reads a chunk's counter while the next chunk runs.  Events belong to
-// the device they were made on and are made anew when the thread changes it.
+// Pinned memory of a thread's solves: two stop counters, with an event each
+// (the engine reads a chunk's counter while the next chunk runs), and the
+// final state and CG coefficients of a single system.  Events belong to the
+// device they were made on and are made anew when the thread changes it.
 struct StopSlots {
-    int32_t *h = nullptr;  // counters at h[0] and h[16]
+    struct Host {
+        int32_t active[32];  // counters at [0] and [16]
+        PcgState state;
+        double hist[2 * kHist];
+    } *h = nullptr;
     hipEvent_t ev[2] = {nullptr, nullptr};
     int dev = -1;
     void drop()
@@ -2269,7 +2597,7 @@ struct StopSlots {
     {
         int d = 0;
         FE_HIP(hipGetDevice(&d));
-        if (!h) FE_HIP(hipHostMalloc(reinterpret_cast<void **>(&h), 32 * sizeof(int32_t), hipHostMallocDefault));
+        if (!h) FE_HIP(hipHostMalloc(reinterpret_cast<void **>(&h), sizeof(Host), hipHostMallocDefault));
         if (d != dev || !ev[0] || !ev[1]) {
             drop();
             for (hipEvent_t &e : ev) FE_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
@@ -2500,6 +2828,8 @@ struct Group {
     int32_t *d_boff;   // count + 1 block offsets of the row kernels
     int grid;
     int lds;           // bytes of dynamic LDS (mode 6: the largest staged box of the group)
+    int small;         // iterated by pcg_small_kernel (1), its form with the matrix in registers (2)
+    int small_lds;     // its LDS: the largest of the group
 };
 
 // A set of problems launched together: the device table is sorted by (SpMV
@@ -2509,6 +2839,7 @@ struct EngineSet {
     std::vector<PcgJob> jobs;   // sorted like the table
     std::vector<PcgProb> hp;
     std::vector<int32_t> hi;
+    std::vector<char> stage;  // the table as copied to the device
     std::vector<Group> groups;
     std::vector<PcgState> hs;
     int np = 0, ge = 0;
@@ -2546,6 +2877,46 @@ static void launch_rows(int which, const Group &g, const PcgProb *probs, hipStre
     }
 }
 
+// The one-workgroup plan of a system, or none.  The rule is LDS: p, q, row
+// starts and 16-bit columns have to fit (the symmetric storage also needs its
+// values there, being read out of row order).  Values that do not fit come
+// from L2.
+static SmallPlan small_plan(const PcgJob &jb)
+{
+    SmallPlan sp{};
+    if (jb.dg || jb.n < 1 || jb.n > kSmallMaxRows || jb.nnz < 1 || jb.nnz > kSmallLds / 2) return sp;
+    const int64_t vb = jb.fp32 ? 4 : 8;
+    const int64_t all = small_bytes(jb.n, jb.nnz, vb), some = small_bytes(jb.n, jb.nnz, 0);
+    if (all <= kSmallLds) sp.resident = 1;
+    else if (jb.sym || some > kSmallLds) return sp;
+    sp.kind = jb.sym ? kSmallSym : (jb.sa ? kSmallStruct : kSmallCsr);
+    sp.lds = int32_t(sp.resident ? all : some);
+    // lanes per row: enough that every thread has a row or part of one, and
+    // that a lane's share of a row is short
+    const double avg = double(jb.nnz) / double(jb.n);
+    while (sp.lanes < 64 && (2 * sp.lanes * jb.n <= kSmallThreads || avg > 24.0 * sp.lanes)) sp.lanes *= 2;
+    sp.regs = sp.resident && sp.lanes * jb.n <= kSmallThreads;
+    return sp;
+}
+
+// Whether the SpMV of a system alternates its direction from iteration to
+// iteration.  A matrix larger than what the 256 MB memory-side cache keeps of
+// it is evicted in the order it is read; read back and forth, its last part
+// is still there when the next iteration starts with it.  The blocks, their
+// rows and partial slots are the same, so are the results.  Measured per
+// iteration (forward / alternating, us): Q1 symmetric storage 128^3 (229 MB)
+// 91.2 / 87.2, 150^3 155.4 / 152.0, but 115^3 (165 MB, which stays cached)
+// 58.7 / 61.2; Q1 CSR values 115^3 (314 MB) 98.8 / 95.3; elasticity Q2 22^3
+// (335 MB) 92.4 / 85.3, 26^3 147.9 / 134.8, 32^3 246 / 236, 18^3 (177 MB)
+// 47.2 / 48.6.  Scalar rows of mode 6 do not gain (Q2 40^3, 240 MB: 71.3 /
+// 76.2; 50^3 149.4 / 149.8), nor do the CSR plans (Q1 128^3 233 / 232, 150^3
+// 340 / 349).
+static bool alternates(const SpmvPlan &pl, int64_t val_bytes)
+{
+    return (pl.mode == 5 || pl.mode == 7 || pl.mode == 8 || (pl.mode == 6 && pl.rpb == 4)) &&
+           val_bytes >= (int64_t(200) << 20);
+}
+
 fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table, hipStream_t s)
 {
     std::vector<int> order;
@@ -2563,8 +2934,11 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
                                                     jobs[i].colind, jobs[i].val);
         if (jobs[i].n > 0) order.push_back(i);
     }
+    std::vector<SmallPlan> small(njobs);
+    for (int i = 0; i < njobs; i++) small[i] = small_plan(jobs[i]);
     auto key = [&](int i) {
-        return ((plans[i].mode * 1024 + plans[i].rpb) * 4 + plans[i].nc) * 2 + (jobs[i].fp32 ? 1 : 0);
+        return (((plans[i].mode * 1024 + plans[i].rpb) * 4 + plans[i].nc) * 2 + (jobs[i].fp32 ? 1 : 0)) * 4 +
+               (small[i].kind ? 1 + small[i].regs : 0);
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
     const int np = int(order.size());
@@ -2602,20 +2976,24 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         if (jb.sa) P.sa = *jb.sa;
         const SpmvPlan &pl = plans[order[t]];
         if (pl.mode == 6) P.xb = xb_shape(*jb.sa, pl.rpb);
+        P.turn = alternates(pl, (jb.sym ? int64_t(sym_slots(jb.sa->dim)) * sym_stride(jb.n) : jb.nnz) * (jb.fp32 ? 4 : 8));
         P.nbr = grid_rows(jb.n, pl, P.xb);
         P.nbe = grid_elems(jb.n);
+        P.small = small[order[t]];
         E.hi[t] = eoff;
-        eoff += P.nbe;
+        if (!P.small.kind) eoff += P.nbe;  // no blocks of the vector kernels for a one-workgroup system
         if (E.groups.empty() || key(order[E.groups.back().first]) != key(order[t])) {
             Group g{};
             g.pl = pl;
             g.fp32 = jb.fp32;
             g.first = t;
             g.count = 0;
+            g.small = P.small.kind ? 1 + P.small.regs : 0;
             E.groups.push_back(g);
         }
         E.groups.back().count++;
         E.groups.back().lds = std::max(E.groups.back().lds, int(P.xb.lds));
+        E.groups.back().small_lds = std::max(E.groups.back().small_lds, int(P.small.lds));
     }
     E.hi[np] = eoff;
     E.ge = eoff;
@@ -2631,8 +3009,11 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         g.d_boff = E.d_ints + pos;
         pos += g.count + 1;
     }
-    FE_HIP(hipMemcpyAsync(E.d_probs, E.hp.data(), sizeof(PcgProb) * size_t(np), hipMemcpyHostToDevice, s));
-    FE_HIP(hipMemcpyAsync(E.d_ints, E.hi.data(), sizeof(int32_t) * size_t(pos), hipMemcpyHostToDevice, s));
+    // problems and block offsets, adjacent in the table, in one copy
+    E.stage.resize(sp + sizeof(int32_t) * size_t(pos));
+    std::memcpy(E.stage.data(), E.hp.data(), sizeof(PcgProb) * size_t(np));
+    std::memcpy(E.stage.data() + sp, E.hi.data(), sizeof(int32_t) * size_t(pos));
+    FE_HIP(hipMemcpyAsync(E.d_probs, E.stage.data(), E.stage.size(), hipMemcpyHostToDevice, s));
     return FE_OK;
 }
 
@@ -2646,11 +3027,27 @@ fe_status engine_init(EngineSet &E, hipStream_t s)
     return FE_OK;
 }
 
-// One CG iteration of every problem still running; marks are event pairs
-// around the SpMV launches when timing is requested.
-static void engine_iteration(const EngineSet &E, hipStream_t q, std::vector<std::pair<hipEvent_t, hipEvent_t>> *marks)
+// iters iterations of the one-workgroup systems still running.
+static fe_status engine_small(const EngineSet &E, int iters, hipStream_t q)
 {
     for (const Group &g : E.groups) {
+        if (!g.small) continue;
+        void (*const f)(const PcgProb *, int) = g.small == 2 ? (g.fp32 ? pcg_small_kernel<float, true> : pcg_small_kernel<double, true>)
+                                                             : (g.fp32 ? pcg_small_kernel<float, false> : pcg_small_kernel<double, false>);
+        if (g.small_lds > 64 * 1024)
+            FE_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize, g.small_lds));
+        f<<<dim3(g.count), dim3(kSmallThreads), g.small_lds, q>>>(E.d_probs + g.first, iters);
+    }
+    return FE_OK;
+}
+
+// One CG iteration of every other problem still running; marks are event
+// pairs around the SpMV launches when timing is requested.
+static void engine_iteration(const EngineSet &E, hipStream_t q, std::vector<std::pair<hipEvent_t, hipEvent_t>> *marks)
+{
+    if (E.ge == 0) return;
+    for (const Group &g : E.groups) {
+        if (g.small) continue;
         hipEvent_t t0 = marks ? timing_mark(q) : nullptr;
         launch_rows(1, g, E.d_probs, q);
         if (t0) marks->emplace_back(t0, timing_mark(q));
@@ -2662,6 +3059,8 @@ static void engine_iteration(const EngineSet &E, hipStream_t q, std::vector<std:
 fe_status engine_iterate(EngineSet &E, int iters, hipStream_t s)
 {
     if (E.np == 0) return FE_OK;
+    const fe_status st = engine_small(E, iters, s);
+    if (st != FE_OK) return st;
     for (int i = 0; i < iters; i++) engine_iteration(E, s, nullptr);
     FE_HIP(hipGetLastError());
     return FE_OK;
@@ -2680,14 +3079,24 @@ fe_status engine_states(EngineSet &E, hipStream_t s)
 }
 
 // True residuals of every problem of the set, then their states and infos.
-fe_status engine_finish(EngineSet &E, hipStream_t s)
+// pin: the state of a single system and its CG coefficients come straight
+// into pinned memory, with one wait.
+static fe_status engine_finish_to(EngineSet &E, hipStream_t s, StopSlots *pin)
 {
     if (E.np == 0) return FE_OK;
     for (const Group &g : E.groups) launch_rows(2, g, E.d_probs, s);
     hipLaunchKernelGGL(resid_finish_kernel, dim3(E.np), dim3(kBlock), 0, s, E.d_probs);
     FE_HIP(hipGetLastError());
-    fe_status st = engine_states(E, s);
-    if (st != FE_OK) return st;
+    if (pin && E.np == 1) {
+        const PcgWs &w = E.hp[0].w;
+        FE_HIP(hipMemcpyAsync(&pin->h->state, w.st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
+        FE_HIP(hipMemcpyAsync(pin->h->hist, w.hist, sizeof(double) * 2 * kHist, hipMemcpyDeviceToHost, s));
+        FE_HIP(hipStreamSynchronize(s));
+        E.hs[0] = pin->h->state;
+    } else {
+        const fe_status st = engine_states(E, s);
+        if (st != FE_OK) return st;
+    }
     for (int t = 0; t < E.np; t++) {
         const PcgState &h = E.hs[t];
         fe_solve_info *info = E.jobs[t].info;
@@ -2700,6 +3109,8 @@ fe_status engine_finish(EngineSet &E, hipStream_t s)
     }
     return FE_OK;
 }
+
+fe_status engine_finish(EngineSet &E, hipStream_t s) { return engine_finish_to(E, s, nullptr); }
 
 bool engine_done(const EngineSet &E, int t) { return pcg_stopped(E.hs[t], E.hs[t].iter); }
 
@@ -2721,8 +3132,9 @@ static fe_status capture_stream(hipStream_t &out)
 // no_alloc: direct launches only (no graph, no timing events) and the stop
 // counter read into pageable host memory, so the solve creates no device,
 // pinned or graph resource of its own.
+// spectrum: fill the extremal Ritz values of a single system.
 static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_graph, hipStream_t s,
-                            bool no_alloc = false)
+                            bool no_alloc = false, bool spectrum = true)
 {
     for (PcgJob &jb : jobs) {
         std::memset(jb.info, 0, sizeof(fe_solve_info));
@@ -2761,32 +3173,49 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         }
     } hold;
     const int gchunk = 16;
+    if (E.ge == 0) use_graph = false;
     if (use_graph && maxit > 0) {
         hipStream_t cs = nullptr;
         st = capture_stream(cs);
         if (st != FE_OK) return st;
         FE_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
+        st = engine_small(E, gchunk, cs);
         for (int i = 0; i < gchunk; i++) engine_iteration(E, cs, nullptr);
         if (hipStreamEndCapture(cs, &hold.g) != hipSuccess) return set_error(FE_EDEVICE, "graph capture failed");
+        if (st != FE_OK) return st;
         if (hipGraphInstantiate(&hold.e, hold.g, nullptr, nullptr, 0) != hipSuccess)
             return set_error(FE_EDEVICE, "graph instantiation failed");
     }
     int j = 0, chunk = 8;
-    for (int c = 0;; c++) {
+    // one-workgroup systems alone: a launch of many iterations (some
+    // milliseconds at most), the states read after each
+    while (E.ge == 0) {
+        const int todo = std::min(1024, maxit - j);
+        if (todo > 0 && (st = engine_small(E, todo, s)) != FE_OK) return st;
+        j += todo;
+        FE_HIP(hipGetLastError());
+        if ((st = engine_finish_to(E, s, no_alloc ? nullptr : &slots)) != FE_OK) return st;
+        bool all = true;
+        for (int t = 0; t < np; t++) all = all && engine_done(E, t);
+        if (all || j >= maxit) break;
+    }
+    for (int c = 0; E.ge > 0; c++) {
         const bool more = j < maxit;
         if (more) {
             if (hold.e) {
                 FE_HIP(hipGraphLaunch(hold.e, s));
                 j += gchunk;
             } else {
-                for (int i = 0; i < chunk && j < maxit; i++, j++) {
+                const int todo = std::min(chunk, maxit - j);
+                if ((st = engine_small(E, todo, s)) != FE_OK) return st;
+                for (int i = 0; i < todo; i++, j++) {
                     const bool mark = timed && j % kTimeEvery == 0;
                     engine_iteration(E, s, mark ? &marks : nullptr);
                     mark_iter.resize(marks.size(), j);
                 }
                 if (no_alloc && chunk < 128) chunk *= 2;
             }
-            int32_t *out = no_alloc ? E.d_active : slots.h + 16 * (c & 1);
+            int32_t *out = no_alloc ? E.d_active : slots.h->active + 16 * (c & 1);
             hipLaunchKernelGGL(count_active_kernel, dim3(1), dim3(64), 0, s, E.d_probs, np, out);
             FE_HIP(hipGetLastError());
             if (!no_alloc) FE_HIP(hipEventRecord(slots.ev[c & 1], s));
@@ -2800,13 +3229,12 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         } else {  // the chunk before this one
             if (c > 0) {
                 FE_HIP(hipEventSynchronize(slots.ev[(c - 1) & 1]));
-                if (*static_cast<volatile int32_t *>(slots.h + 16 * ((c - 1) & 1)) == 0) break;
+                if (*static_cast<volatile int32_t *>(slots.h->active + 16 * ((c - 1) & 1)) == 0) break;
             }
             if (!more) break;
         }
     }
-    st = engine_finish(E, s);
-    if (st != FE_OK) return st;
+    if (E.ge > 0 && (st = engine_finish_to(E, s, no_alloc ? nullptr : &slots)) != FE_OK) return st;
     for (size_t i = 0; i < marks.size(); i++) {
         if (mark_iter[i] < E.hs[0].iter) {
             timing_commit(marks[i].first, marks[i].second, kTimeSpmv);
@@ -2821,12 +3249,14 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         if (stt != FE_OK && worst == FE_OK) worst = fe_status(stt);
     }
     // Lanczos estimates from the CG coefficients (single problem)
-    if (np == 1) {
+    if (np == 1 && spectrum) {
         fe_solve_info *info = E.jobs[0].info;
         const int m = std::min(E.hs[0].iter, kHist);
         if (m > 0) {
-            std::vector<double> h(2 * kHist);
-            FE_HIP(hipMemcpy(h.data(), E.hp[0].w.hist, sizeof(double) * 2 * kHist, hipMemcpyDeviceToHost));
+            std::vector<double> hv(no_alloc ? 2 * kHist : 0);
+            if (no_alloc)
+                FE_HIP(hipMemcpy(hv.data(), E.hp[0].w.hist, sizeof(double) * 2 * kHist, hipMemcpyDeviceToHost));
+            const double *h = no_alloc ? hv.data() : slots.h->hist;
             std::vector<double> d(m), e(m > 1 ? m - 1 : 1);
             for (int i = 0; i < m; i++) {
                 const double a = h[i];
@@ -2845,7 +3275,7 @@ template <typename VT>
 static fe_status pcg_run(int64_t n, int64_t nnz, const int64_t *rowptr, const int32_t *colind, const VT *val,
                          const double *dinv, const double *b, double *x, double rtol, int maxit, void *ws,
                          size_t ws_bytes, fe_solve_info *info, hipStream_t s, const SpaceArgs *sa = nullptr,
-                         bool sym = false, bool dg = false)
+                         bool sym = false, bool dg = false, bool spectrum = true)
 {
     if (ws_bytes < pcg_ws_bytes(n) + engine_table_bytes(1)) return set_error(FE_EINVAL, "pcg workspace too small");
     if (reinterpret_cast<uintptr_t>(ws) & 7u) return set_error(FE_EINVAL, "workspace not 8-byte aligned");
@@ -2853,7 +3283,7 @@ static fe_status pcg_run(int64_t n, int64_t nnz, const int64_t *rowptr, const in
     jobs[0] = PcgJob{n, nnz, rowptr, colind, val, std::is_same<VT, float>::value, dinv, b, x, ws, info, rtol, maxit, sa,
                      sym, dg};
     void *table = static_cast<char *>(ws) + pcg_ws_bytes(n);
-    return pcg_engine(jobs, table, false, s);
+    return pcg_engine(jobs, table, false, s, false, spectrum);
 }
 
 fe_status pcg_solve(const fe_csr *A, const double *b, double *x, double rtol, int maxit, void *ws, size_t ws_bytes,
@@ -3242,13 +3672,13 @@ fe_status refine_solve(const fe_csr *Ahi, const fe_csr *Alo, const float *values
         fe_status st;
         if (sym32)
             st = pcg_run<float>(n, Alo->nnz, Alo->rowptr, Alo->colind, sym32, Alo->dinv, r, d, inner_rtol,
-                                max_inner, pws, inner_bytes, &inner, s, sa, true);
+                                max_inner, pws, inner_bytes, &inner, s, sa, true, false, false);
         else if (values32)
             st = pcg_run<float>(n, Alo->nnz, Alo->rowptr, Alo->colind, values32, Alo->dinv, r, d, inner_rtol,
-                                max_inner, pws, inner_bytes, &inner, s, sa);
+                                max_inner, pws, inner_bytes, &inner, s, sa, false, false, false);
         else
             st = pcg_run<double>(n, Alo->nnz, Alo->rowptr, Alo->colind, Alo->values, Alo->dinv, r, d, inner_rtol,
-                                 max_inner, pws, inner_bytes, &inner, s, sa);
+                                 max_inner, pws, inner_bytes, &inner, s, sa, false, false, false);
         info->inner_iters += inner.iters;
         info->outer_iters = it + 1;
         if (st == FE_EBREAKDOWN || st == FE_EDEVICE || st == FE_EINVAL) {

@@ -388,3 +388,53 @@ def test_block_staged_traversal_of_a_single_row():
     F.spmv_mesh(pair.mesh, 2, pair.coeff, A.csr, x, y)
     torch.cuda.synchronize()
     assert float(y) == 3.0 * float(A.values[0])
+
+
+# Systems small enough for the one-workgroup solver, in each of its forms: the
+# matrix in registers (one row per lane group), in LDS, its values in L2; rows
+# short of, at and past 1024 and at 4096 (the most), one row; the columns read,
+# evaluated, and the symmetric storage.  One call to the end and calls of a few
+# iterations each (from the state the last one left) give the same iterates.
+@pytest.mark.parametrize("dim,n,k,prob,faces", [(3, [1, 1, 1], 2, "poisson", None), (2, [33, 32], 1, "poisson", None),
+                                                (2, [33, 33], 1, "poisson", None), (2, [65, 65], 1, "poisson", None),
+                                                (3, [8, 8, 8], 1, "poisson", None), (3, [11, 10, 12], 1, "poisson", 0b000011),
+                                                (3, [4, 4, 5], 2, "poisson", None), (2, [9, 8], 3, "elasticity", None),
+                                                (3, [2, 3, 2], 2, "elasticity", 0b000001)])
+def test_small_systems_in_one_workgroup(dim, n, k, prob, faces):
+    pair = Pair(dim, n, k, prob, faces=faces, seed=81, source=(0.4, 1.0, -0.7))
+    A = pair.gpu_assembly()
+    say(f"[small] dim {dim} n {n} k {k} {prob} rows {A.n_rows} nnz {A.nnz}")
+    assert A.n_rows <= 4096
+    ws = torch.empty(F.pcg_query(A.n_rows), dtype=torch.uint8, device="cuda")
+    S = pair.system
+    xd = spla.spsolve(S.scipy().tocsc(), S.rhs)
+    solves = [lambda x, it: F.pcg_solve(A.csr, A.rhs, x, 1e-12, it, ws), lambda x, it: A.solve(x, 1e-12, it, ws),
+              lambda x, it: F.pcg_solve_noalloc(A.csr, A.rhs, x, 1e-12, it)]
+    if k == 1 and prob == "poisson":
+        sym = torch.empty(F.sym_query(pair.mesh, 1, pair.coeff) // 8, dtype=torch.float64, device="cuda")
+        F.sym_from_csr(pair.mesh, 1, pair.coeff, A.csr, sym)
+        solves.append(lambda x, it: F.pcg_solve_sym(pair.mesh, 1, pair.coeff, A.csr, sym, A.rhs, x, 1e-12, it, ws))
+    iters = []
+    for solve in solves:
+        x = torch.zeros(A.n_rows, dtype=torch.float64, device="cuda")
+        info = solve(x, 5000)
+        assert info["status"] == F.FE_OK and info["relres"] <= 1e-12 and info["true_relres"] <= 1e-11
+        assert rel(x.cpu().numpy(), xd) <= 1e-9
+        iters.append(info["iters"])
+        cut = max(info["iters"] // 2, 0)
+        if cut:
+            y = torch.zeros_like(x)
+            i1 = solve(y, cut)
+            assert i1["status"] == F.FE_ENOTCONV and i1["iters"] == cut
+            assert float(torch.linalg.vector_norm(y)) > 0
+    assert max(iters) - min(iters) <= 1
+    # batched: bitwise the single solve
+    x1, x2 = (torch.zeros(A.n_rows, dtype=torch.float64, device="cuda") for _ in range(2))
+    F.pcg_solve(A.csr, A.rhs, x1, 1e-12, 5000, ws)
+    big = Pair(3, [9, 9, 9], 2, seed=82)
+    B = big.gpu_assembly()
+    xb = torch.zeros(B.n_rows, dtype=torch.float64, device="cuda")
+    bws = torch.empty(F.pcg_batch_query([A.n_rows, B.n_rows]), dtype=torch.uint8, device="cuda")
+    st, _ = F.pcg_solve_batch([A.csr, B.csr], [A.rhs, B.rhs], [x2, xb], 1e-12, 5000, bws)
+    torch.cuda.synchronize()
+    assert st == F.FE_OK and torch.equal(x1, x2)
