@@ -383,17 +383,109 @@ __device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const Axi
     return g;
 }
 
-template <int NC, typename ET>
+// The NC rows of a node run by run (vector problems).  The columns of one
+// (j1, j2) are a run of w0 NC consecutive entries in every row, and come from
+// consecutive entries of the row node's element-matrix rows; GL lanes take a
+// run (GL the power of two above its length), so a lane keeps its place along
+// x -- column node, component, the one or two cells -- in registers for the
+// whole node, and a run needs two table reads per lane instead of a decode and
+// six per entry.  Every first contribution of two runs of NC rows (three for
+// FP32 entries) is loaded before any is used; the others (runs through the row node's own line or
+// plane, entries of its own column) follow in ascending cell order.
+// What bounds it: HBM, E read once and the values written once, and the waves
+// in flight (107 registers: four per SIMD; six loads per row in flight need
+// 147 and are slower).  Every first contribution is loaded unconditionally.
+// Entry by entry, Q4 24^3 took 6.90 ms from FP64 entries, Q3 32^3 4.19 from
+// FP64 and 3.99 from FP32, Q2 48^3 2.80 and 2.82; now 5.94, 3.83, 3.51, 2.77
+// and 2.63 (Q4: 4.7 TB/s; a copy reaches 5.1).
+template <int NC, int GL, typename ET>
+__device__ __forceinline__ void node_runs(const SpaceArgs &s, const RowGeom &g, const RowTables &t,
+                                          const ET *__restrict__ E, double *__restrict__ values,
+                                          double *__restrict__ dinv, int64_t row0, int lane)
+{
+    constexpr int NG = 64 / GL, U = sizeof(ET) == 4 ? 3 : 2;
+    const int i = lane % GL, grp = lane / GL;
+    const int wx = g.w0 * NC, len = wx * g.w1 * g.w2, nruns = g.w1 * g.w2;
+    const int nloc = s.nloc;
+    const int ic = i < wx ? i : 0;  // lanes past the run work on its first entry and store nothing
+    const int j0 = ic / NC, cc = ic - j0 * NC;
+    const bool two0 = t.cnt[0][j0] > 1;
+    const bool self0 = g.cl0 + j0 == g.I0;
+    const int qself = int(g.I2 - g.cl2) * g.w1 + int(g.I1 - g.cl1);
+    const uint32_t my = uint32_t(1048576.0f * __builtin_amdgcn_rcpf(float(g.w1))) + 2u;
+    const ET *__restrict__ Ec = E + cc;
+    double *__restrict__ out = values + g.start;
+    for (int q0 = grp; q0 < nruns; q0 += U * NG) {
+        ET v[U][NC];
+        int j1[U], j2[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int q = min(q0 + u * NG, nruns - 1);
+            j2[u] = int((uint32_t(q) * my) >> 20);
+            j1[u] = q - j2[u] * g.w1;
+            const ET *__restrict__ e = Ec + (t.off[0][j0][0] + t.off[1][j1[u]][0] + t.off[2][j2[u]][0]);
+#pragma unroll
+            for (int c = 0; c < NC; c++) v[u][c] = e[c * nloc];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int q = q0 + u * NG;
+            double sum[NC];
+#pragma unroll
+            for (int c = 0; c < NC; c++) sum[c] = double(v[u][c]);
+            auto add = [&](int d0, int d1, int d2) {
+                const ET *__restrict__ e = Ec + (t.off[0][j0][d0] + t.off[1][j1[u]][d1] + t.off[2][j2[u]][d2]);
+                ET w[NC];
+#pragma unroll
+                for (int c = 0; c < NC; c++) w[c] = e[c * nloc];
+#pragma unroll
+                for (int c = 0; c < NC; c++) sum[c] += double(w[c]);
+            };
+            const bool two1 = t.cnt[1][j1[u]] > 1, two2 = t.cnt[2][j2[u]] > 1;
+            if (two0) add(1, 0, 0);
+            if (two1) {
+                add(0, 1, 0);
+                if (two0) add(1, 1, 0);
+            }
+            if (two2) {
+                add(0, 0, 1);
+                if (two0) add(1, 0, 1);
+                if (two1) {
+                    add(0, 1, 1);
+                    if (two0) add(1, 1, 1);
+                }
+            }
+            if (q < nruns && i < wx) {
+                double *__restrict__ o = out + (q * wx + i);
+#pragma unroll
+                for (int c = 0; c < NC; c++) o[c * len] = sum[c];
+                if (self0 && q == qself) {  // the diagonal blocks' entries of this lane's component
+                    double dd = sum[0];
+#pragma unroll
+                    for (int c = 1; c < NC; c++)
+                        if (cc == c) dd = sum[c];
+                    dinv[row0 + cc] = 1.0 / dd;
+                }
+            }
+        }
+    }
+}
+
+// RUNS: run by run (node_runs), for vector problems of order >= 2.
+template <int NC, typename ET, bool RUNS>
 __device__ __forceinline__ void k5_entries_body(const SpaceArgs &s, const ET *__restrict__ E,
                                                 const double *__restrict__ F, double *__restrict__ values,
                                                 double *__restrict__ rhs, double *__restrict__ dinv, int64_t lb,
                                                 int64_t nb)
 {
     __shared__ RowTables tabs[4];
-    RowTables &t = tabs[threadIdx.x / 64];
+    // the wave's index as a scalar: its node's geometry is then computed and
+    // held on the scalar unit
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
+    RowTables &t = tabs[wave];
     const int lane = threadIdx.x % 64;
     const int64_t nw = nb * 4;
-    const int64_t lw = lb * 4 + threadIdx.x / 64;
+    const int64_t lw = lb * 4 + wave;
     const int32_t k = s.k, k1 = k + 1;
     AxisClosed A[3];
 #pragma unroll
@@ -467,7 +559,10 @@ __device__ __forceinline__ void k5_entries_body(const SpaceArgs &s, const ET *__
                 }
             }
         };
-        if constexpr (sizeof(ET) == 4) {
+        if constexpr (RUNS) {
+            if (wx <= 16) node_runs<NC, 16, ET>(s, g, t, E, values, dinv, row0, lane);
+            else node_runs<NC, 32, ET>(s, g, t, E, values, dinv, row0, lane);
+        } else if constexpr (sizeof(ET) == 4) {
             // FP32 loads are unconditional: bound them by the node's cells
             const int rm = __builtin_amdgcn_readfirstlane((e0hi > e0lo ? 1 : 0) | (e1hi > e1lo ? 2 : 0) |
                                                           (e2hi > e2lo ? 4 : 0));
@@ -500,21 +595,35 @@ __device__ __forceinline__ void k5_entries_body(const SpaceArgs &s, const ET *__
     }
 }
 
-template <int NC, typename ET>
+template <int NC, typename ET, bool RUNS>
 __global__ __launch_bounds__(256) void k5_entries_kernel(SpaceArgs s, const ET *__restrict__ E,
                                                          const double *__restrict__ F, double *__restrict__ values,
                                                          double *__restrict__ rhs, double *__restrict__ dinv)
 {
-    k5_entries_body<NC, ET>(s, E, F, values, rhs, dinv, xcd_block(blockIdx.x, gridDim.x), gridDim.x);
+    k5_entries_body<NC, ET, RUNS>(s, E, F, values, rhs, dinv, xcd_block(blockIdx.x, gridDim.x), gridDim.x);
 }
 
-template <int NC, typename ET>
+template <int NC, typename ET, bool RUNS>
 __global__ __launch_bounds__(256) void k5_entries_batch_kernel(const AsmJob *__restrict__ jobs,
                                                                const int32_t *__restrict__ boff, int njobs)
 {
     int64_t lb, nb;
     const AsmJob &J = jobs[find_job(boff, njobs, lb, nb)];
-    k5_entries_body<NC, ET>(J.s, static_cast<const ET *>(J.E), J.F, J.values, J.rhs, J.dinv, lb, nb);
+    k5_entries_body<NC, ET, RUNS>(J.s, static_cast<const ET *>(J.E), J.F, J.values, J.rhs, J.dinv, lb, nb);
+}
+
+// Whether a space's rows are scattered run by run (node_runs): 3D vector
+// problems of order >= 2.  Rows of Q1 elasticity (runs of 9 in 16 lanes) took
+// 667 us at 60^3 that way, 440 entry by entry.
+static bool by_runs(const SpaceArgs &sa) { return sa.ncomp == 3 && sa.k >= 2; }
+
+// Blocks of the cell-major scatter, a wave per node, nodes interleaved over a
+// grid that fills the chip: the most, measured (run by run, Q4 24^3 / Q3 32^3
+// FP64: 3000 blocks 6.63 / 4.26 ms, 5000 5.94 / 3.83, 8192 6.54 / 4.13; entry by
+// entry, scalar Q2 48^3: 2048 blocks 917 us, 8192 836).
+static int64_t entries_grid(const SpaceArgs &sa)
+{
+    return std::min<int64_t>((sa.n_rows / sa.ncomp + 3) / 4, by_runs(sa) ? 5000 : 8192);
 }
 
 fe_status launch_scatter(const SpaceArgs &sa, const ElemLayout &el, const void *ws, double *values, double *rhs,
@@ -538,20 +647,22 @@ fe_status launch_scatter(const SpaceArgs &sa, const ElemLayout &el, const void *
         }
 #undef FE_K5Q
     } else {
-        // wave per row, rows interleaved over a grid that fills the chip
-        const int64_t grid = std::min<int64_t>((sa.n_rows / sa.ncomp + 3) / 4, 8192);
-#define FE_K5E(NCV, T)                                                                                              \
-    hipLaunchKernelGGL((k5_entries_kernel<NCV, T>), dim3(grid), dim3(256), 0, s, sa, static_cast<const T *>(ws), F, \
+        const int64_t grid = entries_grid(sa);
+#define FE_K5E(NCV, T, R)                                                                                           \
+    hipLaunchKernelGGL((k5_entries_kernel<NCV, T, R>), dim3(grid), dim3(256), 0, s, sa, static_cast<const T *>(ws), F, \
                        values, rhs, dinv)
         if (sa.ncomp == 1) {
-            if (el.elem_bytes == 8) FE_K5E(1, double);
-            else FE_K5E(1, float);
+            if (el.elem_bytes == 8) FE_K5E(1, double, false);
+            else FE_K5E(1, float, false);
         } else if (sa.ncomp == 2) {
-            if (el.elem_bytes == 8) FE_K5E(2, double);
-            else FE_K5E(2, float);
+            if (el.elem_bytes == 8) FE_K5E(2, double, false);
+            else FE_K5E(2, float, false);
+        } else if (by_runs(sa)) {
+            if (el.elem_bytes == 8) FE_K5E(3, double, true);
+            else FE_K5E(3, float, true);
         } else {
-            if (el.elem_bytes == 8) FE_K5E(3, double);
-            else FE_K5E(3, float);
+            if (el.elem_bytes == 8) FE_K5E(3, double, false);
+            else FE_K5E(3, float, false);
         }
 #undef FE_K5E
     }
@@ -564,7 +675,7 @@ int64_t scatter_blocks(const SpaceArgs &sa, const ElemLayout &el)
 {
     if (sa.n_rows == 0) return 0;
     if (el.cb > 1) return (q1_chunks(sa) + 3) / 4;
-    return std::min<int64_t>((sa.n_rows / sa.ncomp + 3) / 4, 8192);
+    return entries_grid(sa);
 }
 
 fe_status launch_scatter_batch(const AsmJob &h, const ElemLayout &el, const AsmJob *jobs, const int32_t *boff,
@@ -585,17 +696,20 @@ fe_status launch_scatter_batch(const AsmJob &h, const ElemLayout &el, const AsmJ
                 hipLaunchKernelGGL((k5_q1_batch_kernel<2, float>), dim3(grid), dim3(256), 0, s, jobs, boff, njobs);
         }
     } else {
-#define FE_K5B(NCV, T) \
-    hipLaunchKernelGGL((k5_entries_batch_kernel<NCV, T>), dim3(grid), dim3(256), 0, s, jobs, boff, njobs)
+#define FE_K5B(NCV, T, R) \
+    hipLaunchKernelGGL((k5_entries_batch_kernel<NCV, T, R>), dim3(grid), dim3(256), 0, s, jobs, boff, njobs)
         if (h.s.ncomp == 1) {
-            if (el.elem_bytes == 8) FE_K5B(1, double);
-            else FE_K5B(1, float);
+            if (el.elem_bytes == 8) FE_K5B(1, double, false);
+            else FE_K5B(1, float, false);
         } else if (h.s.ncomp == 2) {
-            if (el.elem_bytes == 8) FE_K5B(2, double);
-            else FE_K5B(2, float);
+            if (el.elem_bytes == 8) FE_K5B(2, double, false);
+            else FE_K5B(2, float, false);
+        } else if (by_runs(h.s)) {
+            if (el.elem_bytes == 8) FE_K5B(3, double, true);
+            else FE_K5B(3, float, true);
         } else {
-            if (el.elem_bytes == 8) FE_K5B(3, double);
-            else FE_K5B(3, float);
+            if (el.elem_bytes == 8) FE_K5B(3, double, false);
+            else FE_K5B(3, float, false);
         }
 #undef FE_K5B
     }
