@@ -287,8 +287,8 @@ fe_status fe_dg_query(fe_mesh mesh, int32_t order, int64_t *n_rows, int64_t *nnz
 fe_status fe_dg_pattern(fe_mesh mesh, int32_t order, fe_csr *out, fe_stream stream);
 
 /* Numeric phase: volume element matrices and loads into ws (the integration
- * kernels of fe_integrate, coefficient 1, FP64), then one workgroup per cell
- * writes the values of the cell's rows: the volume block plus, for each
+ * kernels of fe_integrate, coefficient 1, FP64), then one workgroup per few cells
+ * writes the values of their rows: the volume block plus, for each
  * facet, its two facet matrices with the cell on the row side, and the
  * facet terms of the rhs; dinv = 1 / diagonal.  No atomics: bitwise
  * reproducible; for tau = 1 the off-diagonal blocks of the two cells of a

@@ -7,8 +7,8 @@
 // DOF(K, a) holds the nn columns of K and of each facet neighbour of K, cells
 // in ascending order, so the pattern is a closed form of the cell index.
 //
-// Assembly is a gather over cells, with no atomics: one workgroup per cell K
-// writes every entry of K's nn rows.
+// Assembly is a gather over cells, with no atomics: one workgroup per few cells
+// writes every entry of the nn rows of its cells.
 //  - The volume block is the Poisson element matrix with coefficient 1 (the
 //    integration kernels of fe_integrate*.hip).
 //  - Each of the 2d facets of K adds its two facet matrices with K as the row
@@ -27,13 +27,15 @@
 // Trace structure used by the facet kernel.  The trace of the Lagrange basis
 // on a facet is nonzero only for the (k+1)^(d-1) nodes on it.  Its value at
 // a facet point is a product of 1D Lagrange values, the same on both sides.
-// Per facet the kernel builds three small tables in LDS:
+// With
 //   A[t][b] = sum_q W_q phi_t(q) (n . grad phi_b^K)(q)   (K's normal derivatives)
 //   B[t][b] = sum_q W_q phi_t(q) (n . grad phi_b^L)(q)   (the neighbour's)
 //   M[t][u] = sum_q W_q phi_t(q) phi_u(q)                 (facet mass)
-// Here t and u run over facet nodes, b over the cell's nodes, n is K's
-// outward unit normal and W_q = Gauss weight x facet measure.  Every facet
-// entry is a signed combination of at most three table values.
+// for facet nodes t and u, cell nodes b, K's outward unit normal n and W_q =
+// Gauss weight x facet measure, every facet entry is a signed combination of
+// at most three of these values.  For b with index j along the facet's axis
+// and tangential index u they are D_end(j) X0[t][u], plus X1[t][u] if b is on
+// the facet: the kernel sums X0, X1 and M once for each (t, u).
 #include <algorithm>
 #include <cmath>
 
@@ -125,355 +127,362 @@ struct DgShape {
     static constexpr int NF = DIM == 3 ? K1 * K1 : K1;           // nodes per facet
     static constexpr int NP = NF;                                // facet points (k + 1 per direction)
     static constexpr int NFACE = 2 * DIM;
-    // threads: enough for one entry of the nn x nn block each, up to 256
-    static constexpr int BS = NN * NN <= 64 ? 64 : (NN * NN <= 128 ? 128 : 256);
-    static constexpr int JD = (NN * NN + BS - 1) / BS;  // diagonal-block entries per thread
-    static constexpr bool DREG = JD <= 16;              // diagonal block held in registers
-    static constexpr int NIT = 2 * NFACE * NP;          // (facet, side, point) items
-    static constexpr int IT = (NIT + BS - 1) / BS;      // items per thread
+    static constexpr int NT = NF * NF;  // threads of a cell: one per pair (t, u) of tangential indices
+    // 3D Q2: three cells (243 of 256 threads) beat one in 128 threads (896 us
+    // against 857) and two in 192 (848 against 815)
+    static constexpr int BS = NT > 256 ? 640 : (DIM == 3 && KO >= 2 ? 256 : 64);
+    static constexpr int CB = BS / NT;  // cells per workgroup
+    // waves per SIMD asked of the register allocator: 3D Q2 takes 128 registers
+    // instead of 136 and a fourth wave (857 -> 815 us at 32^3 with the element
+    // matrices; a fifth spills, 1055)
+    static constexpr int MINW = DIM == 3 && KO == 2 ? 4 : 1;
+    static_assert(CB >= 1 && CB * NN <= BS, "a thread per row of the workgroup's cells");
 };
 
-// Index of node a on facet (r, side) (tangential indices, first axis
-// fastest), or -1 if a is not on it.
-template <int DIM, int KO>
-__device__ __forceinline__ int face_node(int a, int r, int side)
+// First node (index 0 along axis R) of tangential index t: its digits have the
+// strides of the other axes.
+template <int DIM, int KO, int R>
+__device__ __forceinline__ int dg_tangent(int t)
 {
     constexpr int K1 = KO + 1;
-    int rem = a, t = 0, mul = 1, ar = 0;
-#pragma unroll
-    for (int s = 0; s < DIM; s++) {
-        const int as = rem % K1;
-        rem /= K1;
-        if (s == r) {
-            ar = as;
-        } else {
-            t += as * mul;
-            mul *= K1;
-        }
-    }
-    return ar == (side ? KO : 0) ? t : -1;
+    if (DIM == 2) return R == 0 ? t * K1 : t;
+    if (R == 0) return t * K1;
+    if (R == 2) return t;
+    return t % K1 + (t / K1) * (K1 * K1);
 }
 
-// One workgroup per cell K.  Phases:
-//  0. tables, neighbours, and the vertices of K and its neighbours into LDS;
-//  1. the geometry of every (facet, side, point) at once: J^-1 on each side,
-//     the facet normal from the cell below the facet, weights, Dirichlet
-//     data, penalties;
-//  2. per facet: the normal derivatives of both sides at the facet points,
-//     the facet mass, the tables A and B in place, then the facet's entries.
-// The diagonal block (volume + every facet) accumulates in registers when a
-// thread holds at most 16 of its entries, else in the output (re-read by the
-// thread that wrote it).
+// One thread's (t, u) of its cell, and its 1D products at the Gauss points of
+// the two tangential directions: phi_t phi_u, phi_t phi_u' and phi_t' phi_u.
+struct DgPair {
+    int t, u;
+    const double *m0, *g0, *h0, *m1, *g1, *h1;
+};
+
+// Both facets of axis R for one pair (t, u): their entries (a, b) with a =
+// (ar, t), b = (br, u), for all ar and br.  sS holds, for each facet point, W,
+// W J^-1 n on K's side and on the neighbour's (along r, t0, t1).
+template <int DIM, int KO, int R>
+__device__ __forceinline__ void dg_axis(const DgArgs &d, const DgPair &P, const double *__restrict__ sS,
+                                        const double *__restrict__ sSig, const int *__restrict__ sSlot,
+                                        double *__restrict__ diag, double *__restrict__ out, int rlen)
+{
+    using S = DgShape<DIM, KO>;
+    constexpr int K1 = S::K1, NN = S::NN, NP = S::NP;
+    constexpr int UQ = KO <= 1 ? KO + 1 : 1;
+    constexpr int SR = R == 0 ? 1 : (R == 1 ? K1 : K1 * K1);  // node stride along R
+    const int a0 = dg_tangent<DIM, KO, R>(P.t), b0 = dg_tangent<DIM, KO, R>(P.u);
+    double dg[K1][K1];
+#pragma unroll
+    for (int i = 0; i < K1; i++)
+#pragma unroll
+        for (int j = 0; j < K1; j++) dg[i][j] = 0.0;
+#pragma unroll
+    for (int side = 0; side < 2; side++) {
+        const int f = 2 * R + side;
+        const int slot = sSlot[f];
+        const bool interior = slot >= 0;
+        // X0 = sum_q W (J^-1 n)_r phi_t phi_u on either side, X1 = sum_q W
+        // phi_t ((J^-1 n)_t0 d0 phi_u + (J^-1 n)_t1 d1 phi_u), T1 the same with
+        // t and u exchanged, M = sum_q W phi_t phi_u
+        double M = 0.0, X0 = 0.0, X1 = 0.0, T1 = 0.0, Y0 = 0.0, Y1 = 0.0;
+        const double *__restrict__ q = sS + f * NP * 8;
+        if (DIM == 2) {
+#pragma unroll
+            for (int q0 = 0; q0 < K1; q0++, q += 8) {
+                M += q[0] * P.m0[q0];
+                X0 += q[1] * P.m0[q0];
+                X1 += q[2] * P.g0[q0];
+                T1 += q[2] * P.h0[q0];
+                Y0 += q[4] * P.m0[q0];
+                Y1 += q[5] * P.g0[q0];
+            }
+        } else {
+            double m1[K1], g1[K1], h1[K1];
+#pragma unroll
+            for (int q1 = 0; q1 < K1; q1++) {
+                m1[q1] = P.m1[q1];
+                g1[q1] = P.g1[q1];
+                h1[q1] = P.h1[q1];
+            }
+#pragma unroll UQ
+            for (int q0 = 0; q0 < K1; q0++) {
+                double wM = 0.0, wX = 0.0, wY = 0.0, a = 0.0, ga = 0.0, ha = 0.0, b = 0.0, gb = 0.0;
+#pragma unroll
+                for (int q1 = 0; q1 < K1; q1++) {
+                    const double *__restrict__ v = q + (q0 + q1 * K1) * 8;
+                    wM += v[0] * m1[q1];
+                    wX += v[1] * m1[q1];
+                    a += v[2] * m1[q1];
+                    ga += v[3] * g1[q1];
+                    ha += v[3] * h1[q1];
+                    wY += v[4] * m1[q1];
+                    b += v[5] * m1[q1];
+                    gb += v[6] * g1[q1];
+                }
+                M += wM * P.m0[q0];
+                X0 += wX * P.m0[q0];
+                X1 = fma(ga, P.m0[q0], fma(a, P.g0[q0], X1));
+                T1 = fma(ha, P.m0[q0], fma(a, P.h0[q0], T1));
+                Y0 += wY * P.m0[q0];
+                Y1 = fma(gb, P.m0[q0], fma(b, P.g0[q0], Y1));
+            }
+        }
+        // normal derivatives: A of K's basis functions, B of the neighbour's
+        // (whose reference coordinate along R is 1 - side); index on the facet
+        // along R on K's side is e, on the neighbour's side o.  The roundings are
+        // spelled out where the two cells of a facet compute the same number in
+        // different roles: their blocks are transposes to the last bit at tau 1.
+        constexpr int ends[2] = {0, KO};
+        const int e = ends[side], o = ends[1 - side];
+        const double cc = interior ? 0.5 : 1.0;
+        double A[K1], At[K1], B[K1];
+#pragma unroll
+        for (int i = 0; i < K1; i++) {
+            const double de = d.De[2 * i + side], dn = d.De[2 * i + 1 - side];
+            A[i] = i == e ? fma(de, X0, X1) : de * X0;
+            At[i] = i == e ? fma(de, X0, T1) : de * X0;
+            B[i] = i == o ? fma(dn, Y0, Y1) : dn * Y0;
+        }
+#pragma unroll
+        for (int i = 0; i < K1; i++) {
+            dg[e][i] -= cc * A[i];
+            dg[i][e] -= cc * d.tau * At[i];
+        }
+        dg[e][e] = fma(sSig[f], M, dg[e][e]);
+        if (interior) {
+            double *__restrict__ w = out + (int64_t(a0) * rlen + slot * NN + b0);
+#pragma unroll
+            for (int i = 0; i < K1; i++)
+#pragma unroll
+                for (int j = 0; j < K1; j++) {
+                    double v = 0.0;
+                    if (i == e) v = -0.5 * B[j];
+                    if (j == o) v = fma(0.5 * d.tau, At[i], v);
+                    if (i == e && j == o) v = fma(-sSig[f], M, v);
+                    w[int64_t(i) * SR * rlen + j * SR] = v;
+                }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < K1; i++)
+#pragma unroll
+        for (int j = 0; j < K1; j++)
+            if (i == 0 || i == KO || j == 0 || j == KO) diag[(a0 + i * SR) * NN + b0 + j * SR] += dg[i][j];
+}
+
+// One workgroup per CB cells, one thread per cell and pair (t, u) of
+// tangential indices.  Phases:
+//  0. neighbours, vertices of the cells and their neighbours, and the element
+//     matrices into LDS; the 1D products of a pair into registers;
+//  1. the geometry of every (cell, facet, point) by one thread: the facet
+//     normal from the cell below the facet, then weight times J^-1 n on each
+//     side, Dirichlet data; 2. penalties;
+//  3. per axis, from the sums over the points of both facets, a pair's
+//     (k + 1)^2 entries of the diagonal block and of each neighbour's.
+// What bounds it: waiting, for the barriers of a cell and the stores.  The basis is a
+// tensor product, so along the axis of a facet only the ends differ: a pair's
+// entries come from six sums over the points (phi_t phi_u with W and with the
+// normal parts of either side, phi_t grad phi_u likewise), each separable in
+// the two tangential directions, instead of a table of normal derivatives per
+// (facet node, basis function), built facet by facet by one workgroup per cell
+// and read back seven values an entry: kernel 1063 -> 579 us at 32^3 Q2 (1.3 GB
+// written, 2.5 TB/s; 2780 vector instructions a cell, a quarter of the time);
+// with the element matrices 1209 -> 815, 3D Q1 33x29x35 151 ->
+// 78, Q3 20x21x19 1360 -> 785, Q4 14x13x12 2500 -> 1092, 2D Q1 300x280 129 ->
+// 55, Q4 90x100 243 -> 208.  What is left at Q2 is half stores (565 us without
+// those of the neighbours' blocks, against 857): each is in runs of 24 to 72
+// bytes of 216-byte pieces.  Passing the blocks through LDS makes the pieces
+// whole and costs two barriers a facet: 857 -> 839 us at Q2, 780 -> 859 at Q3.
 template <int DIM, int KO>
-__global__ __launch_bounds__((DgShape<DIM, KO>::BS)) void dg_cell_kernel(
+__global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) void dg_cell_kernel(
     DgArgs d, MeshArgs m, ProblemArgs p, ElemLayout el, const double *__restrict__ E, const double *__restrict__ F,
     const int64_t *__restrict__ rowptr, double *__restrict__ values, double *__restrict__ rhs,
     double *__restrict__ dinv)
 {
     using S = DgShape<DIM, KO>;
-    constexpr int K1 = S::K1, NN = S::NN, NF = S::NF, NP = S::NP, NFACE = S::NFACE, BS = S::BS, JD = S::JD;
-    constexpr int NV = 1 << DIM;
-    // per facet: normal derivatives of K's and the neighbour's basis at the
-    // facet points, overwritten in place by the tables A and B; facet mass M
-    __shared__ double sX[NP * NN], sY[NP * NN], sM[NF * NF];
-    __shared__ double sL[K1 * K1], sD[K1 * K1], sLe[2 * K1], sDe[2 * K1];
-    __shared__ double sV[1 + NFACE][NV][3];  // vertices of K (slot 0) and of the neighbour across facet f (1 + f)
-    __shared__ double sNv[NFACE][NP][3];     // det J J^-T e_r of the cell below the facet
-    __shared__ double sMv[NFACE][2][NP][3];  // J^-1 n on K's side and on the neighbour's, n = K's outward normal
-    __shared__ double sW[NFACE][NP], sU[NFACE][NP], sSig[NFACE];
-    __shared__ int sFK[NN], sFL[NN];  // facet index of each node on K's facet and on the neighbour's
-    __shared__ int64_t sNb[6];
-    __shared__ int sSlot[6], sSelf, sNc, sBad;
+    constexpr int K1 = S::K1, NN = S::NN, NF = S::NF, NP = S::NP, NFACE = S::NFACE, BS = S::BS, CB = S::CB;
+    constexpr int NT = S::NT, NV = 1 << DIM;
+    __shared__ double sDiag[CB][NN * NN];
+    // per facet point: W, W J^-1 n on K's side (along r, t0, t1) and on the
+    // neighbour's, n = K's outward normal, and the Dirichlet value
+    __shared__ __attribute__((aligned(16))) double sS[CB][NFACE * NP * 8];
+    __shared__ double sV[CB][1 + NFACE][NV][3];  // vertices of K (slot 0) and of the neighbour across facet f (1 + f)
+    __shared__ double sPr[2][K1 * K1 * K1];      // phi_t phi_u and phi_t phi_u' at a 1D Gauss point, [(t K1 + u) K1 + q]
+    __shared__ double sSig[CB][NFACE];
+    __shared__ int sSlot[CB][NFACE], sSelf[CB], sNc[CB];
 
-    const int64_t K = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t Kb = xcd_block(blockIdx.x, gridDim.x) * CB;
     const int tid = threadIdx.x;
-    for (int t = tid; t < K1 * K1; t += BS) {
-        sL[t] = d.L[t];
-        sD[t] = d.D[t];
-    }
-    for (int t = tid; t < 2 * K1; t += BS) {
-        sLe[t] = d.Le[t];
-        sDe[t] = d.De[t];
-    }
-    if (tid == 0) {
+    const int ncb = d.ncells - Kb < CB ? int(d.ncells - Kb) : CB;  // cells of this workgroup
+    if (tid < ncb) {
         int64_t nb[6];
         int slot[6], self, nc;
-        dg_cell_faces(d, K, nb, slot, self, nc);
-        for (int f = 0; f < NFACE; f++) {
-            sNb[f] = nb[f];
-            sSlot[f] = slot[f];
-        }
-        sSelf = self;
-        sNc = nc;
-        sBad = 0;
+        dg_cell_faces(d, Kb + tid, nb, slot, self, nc);
+#pragma unroll
+        for (int f = 0; f < NFACE; f++) sSlot[tid][f] = slot[f];
+        sSelf[tid] = self;
+        sNc[tid] = nc;
     }
-    __syncthreads();
-    for (int t = tid; t < (1 + NFACE) * NV; t += BS) {
-        const int sl = t / NV, v = t % NV;
-        const int64_t cell = sl == 0 ? K : sNb[sl - 1];
-        if (cell < 0) continue;
-        const int64_t e0 = cell % m.n0, e1 = (cell / m.n0) % m.n1, e2 = cell / (int64_t(m.n0) * m.n1);
-        const int64_t vid = (e0 + (v & 1)) +
-                            int64_t(m.n0 + 1) * ((e1 + ((v >> 1) & 1)) + int64_t(m.n1 + 1) * (DIM == 3 ? e2 + ((v >> 2) & 1) : 0));
-        sV[sl][v][0] = m.x[vid];
-        sV[sl][v][1] = m.y[vid];
-        sV[sl][v][2] = DIM == 3 ? m.z[vid] : 0.0;
+    for (int e = tid; e < ncb * ((1 + NFACE) * NV); e += BS) {
+        const int ci = e / ((1 + NFACE) * NV), i = e - ci * ((1 + NFACE) * NV), sl = i / NV, v = i % NV;
+        const int32_t cell = int32_t(Kb) + ci;  // rows, so cells, are below 2^31
+        const int32_t cy = cell / d.n[0], cz = DIM == 3 ? cy / d.n[1] : 0;
+        const int r = sl > 0 ? (sl - 1) >> 1 : 3, step = (sl - 1) & 1 ? 1 : -1;
+        const int32_t c0 = cell - cy * d.n[0] + (r == 0 ? step : 0);
+        const int32_t c1 = (DIM == 3 ? cy - cz * d.n[1] : cy) + (r == 1 ? step : 0);
+        const int32_t c2 = cz + (r == 2 ? step : 0);
+        if (c0 < 0 || c0 >= d.n[0] || c1 < 0 || c1 >= d.n[1] || c2 < 0 || (DIM == 3 && c2 >= d.n[2])) continue;
+        const int64_t vid = (c0 + (v & 1)) + int64_t(m.n0 + 1) * ((c1 + ((v >> 1) & 1)) +
+                                                                  int64_t(m.n1 + 1) * (DIM == 3 ? c2 + ((v >> 2) & 1) : 0));
+        sV[ci][sl][v][0] = m.x[vid];
+        sV[ci][sl][v][1] = m.y[vid];
+        sV[ci][sl][v][2] = DIM == 3 ? m.z[vid] : 0.0;
     }
-    const int self = sSelf, nc = sNc;
-    const int64_t row0 = rowptr[K * NN];
-    const int64_t rlen = int64_t(nc) * NN;
+    for (int e = tid; e < K1 * K1 * K1; e += BS) {
+        const int t = e / (K1 * K1), u = e / K1 % K1, q = e % K1;
+        sPr[0][e] = d.L[t * K1 + q] * d.L[u * K1 + q];
+        sPr[1][e] = d.L[t * K1 + q] * d.D[u * K1 + q];
+    }
+    // the diagonal blocks start from the element matrices
+    for (int e = tid; e < ncb * (NN * NN); e += BS) {
+        const int ci = e / (NN * NN), i = e - ci * (NN * NN);
+        sDiag[ci][i] = E[elem_index(Kb + ci, i / NN, i % NN, NN, el.cb, el.packed, el.ne)];
+    }
+    const int rc = tid / NN, rb = tid - rc * NN;  // row of the workgroup that this thread holds the rhs of
+    double racc = rc < ncb ? F[(Kb + rc) * NN + rb] : 0.0;
+    DgPair P;
+    const int ci = tid / NT;
+    const bool on = ci < ncb;
+    {
+        const int pr = min(tid - ci * NT, NT - 1);
+        P.t = pr / NF;
+        P.u = pr - P.t * NF;
+        const int t0 = P.t % K1, t1 = P.t / K1 % K1, u0 = P.u % K1, u1 = P.u / K1 % K1;
+        P.m0 = sPr[0] + (t0 * K1 + u0) * K1;
+        P.g0 = sPr[1] + (t0 * K1 + u0) * K1;
+        P.h0 = sPr[1] + (u0 * K1 + t0) * K1;
+        P.m1 = sPr[0] + (t1 * K1 + u1) * K1;
+        P.g1 = sPr[1] + (t1 * K1 + u1) * K1;
+        P.h1 = sPr[1] + (u1 * K1 + t1) * K1;
+    }
     __syncthreads();
 
-    // 1a. J^-1 at every facet point on both sides; the facet normal from the
-    // cell below the facet (K on its upper facets and on the boundary)
-    double Ji[S::IT][9];
-#pragma unroll
-    for (int it = 0; it < S::IT; it++) {
-        const int i = tid + it * BS;
-        if (i >= S::NIT) continue;
-        const int f = i / (2 * NP), gs = (i / NP) & 1, q = i % NP;
+    // 1. the facet normal from the cell below the facet (K on its upper facets
+    // and on the boundary), then J^-1 n there and on the other side
+    for (int i = tid; i < ncb * (NFACE * NP); i += BS) {
+        const int cj = i / (NFACE * NP), fq = i - cj * (NFACE * NP), f = fq / NP, q = fq - f * NP;
         const int r = f >> 1, side = f & 1;
-        const bool interior = sNb[f] >= 0;
-        if (gs == 1 && !interior) continue;
+        const bool interior = sSlot[cj][f] >= 0;
         const int t0 = DIM == 2 ? 1 - r : (r == 0 ? 1 : 0), t1 = DIM == 2 ? -1 : (r == 2 ? 1 : 2);
         const int q0 = q % K1, q1 = q / K1;
-        const double er = (gs == 0) == (side == 1) ? 1.0 : 0.0;  // reference coordinate along r
-        double xi[3];
-#pragma unroll
-        for (int sx = 0; sx < 3; sx++) xi[sx] = sx == r ? er : (sx == t0 ? d.gx[q0] : (sx == t1 ? d.gx[q1] : 0.0));
-        double X[NV][3], J[9], xq[3];
-#pragma unroll
-        for (int v = 0; v < NV; v++)
-#pragma unroll
-            for (int c = 0; c < 3; c++) X[v][c] = sV[gs == 0 ? 0 : 1 + f][v][c];
-        const double det = geometry<DIM>(X, xi, J, Ji[it], xq);
-        if (!(det > 0.0)) atomicOr(&sBad, 1);
-        const bool owner = gs == 0 ? (side == 1 || !interior) : side == 0;
-        if (owner) {
-#pragma unroll
-            for (int rr = 0; rr < DIM; rr++)
-                if (rr == r) {
-#pragma unroll
-                    for (int c = 0; c < DIM; c++) sNv[f][q][c] = det * Ji[it][rr * DIM + c];
-                }
-        }
-        if (gs == 0) {
-            double u = 0.0;
-            if (!interior && p.dirichlet_kind == FE_DIRICHLET_AFFINE) {
-                u = p.aff[0];
-#pragma unroll
-                for (int c = 0; c < DIM; c++) u += p.aff[1 + c] * xq[c];
-            }
-            sU[f][q] = u;
-        }
-    }
-    __syncthreads();
-    // 1b. K's outward unit normal n, J^-1 n on each side, weights
-#pragma unroll
-    for (int it = 0; it < S::IT; it++) {
-        const int i = tid + it * BS;
-        if (i >= S::NIT) continue;
-        const int f = i / (2 * NP), gs = (i / NP) & 1, q = i % NP;
-        if (gs == 1 && sNb[f] < 0) continue;
-        double nv[3] = {0.0, 0.0, 0.0}, nn2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < DIM; c++) {
-            nv[c] = sNv[f][q][c];
-            nn2 += nv[c] * nv[c];
-        }
-        const double dS = sqrt(nn2);
-        const double sgn = (f & 1) ? 1.0 : -1.0;
-        double n[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < DIM; c++) n[c] = sgn * (nv[c] / dS);
-#pragma unroll
-        for (int sx = 0; sx < 3; sx++) {
-            double mv = 0.0;
-            if (sx < DIM) {
-#pragma unroll
-                for (int c = 0; c < DIM; c++) mv += Ji[it][sx * DIM + c] * n[c];
-            }
-            sMv[f][gs][q][sx] = mv;
-        }
-        if (gs == 0) {
-            const int q0 = q % K1, q1 = q / K1;
-            sW[f][q] = (d.gw[q0] * (DIM == 3 ? d.gw[q1] : 1.0)) * dS;
-        }
-    }
-    __syncthreads();
-    if (tid < NFACE) {
-        double area = 0.0;
-        for (int q = 0; q < NP; q++) area += sW[tid][q];
-        sSig[tid] = d.gamma / (DIM == 3 ? sqrt(area) : area);
-    }
-
-    // the diagonal block starts from the element matrix of K
-    double dacc[S::DREG ? JD : 1];
-#pragma unroll
-    for (int j = 0; j < (S::DREG ? JD : 1); j++) dacc[j] = 0.0;
-    if constexpr (S::DREG) {
-#pragma unroll
-        for (int j = 0; j < JD; j++) {
-            const int e = tid + j * BS;
-            if (e < NN * NN) dacc[j] = E[elem_index(K, e / NN, e % NN, NN, el.cb, el.packed, el.ne)];
-        }
-    } else {
-        for (int e = tid; e < NN * NN; e += BS) {
-            const int a = e / NN, b = e % NN;
-            values[row0 + a * rlen + self * NN + b] = E[elem_index(K, a, b, NN, el.cb, el.packed, el.ne)];
-        }
-    }
-    double racc = tid < NN ? F[K * NN + tid] : 0.0;
-
+        double *__restrict__ o = sS[cj] + fq * 8;
+        double n[3] = {0.0, 0.0, 0.0}, w = 0.0;
 #pragma unroll 1
-    for (int f = 0; f < NFACE; f++) {
-        const int r = f >> 1, side = f & 1;
-        const bool interior = sNb[f] >= 0;
-        const int t0 = DIM == 2 ? 1 - r : (r == 0 ? 1 : 0);
-        if (f > 0) __syncthreads();  // the previous facet's tables are no longer read
-        for (int a = tid; a < NN; a += BS) {
-            sFK[a] = face_node<DIM, KO>(a, r, side);
-            sFL[a] = face_node<DIM, KO>(a, r, 1 - side);
-        }
-        // normal derivatives of both sides at the facet points, facet mass
-        const int nside = interior ? 2 : 1;
-        for (int e = tid; e < nside * NP * NN; e += BS) {
-            const int sd = e / (NP * NN), e2 = e - sd * (NP * NN);
-            const int q = e2 / NN, b = e2 % NN;
-            const int es = sd == 0 ? side : 1 - side;  // reference coordinate along r on this side
-            const int qi[2] = {q % K1, q / K1};
-            const int bi[3] = {b % K1, (b / K1) % K1, DIM == 3 ? b / (K1 * K1) : 0};
-            double v[3], g[3];
+        for (int gs = 0; gs < 2; gs++) {
+            const bool mine = gs == 0 ? side == 1 || !interior : !(side == 1 || !interior);  // K's own side
+            if (gs == 1 && !interior) break;
+            const double er = mine == (side == 1) ? 1.0 : 0.0;  // reference coordinate along r
+            double xi[3];
 #pragma unroll
-            for (int sx = 0; sx < DIM; sx++) {
-                if (sx == r) {
-                    v[sx] = sLe[2 * bi[sx] + es];
-                    g[sx] = sDe[2 * bi[sx] + es];
-                } else {
-                    const int qs = sx == t0 ? qi[0] : qi[1];
-                    v[sx] = sL[bi[sx] * K1 + qs];
-                    g[sx] = sD[bi[sx] * K1 + qs];
-                }
-            }
-            const double *mv = sMv[f][sd][q];
-            double out = 0.0;
+            for (int sx = 0; sx < 3; sx++) xi[sx] = sx == r ? er : (sx == t0 ? d.gx[q0] : (sx == t1 ? d.gx[q1] : 0.0));
+            double X[NV][3], J[9], Ji[9], xq[3];
 #pragma unroll
-            for (int sx = 0; sx < DIM; sx++) {
-                double gr = g[sx];
+            for (int v = 0; v < NV; v++)
 #pragma unroll
-                for (int t = 0; t < DIM; t++)
-                    if (t != sx) gr *= v[t];
-                out += mv[sx] * gr;
-            }
-            (sd == 0 ? sX : sY)[e2] = out;
-        }
-        for (int e = tid; e < NF * NF; e += BS) {
-            const int t = e / NF, u = e % NF;
-            double sm = 0.0;
+                for (int c = 0; c < 3; c++) X[v][c] = sV[cj][mine ? 0 : 1 + f][v][c];
+            const double det = geometry<DIM>(X, xi, J, Ji, xq);
+            if (!(det > 0.0)) atomicOr(m.status, 1);
+            if (gs == 0) {
+                double nn2 = 0.0;
 #pragma unroll
-            for (int q = 0; q < NP; q++) {
-                const double pt = DIM == 3 ? sL[(t % K1) * K1 + q % K1] * sL[(t / K1) * K1 + q / K1] : sL[t * K1 + q];
-                const double pu = DIM == 3 ? sL[(u % K1) * K1 + q % K1] * sL[(u / K1) * K1 + q / K1] : sL[u * K1 + q];
-                sm += sW[f][q] * (pt * pu);  // symmetric in (t, u) to the last bit
-            }
-            sM[e] = sm;
-        }
-        __syncthreads();
-        const double sigma = sSig[f];
-        // A (from sX) and B (from sY) in place, one thread per column b:
-        // T[t][b] = sum_q W_q phi_t(q) DN[q][b], t over the facet nodes
-        if (tid < nside * NN) {
-            const int sd = tid / NN, b = tid - sd * NN;
-            double *T = sd == 0 ? sX : sY;
-            double col[NP];
+                for (int rr = 0; rr < DIM; rr++)
+                    if (rr == r) {
 #pragma unroll
-            for (int q = 0; q < NP; q++) col[q] = T[q * NN + b];
-            if (sd == 0 && !interior) {
-                // weak Dirichlet data of row b: sum_q W u_D (-tau n.grad phi_b + sigma phi_b)
-                const int bf = sFK[b];
-                double sr = 0.0;
-#pragma unroll
-                for (int q = 0; q < NP; q++) {
-                    double v = -d.tau * col[q];
-                    if (bf >= 0) {
-                        const double phi = DIM == 3 ? sL[(bf % K1) * K1 + q % K1] * sL[(bf / K1) * K1 + q / K1]
-                                                    : sL[bf * K1 + q];
-                        v += sigma * phi;
+                        for (int c = 0; c < DIM; c++) n[c] = det * Ji[rr * DIM + c];
                     }
-                    sr += sW[f][q] * sU[f][q] * v;
+#pragma unroll
+                for (int c = 0; c < DIM; c++) nn2 += n[c] * n[c];
+                const double dS = sqrt(nn2);
+                const double sgn = side ? 1.0 : -1.0;
+#pragma unroll
+                for (int c = 0; c < DIM; c++) n[c] = sgn * (n[c] / dS);
+                w = (d.gw[q0] * (DIM == 3 ? d.gw[q1] : 1.0)) * dS;
+                o[0] = w;
+            }
+#pragma unroll
+            for (int sx = 0; sx < DIM; sx++) {
+                double mv = 0.0;
+#pragma unroll
+                for (int c = 0; c < DIM; c++) mv += Ji[sx * DIM + c] * n[c];
+                o[(mine ? 1 : 4) + (sx == r ? 0 : (sx == t0 ? 1 : 2))] = w * mv;
+            }
+            if (mine) {
+                double u = 0.0;
+                if (!interior && p.dirichlet_kind == FE_DIRICHLET_AFFINE) {
+                    u = p.aff[0];
+#pragma unroll
+                    for (int c = 0; c < DIM; c++) u += p.aff[1 + c] * xq[c];
                 }
-                racc += sr;  // thread b holds the rhs of row b
+                o[7] = u;
             }
-#pragma unroll 1
-            for (int t = 0; t < NF; t++) {
-                const int ta = t % K1, tb = t / K1;
-                double sa = 0.0;
-#pragma unroll
-                for (int q = 0; q < NP; q++) {
-                    const double phi = DIM == 3 ? sL[ta * K1 + q % K1] * sL[tb * K1 + q / K1] : sL[ta * K1 + q];
-                    sa += sW[f][q] * phi * col[q];
-                }
-                T[t * NN + b] = sa;
-            }
-        }
-        __syncthreads();
-        const double *sA = sX, *sB = sY;
-        const double cc = interior ? 0.5 : 1.0;
-        // A^F_KK: the cross of K's facet rows and columns in the diagonal block
-        auto cross = [&](int e) -> double {
-            const int a = e / NN, b = e % NN;
-            const int af = sFK[a], bf = sFK[b];
-            double v = 0.0;
-            if (af >= 0) v -= cc * sA[af * NN + b];
-            if (bf >= 0) v -= cc * d.tau * sA[bf * NN + a];
-            if (af >= 0 && bf >= 0) v += sigma * sM[af * NF + bf];
-            return v;
-        };
-        if constexpr (S::DREG) {
-#pragma unroll
-            for (int j = 0; j < JD; j++) {
-                const int e = tid + j * BS;
-                if (e < NN * NN) dacc[j] += cross(e);
-            }
-        } else {
-            for (int e = tid; e < NN * NN; e += BS) {
-                const int a = e / NN, b = e % NN;
-                if (sFK[a] >= 0 || sFK[b] >= 0) values[row0 + a * rlen + self * NN + b] += cross(e);
-            }
-        }
-        // A^F_KL: the block of the neighbour
-        if (interior) {
-            const int64_t off = row0 + int64_t(sSlot[f]) * NN;
-            for (int e = tid; e < NN * NN; e += BS) {
-                const int a = e / NN, b = e % NN;
-                const int af = sFK[a], bl = sFL[b];
-                double v = 0.0;
-                if (af >= 0) v -= 0.5 * sB[af * NN + b];
-                if (bl >= 0) v += 0.5 * d.tau * sA[bl * NN + a];
-                if (af >= 0 && bl >= 0) v -= sigma * sM[af * NF + bl];
-                values[off + a * rlen + b] = v;
-            }
-        }
-    }
-    if (tid < NN) rhs[K * NN + tid] = racc;
-    // the diagonal block, and 1 / its diagonal from the thread holding it
-    if constexpr (S::DREG) {
-#pragma unroll
-        for (int j = 0; j < JD; j++) {
-            const int e = tid + j * BS;
-            if (e >= NN * NN) continue;
-            const int a = e / NN, b = e % NN;
-            values[row0 + a * rlen + self * NN + b] = dacc[j];
-            if (a == b) dinv[K * NN + a] = 1.0 / dacc[j];
-        }
-    } else {
-        for (int e = tid; e < NN * NN; e += BS) {
-            const int a = e / NN, b = e % NN;
-            if (a == b) dinv[K * NN + a] = 1.0 / values[row0 + a * rlen + self * NN + b];
         }
     }
     __syncthreads();
-    if (tid == 0 && sBad) atomicOr(m.status, 1);
+    if (tid < ncb * NFACE) {
+        const int cj = tid / NFACE, f = tid - cj * NFACE;
+        double area = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP; q++) area += sS[cj][(f * NP + q) * 8];
+        sSig[cj][f] = d.gamma / (DIM == 3 ? sqrt(area) : area);
+    }
+    __syncthreads();
+
+    // weak Dirichlet data of row b on its cell's boundary facets:
+    // sum_q W u_D (-tau n.grad phi_b + sigma phi_b)
+    if (rc < ncb && p.dirichlet_kind == FE_DIRICHLET_AFFINE) {
+        const int b0 = rb % K1, b1 = rb / K1 % K1, b2 = DIM == 3 ? rb / (K1 * K1) : 0;
+        for (int f = 0; f < NFACE; f++) {
+            if (sSlot[rc][f] >= 0) continue;
+            const int r = f >> 1, side = f & 1;
+            const int br = r == 0 ? b0 : (r == 1 ? b1 : b2), bt0 = r == 0 ? b1 : b0, bt1 = r == 2 ? b1 : b2;
+            const double le = d.Le[2 * br + side], de = d.De[2 * br + side], sig = sSig[rc][f];
+            double sr = 0.0;
+            for (int q = 0; q < NP; q++) {
+                const int i0 = bt0 * K1 + q % K1, i1 = bt1 * K1 + q / K1;
+                const double l0 = d.L[i0], l1 = DIM == 3 ? d.L[i1] : 1.0;
+                const double *__restrict__ v = sS[rc] + (f * NP + q) * 8;
+                double dn = v[1] * (de * l0 * l1) + v[2] * (le * d.D[i0] * l1);
+                if (DIM == 3) dn += v[3] * (le * l0 * d.D[i1]);
+                double t = -d.tau * dn;
+                if (br == (side ? KO : 0)) t += sig * (v[0] * (l0 * l1));
+                sr += v[7] * t;
+            }
+            racc += sr;
+        }
+    }
+    if (rc < ncb) rhs[(Kb + rc) * NN + rb] = racc;
+
+    const int cs = on ? ci : 0;
+    const int64_t row0 = rowptr[(Kb + cs) * NN];
+    const int rlen = sNc[cs] * NN;
+    if (on) dg_axis<DIM, KO, 0>(d, P, sS[ci], sSig[ci], sSlot[ci], sDiag[ci], values + row0, rlen);
+    __syncthreads();
+    if (on) dg_axis<DIM, KO, 1>(d, P, sS[ci], sSig[ci], sSlot[ci], sDiag[ci], values + row0, rlen);
+    __syncthreads();
+    if constexpr (DIM == 3) {
+        if (on) dg_axis<DIM, KO, 2>(d, P, sS[ci], sSig[ci], sSlot[ci], sDiag[ci], values + row0, rlen);
+        __syncthreads();
+    }
+    // the diagonal blocks, and 1 / their diagonals; the cell's threads are a
+    // multiple of nn, so a thread keeps its column
+    if (on) {
+        constexpr int NR = NT / NN;  // rows at a time
+        const int lane = tid - ci * NT;
+        double *__restrict__ out = values + (row0 + sSelf[ci] * NN + int64_t(lane / NN) * rlen + lane % NN);
+#pragma unroll
+        for (int i = 0; i < NN / NR; i++) out[int64_t(i) * NR * rlen] = sDiag[ci][lane + i * NT];
+    }
+    if (rc < ncb) dinv[(Kb + rc) * NN + rb] = 1.0 / sDiag[rc][rb * NN + rb];
 }
 
 // ---------------------------------------------------------------------------
@@ -554,8 +563,8 @@ fe_status launch_dg_facets(int dim, const int32_t *n, int k, double gamma, doubl
     const double *E = static_cast<const double *>(ws);
     const double *F = reinterpret_cast<const double *>(static_cast<const char *>(ws) + el.f_offset);
 #define FE_DGK(D, KO)                                                                                  \
-    hipLaunchKernelGGL((dg_cell_kernel<D, KO>), dim3(d.ncells), dim3((DgShape<D, KO>::BS)), 0, s, d, ma, pa, el, E, \
-                       F, rowptr, values, rhs, dinv)
+    hipLaunchKernelGGL((dg_cell_kernel<D, KO>), dim3((d.ncells + DgShape<D, KO>::CB - 1) / DgShape<D, KO>::CB),        \
+                       dim3((DgShape<D, KO>::BS)), 0, s, d, ma, pa, el, E, F, rowptr, values, rhs, dinv)
     if (dim == 3) {
         switch (k) {
             case 1: FE_DGK(3, 1); break;

@@ -192,3 +192,23 @@ def test_dg_rows_of_sampled_cells_at_workload_size():
         worst_spmv = max(worst_spmv, float(np.max(np.abs(y[K * nn:(K + 1) * nn] - yo) / scale)))
     say(f"worst sampled-row rel err {worst:.2e}, cell-block SpMV {worst_spmv:.2e}")
     assert worst <= MATRIX_RTOL and worst_spmv <= 1e-12
+
+
+# cells per workgroup of the facet kernel: 16, 7, 4, 2 in 2D (orders 1-4) and
+# 4, 3, 1, 1 in 3D; one cell, one less than a workgroup, and one and three more
+@pytest.mark.parametrize("dim,k,per", [(2, 1, 16), (2, 2, 7), (2, 3, 4), (2, 4, 2), (3, 1, 4), (3, 2, 3), (3, 3, 1),
+                                       (3, 4, 1)])
+def test_dg_cells_beside_the_workgroup_size(dim, k, per):
+    for cells in sorted({1, max(1, per - 1), per + 1, per + 3}):
+        for axis in (0, dim - 1):
+            n = [1] * dim
+            n[axis] = cells
+            say(f"[dg cells] dim={dim} n={n} k={k}")
+            v = structured_vertices(dim, n, jitter=0.2, seed=95)
+            mesh, coeff, A = gpu_dg(dim, n, k, v, penalty(k), 1.0)
+            D = O.DGSystem(O.Problem(dim, n, k, source_kind=1, source=(1.0,), dirichlet_kind=1, dirichlet_affine=AFF),
+                           v, gamma=penalty(k), tau=1.0)
+            assert D.ok
+            assert rel(A.values[: A.nnz].cpu().numpy(), D.values) <= MATRIX_RTOL
+            assert rel(A.rhs[: A.n_rows].cpu().numpy(), D.rhs) <= MATRIX_RTOL
+            assert rel(A.dinv[: A.n_rows].cpu().numpy(), 1.0 / np.diag(D.dense())) <= MATRIX_RTOL
