@@ -286,13 +286,13 @@ __device__ __forceinline__ void dg_axis(const DgArgs &d, const DgPair &P, const 
 // the two tangential directions, instead of a table of normal derivatives per
 // (facet node, basis function), built facet by facet by one workgroup per cell
 // and read back seven values an entry: kernel 1063 -> 579 us at 32^3 Q2 (1.3 GB
-// written, 2.5 TB/s; 2780 vector instructions a cell, a quarter of the time);
-// with the element matrices 1209 -> 815, 3D Q1 33x29x35 151 ->
-// 78, Q3 20x21x19 1360 -> 785, Q4 14x13x12 2500 -> 1092, 2D Q1 300x280 129 ->
-// 55, Q4 90x100 243 -> 208.  What is left at Q2 is half stores (565 us without
-// those of the neighbours' blocks, against 857): each is in runs of 24 to 72
+// written, 2.5 TB/s; 2780 vector instructions a cell, a quarter of the time).
+// With the element matrices (of the contraction kernels, before they were
+// summed by factors) 1209 -> 815, 3D Q1 33x29x35 151 -> 78, Q3 20x21x19 1360 ->
+// 785, Q4 14x13x12 2500 -> 1092, 2D Q1 300x280 129 -> 55, Q4 90x100 243 -> 208;
+// of the 815, 250 go into storing the neighbours' blocks: runs of 24 to 72
 // bytes of 216-byte pieces.  Passing the blocks through LDS makes the pieces
-// whole and costs two barriers a facet: 857 -> 839 us at Q2, 780 -> 859 at Q3.
+// whole and costs two barriers a facet: 857 -> 839 at Q2, 780 -> 859 at Q3.
 template <int DIM, int KO>
 __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) void dg_cell_kernel(
     DgArgs d, MeshArgs m, ProblemArgs p, ElemLayout el, const double *__restrict__ E, const double *__restrict__ F,

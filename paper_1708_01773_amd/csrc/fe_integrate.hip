@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void k3_q1_batch_kernel(const AsmJob *__restri
 }
 
 // ---------------------------------------------------------------------------
-// Generic tiled kernel (any order, Poisson or elasticity, FP64): one
+// Generic tiled kernel (2D, any order, Poisson or elasticity, FP64): one
 // workgroup computes a TILE x TILE block of one cell's element matrix.
 // Quadrature points are processed in slabs of QS: the slab's geometry and the
 // physical gradients of the tile's row and column shape functions are staged
@@ -410,10 +410,7 @@ static fe_status launch_tiled(const SpaceArgs &sa, const MeshArgs &ma, const Pro
 {
     const int nloc = sa.nloc;
     int mt = (nloc + 15) / 16;
-    if (mt > 8) mt = 8;
-    if (mt == 3) mt = 4;
-    if (mt == 5) mt = 6;
-    if (mt == 7) mt = 8;
+    if (mt == 3) mt = 4;  // at most 50 rows (2D Q4 elasticity)
     const int tile = 16 * mt;
     const int tiles = (nloc + tile - 1) / tile;
     const int64_t grid = sa.ncells * tiles * tiles;
@@ -427,8 +424,6 @@ static fe_status launch_tiled(const SpaceArgs &sa, const MeshArgs &ma, const Pro
         FE_TILED_CASE(1)
         FE_TILED_CASE(2)
         FE_TILED_CASE(4)
-        FE_TILED_CASE(6)
-        FE_TILED_CASE(8)
         default:
             return set_error(FE_EINVAL, "unsupported element size");
     }
@@ -443,6 +438,7 @@ fe_status launch_integrate(const SpaceArgs &sa, const MeshArgs &ma, const Proble
     double *E = static_cast<double *>(ws);
     double *F = reinterpret_cast<double *>(static_cast<char *>(ws) + el.f_offset);
     if (sa.ncells == 0) return FE_OK;
+    if (tensor_integrated(sa, pa)) return launch_integrate_tensor(sa, ma, pa, rt, E, F, s);
     if (sa.dim == 3 && sa.k >= 2) return launch_integrate_mfma(sa, ma, pa, rt, ws, F, s);
     fe_status st = FE_OK;
     if (sa.k == 1 && sa.ncomp == 1) {
@@ -467,8 +463,6 @@ fe_status launch_integrate(const SpaceArgs &sa, const MeshArgs &ma, const Proble
         FE_HIP(hipGetLastError());
     } else if (pa.precision != FE_FP64) {
         return set_error(FE_EINVAL, "reduced-precision integration needs 3D hexahedra (any order) or scalar Q1");
-    } else if (sa.dim == 3) {
-        st = pa.problem == 1 ? launch_tiled<3, 1>(sa, ma, pa, rt, E, F, s) : launch_tiled<3, 0>(sa, ma, pa, rt, E, F, s);
     } else {
         st = pa.problem == 1 ? launch_tiled<2, 1>(sa, ma, pa, rt, E, F, s) : launch_tiled<2, 0>(sa, ma, pa, rt, E, F, s);
     }
@@ -512,6 +506,7 @@ bool integrate_batchable(const SpaceArgs &sa, const ProblemArgs &pa)
 int64_t integrate_blocks(const SpaceArgs &sa, const ProblemArgs &pa, int32_t &parts)
 {
     parts = 1;
+    if (tensor_integrated(sa, pa)) return tensor_blocks(sa, pa, parts);
     if (sa.dim == 3 && sa.k >= 2) return mfma_blocks(sa, pa, parts);
     return (sa.ncells + 255) / 256;
 }
@@ -521,6 +516,7 @@ fe_status launch_integrate_batch(const AsmJob &h, const AsmJob *jobs, const int3
 {
     if (grid == 0) return FE_OK;
     const SpaceArgs &sa = h.s;
+    if (tensor_integrated(sa, h.p)) return launch_tensor_batch(h, jobs, boff, njobs, grid, s);
     if (sa.dim == 3 && sa.k >= 2) return launch_mfma_batch(h, jobs, boff, njobs, grid, s);
     if (!(sa.k == 1 && sa.ncomp == 1)) return set_error(FE_EINVAL, "no batched kernel for this class");
 #define FE_Q1B(D, P) hipLaunchKernelGGL((k3_q1_batch_kernel<D, P>), dim3(grid), dim3(256), 0, s, jobs, boff, njobs)

@@ -1,14 +1,15 @@
 // fe_integrate_mfma.hip -- K3 on the matrix cores: element matrices of Q_k
-// hexahedra (k >= 2) as small GEMMs on MFMA (Sect. 3.7 eq. fematrix; the
-// Poisson element loop of Sect. 8.5 written as a contraction).
+// hexahedra (k >= 2) with FP32, FP16 or BF16 operands as small GEMMs on MFMA
+// (Sect. 3.7 eq. fematrix; the Poisson element loop of Sect. 8.5 written as a
+// contraction).  FP64 is summed by tensor factors (fe_integrate_tensor.hip).
 //
 // With G[(c,q)][a] = (grad phi_a)_c at quadrature point q (physical, FP64
 // geometry) and w_q = w_q k_K |det J_q|:
 //   Poisson     A[a][b]        = sum_(c,q) G[(c,q)][a] w_q G[(c,q)][b]          (K = d nq)
 //   Elasticity  M_ij[a][b]     = sum_q G[(i,q)][a] w_q G[(j,q)][b]              (9 Gram blocks, K = nq)
 //               A[(a,i)][(b,j)] = lambda M_ij + mu (M_ji + delta_ij sum_l M_ll)  (combined per lane)
-// FP64 (v_mfma_f64_16x16x4) and FP32 (v_mfma_f32_16x16x4): a workgroup owns
-// one cell (or a part of its tile pairs); it stages the physical gradients of
+// FP32 (v_mfma_f32_16x16x4): a workgroup owns one cell (or a part of its tile
+// pairs); it stages the physical gradients of
 // a slab of quadrature points in LDS, then every wave accumulates its
 // node-tile pairs (ta <= tb, 16 x 16 each) with MFMA; the lower triangle is
 // written as the mirror of the upper one.  FP16 / BF16 inputs with FP32
@@ -24,27 +25,15 @@
 
 namespace fe {
 
-typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 b8_t __attribute__((ext_vector_type(8)));
-
-struct PolF64 {
-    using S = double;
-    using Acc = d4_t;
-    using Out = double;
-    static constexpr int KM = 4;
-    static constexpr bool ROW_INTERLEAVED = true;  // D register r of lane l is row 4 r + l / 16
-    __device__ static Acc zero() { return Acc{0.0, 0.0, 0.0, 0.0}; }
-    __device__ static Acc mma(S a, S b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-};
 
 struct PolF32 {
     using S = float;
     using Acc = f4_t;
     using Out = float;
     static constexpr int KM = 4;
-    static constexpr bool ROW_INTERLEAVED = false;  // row 4 (l / 16) + r
     __device__ static Acc zero() { return Acc{0.f, 0.f, 0.f, 0.f}; }
     __device__ static Acc mma(S a, S b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 };
@@ -333,7 +322,7 @@ __device__ __forceinline__ void k3_mfma_body(const SpaceArgs &s, const MeshArgs 
         const int col = ptb[t] * 16 + i16;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            const int row = pta[t] * 16 + (Pol::ROW_INTERLEAVED ? 4 * r + g4 : 4 * g4 + r);
+            const int row = pta[t] * 16 + 4 * g4 + r;
             if (row >= nn || col >= nn) continue;
             // on a diagonal tile only the upper triangle is taken, and mirrored,
             // so the element matrix is exactly symmetric in every precision
@@ -757,13 +746,10 @@ struct Cell16Batch {
 // (order, problem, precision).  Every shape sums each entry over the
 // quadrature points in the same order, so the element matrices do not depend
 // on it; the autotuner (fe_integrate_autotune) times the candidates of a
-// class and keeps the fastest for the process.  Defaults measured on 32^3 Q3
-// and 24^3 Q4 elasticity (Q3: 3.75 ms with one pair per wave against 5.57 ms
-// with two).  FP64 Q4 elasticity runs one pair per wave (10.0 ms): two need
-// more than 256 VGPRs and spill to private memory, and a variant of that
-// kernel with more spills gave element matrices that differed from run to
-// run, so no kernel here spills.  FP16 / BF16 have the one shape of the
-// whole-cell kernel.
+// class and keeps the fastest for the process.  FP64 and FP16 / BF16 have one
+// shape a class: the sum-factorized and the whole-cell kernel.  A variant of
+// this kernel that spilled registers to private memory gave element matrices
+// that differed from run to run, so no kernel here spills.
 // ---------------------------------------------------------------------------
 static std::mutex g_k3_mu;
 static std::map<int, int> g_k3_tuned;  // class -> pairs per wave
@@ -784,18 +770,19 @@ static int cell16_ppw(int k)
 
 static std::vector<int> k3_candidates(int k, bool el, int prec)
 {
+    if (prec == FE_FP64) return {1};
     if (whole_cell(prec)) return {cell16_ppw(k)};
     if (k == 2) return {1};
     if (k == 3) return el ? std::vector<int>{1, 2} : std::vector<int>{1, 2, 3};
-    if (el) return prec == FE_FP64 ? std::vector<int>{1} : std::vector<int>{1, 2};
-    return {3, 5, 9};
+    return el ? std::vector<int>{1, 2} : std::vector<int>{3, 5, 9};
 }
 
 static int k3_default(int k, bool el, int prec)
 {
     if (whole_cell(prec)) return cell16_ppw(k);
+    if (prec == FE_FP64) return 1;
     if (k == 3) return el ? 1 : 3;
-    if (k == 4) return el ? (prec == FE_FP64 ? 1 : 2) : 9;
+    if (k == 4) return el ? 2 : 9;
     return 1;
 }
 
@@ -813,7 +800,7 @@ static int parts_of(int k, int ppw)
 }
 
 // Workgroups per cell of the shape (ppw) of a class.
-static int parts_for(int k, int prec, int ppw) { return whole_cell(prec) ? 1 : parts_of(k, ppw); }
+static int parts_for(int k, int prec, int ppw) { return prec == FE_FP32 ? parts_of(k, ppw) : 1; }
 
 template <class Pol, int PROB, int NNP, int PPW, int QS>
 static fe_status launch_one(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
@@ -858,15 +845,6 @@ static fe_status with_shape(int k, bool el, int ppw, Body body)
     }
 }
 
-// The shapes built for a precision: two pairs per wave at Q4 elasticity would
-// need more than 256 VGPRs in FP64 (private-memory spills), so that shape is
-// built for FP32 only.
-template <class Pol, int PROB, int NNP, int PPW>
-constexpr bool shape_built()
-{
-    return !(std::is_same<Pol, PolF64>::value && PROB == 1 && NNP == 128 && PPW == 2);
-}
-
 template <class Pol>
 struct SingleLaunch {
     const SpaceArgs &sa;
@@ -879,10 +857,7 @@ struct SingleLaunch {
     template <int PROB, int NNP, int PPW>
     fe_status operator()() const
     {
-        if constexpr (shape_built<Pol, PROB, NNP, PPW>())
-            return launch_one<Pol, PROB, NNP, PPW, 16>(sa, ma, pa, rt, E, F, s);
-        else
-            return set_error(FE_EINVAL, "tile shape not built for this precision");
+        return launch_one<Pol, PROB, NNP, PPW, 16>(sa, ma, pa, rt, E, F, s);
     }
 };
 
@@ -895,10 +870,7 @@ struct BatchLaunch {
     template <int PROB, int NNP, int PPW>
     fe_status operator()() const
     {
-        if constexpr (shape_built<Pol, PROB, NNP, PPW>())
-            return launch_batch_one<Pol, PROB, NNP, PPW, 16>(jobs, boff, njobs, grid, s);
-        else
-            return set_error(FE_EINVAL, "tile shape not built for this precision");
+        return launch_batch_one<Pol, PROB, NNP, PPW, 16>(jobs, boff, njobs, grid, s);
     }
 };
 
@@ -908,7 +880,7 @@ static fe_status launch_with(const SpaceArgs &sa, const MeshArgs &ma, const Prob
     const bool el = pa.problem == FE_ELASTICITY;
     if (sa.k < 2 || sa.k > 4) return set_error(FE_EINVAL, "matrix-core integration needs order 2..4");
     switch (pa.precision) {
-        case FE_FP64: return with_shape(sa.k, el, ppw, SingleLaunch<PolF64>{sa, ma, pa, rt, E, F, s});
+        case FE_FP64: return launch_integrate_tensor(sa, ma, pa, rt, static_cast<double *>(E), F, s);
         case FE_FP32: return with_shape(sa.k, el, ppw, SingleLaunch<PolF32>{sa, ma, pa, rt, E, F, s});
         case FE_FP16: return with_cell16(sa.k, el, Cell16Single<PolF16>{sa, ma, pa, rt, E, F, s});
         default: return with_cell16(sa.k, el, Cell16Single<PolBF16>{sa, ma, pa, rt, E, F, s});
@@ -928,7 +900,6 @@ fe_status launch_mfma_batch(const AsmJob &h, const AsmJob *jobs, const int32_t *
     const bool el = h.p.problem == FE_ELASTICITY;
     const int ppw = k3_ppw(h.s.k, el, h.p.precision);
     switch (h.p.precision) {
-        case FE_FP64: return with_shape(h.s.k, el, ppw, BatchLaunch<PolF64>{jobs, boff, njobs, grid, s});
         case FE_FP32: return with_shape(h.s.k, el, ppw, BatchLaunch<PolF32>{jobs, boff, njobs, grid, s});
         case FE_FP16: return with_cell16(h.s.k, el, Cell16Batch<PolF16>{jobs, boff, njobs, grid, s});
         default: return with_cell16(h.s.k, el, Cell16Batch<PolBF16>{jobs, boff, njobs, grid, s});

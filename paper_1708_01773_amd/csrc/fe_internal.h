@@ -160,6 +160,13 @@ fe_status launch_integrate(const SpaceArgs &sa, const MeshArgs &ma, const Proble
                            const ElemLayout &el, void *ws, hipStream_t s);
 fe_status launch_integrate_mfma(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
                                 void *E, double *F, hipStream_t s);
+// FP64 hexahedra of order >= 2 and Q1 elasticity (fe_integrate_tensor.hip)
+inline bool tensor_integrated(const SpaceArgs &sa, const ProblemArgs &pa)
+{
+    return sa.dim == 3 && pa.precision == FE_FP64 && (sa.k >= 2 || sa.ncomp == 3);
+}
+fe_status launch_integrate_tensor(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
+                                  double *E, double *F, hipStream_t s);
 fe_status launch_lift(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const int32_t *cell_dofs,
                       const ElemLayout &el, void *ws, hipStream_t s);
 
@@ -167,6 +174,9 @@ fe_status launch_lift(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs
 // the host job h (dimension, order, problem, precision); grid = boff[njobs].
 bool integrate_batchable(const SpaceArgs &sa, const ProblemArgs &pa);
 int64_t integrate_blocks(const SpaceArgs &sa, const ProblemArgs &pa, int32_t &parts);
+int64_t tensor_blocks(const SpaceArgs &sa, const ProblemArgs &pa, int32_t &parts);
+fe_status launch_tensor_batch(const AsmJob &h, const AsmJob *jobs, const int32_t *boff, int njobs, int grid,
+                              hipStream_t s);
 int64_t mfma_blocks(const SpaceArgs &sa, const ProblemArgs &pa, int32_t &parts);
 fe_status integrate_autotune(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
                              void *E, double *F, int reps, fe_k3_plan *tried, int max_tried, int *n_tried,

@@ -133,3 +133,26 @@ def test_quadrature_point_status_is_clear():
     pair = Pair(3, [3, 3, 3], 2)
     pair.gpu_assembly()
     assert F.get_status(pair.mesh) == F.FE_OK
+
+
+# cells per workgroup of the sum-factorized kernel: 7 (Q1 elasticity), 4 (Q2
+# Poisson), 1; plane pairs split over workgroups below 1024 groups of cells.
+# The tolerance is the one of every FP64 element matrix here.
+@pytest.mark.parametrize("n,k,prob", [([1, 1, 1], 1, "elasticity"), ([2, 3, 1], 1, "elasticity"),
+                                      ([2, 2, 2], 1, "elasticity"), ([20, 19, 19], 1, "elasticity"),
+                                      ([1, 1, 1], 2, "poisson"), ([1, 5, 1], 2, "poisson"),
+                                      ([17, 16, 16], 2, "poisson"), ([3, 1, 1], 2, "elasticity"),
+                                      ([11, 10, 10], 2, "elasticity"), ([2, 1, 2], 3, "poisson"),
+                                      ([1, 2, 2], 3, "elasticity"), ([11, 10, 10], 3, "elasticity"),
+                                      ([2, 2, 1], 4, "poisson"), ([11, 10, 10], 4, "poisson"),
+                                      ([2, 1, 1], 4, "elasticity")])
+def test_sum_factorized_element_matrices(n, k, prob):
+    say(f"[tensor] n={n} k={k} {prob}")
+    pair = Pair(3, n, k, prob, seed=83, source_kind=2, source=(0.5, 2.0, -1.0))
+    A = pair.gpu_assembly()
+    nc = pair.P.ncells
+    cells = sorted({0, nc // 3, nc // 2, max(nc - 8, 0), nc - 1})
+    Es, _ = element_matrices(pair, A, cells)
+    for c, E in zip(cells, Es):
+        assert rel(E, pair.oracle_element(c)) <= MATRIX_RTOL
+        assert np.array_equal(E, E.T)
