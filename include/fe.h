@@ -635,7 +635,10 @@ fe_status fe_integrate_autotune(fe_mesh mesh, int32_t order, const fe_coeff *coe
                                 fe_k3_plan *chosen, fe_stream stream);
 fe_status fe_integrate_plan_of(fe_mesh mesh, int32_t order, const fe_coeff *coeff, fe_k3_plan *plan);
 
-/* The plan a matrix of n_rows rows and nnz entries gets now, and its class. */
+/* The plan a matrix of n_rows rows and nnz entries gets now, and its class.
+ * Where no plan of the class was tuned or set, a matrix of at most 200 MiB
+ * (columns and FP64 values) is launched with the wave-level plan of its row
+ * length instead of the block tiles reported here. */
 fe_status fe_spmv_plan_of(int64_t n_rows, int64_t nnz, fe_spmv_plan *plan, int32_t *row_class);
 /* Makes `plan` (mode and rows_per_wave of one of the CSR plans fe_spmv_autotune
  * times; us is ignored) the plan of the row-length class of a matrix of n_rows

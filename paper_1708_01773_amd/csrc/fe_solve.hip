@@ -138,7 +138,8 @@ struct SpmvPlan {
                // 3: structured short rows, two lanes per row (rpb = longest row),
                // 4: structured Q1 scalar rows, values and x runs staged in LDS (rpb = longest row),
                // 5: mode 4 with one wave step per wave (launch form only),
-               // 6: structured rows, x of a 32-row chunk's column box staged per block (rpb 8),
+               // 6: structured rows, x of a 64-row chunk's column box staged per block (rpb 8: a row
+               //    per lane group, 4: the rows of a node),
                // 7: Q1 scalar rows of a system in symmetric storage (rpb = longest row),
                // 8: mode 7 with one wave step per wave (launch form only)
     int nc = 1;  // components (mode 2)
@@ -196,8 +197,11 @@ static SpmvPlan stream_plan(double avg)
         pl.lanes = 64;
         return pl;
     }
-    int rpw = 32;  // a run's rpw + 1 row pointers sit in one wave's lanes
-    while (rpw > 1 && rpw * avg > double(kWaveCap)) rpw /= 2;
+    // a run's rpw + 1 row pointers sit in one wave's lanes; runs whose entries
+    // exceed what the wave stages take a slower path, so the average run is
+    // kept a little below it
+    int rpw = 32;
+    while (rpw > 1 && rpw * avg > double(kWaveCap - kWaveCap / 32)) rpw /= 2;
     pl.mode = 0;
     pl.rpb = rpw;
     pl.lanes = 64 / rpw;
@@ -242,14 +246,36 @@ static int plan_class(int64_t n, int64_t nnz)
     return int(std::floor(2.0 * std::log2(std::max(avg, 1.0))));
 }
 
-static SpmvPlan plan_for(int64_t n, int64_t nnz)
+// The plan of a matrix's class: the tuned one, or the default.
+static SpmvPlan plan_for(int64_t n, int64_t nnz, bool *tuned = nullptr)
 {
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(plan_class(n, nnz));
+        if (tuned) *tuned = it != g_tuned.end();
         if (it != g_tuned.end()) return it->second;
     }
     return heuristic_plan(n > 0 ? double(nnz) / double(n) : 1.0);
+}
+
+// The plan a CSR matrix is launched with: that of its class, but the
+// wave-level plan of its row length where no plan was tuned and the matrix
+// stays in the 256 MB memory-side cache.  There an iteration is bound by the
+// latency of a block's first pass, and waves of their own, without block
+// barriers, shorten it.  Measured per CG iteration (block tiles / wave-level,
+// us, by entries per row): 25, 9 MB 17.4 / 15.5, 133 MB 51.7 / 41.6; 60, 41 MB
+// 27.0 / 25.2, 181 MB 63.8 / 57.0; 101, 15 MB 24.2 / 17.9; 170, 53 MB 34.4 /
+// 27.1, 182 MB 65.1 / 51.5; 310, 196 MB 74.6 / 45.6; 9, 87 MB 43.2 / 41.4.
+// Beyond it the tiles' wide loads win for long rows: 174, 372 MB 119 / 130; 61,
+// 262 MB 83.2 / 88.4.  The plan depends on the matrix alone, so a matrix is
+// summed alike alone and in a batch.
+constexpr int64_t kCsrCached = int64_t(200) << 20;  // bytes of columns and FP64 values
+static SpmvPlan csr_plan(int64_t n, int64_t nnz, const int32_t *colind, const void *val)
+{
+    bool tuned = false;
+    const SpmvPlan pl = plan_for(n, nnz, &tuned);
+    if (pl.mode == 9 && !tuned && 12 * nnz <= kCsrCached) return stream_plan(n > 0 ? double(nnz) / double(n) : 1.0);
+    return csr_launch_form(pl, n, nnz, colind, val);
 }
 
 // ---------------------------------------------------------------------------
@@ -1264,8 +1290,8 @@ __global__ __launch_bounds__(kQ1Block) void sym_fill_kernel(SpaceArgs s, const d
 // (wx, w1: the row's own box), so a column costs two multiply-shift divisions
 // and no load.  L lanes stream a group's values, two consecutive ones per
 // 16-byte load (8-byte aligned: the rows start anywhere), U loads per row in
-// flight; the first U are issued before x is staged, so the two round trips
-// overlap.
+// flight.  Issuing the first U before x is staged did not pay: it costs
+// registers, so waves, and other blocks fill the round trip.
 // What bounds it: the values, from HBM (x is 12-40% of them, from L2); with
 // 8-byte loads of eight lanes per row it was bound by the loads it could keep
 // in flight (the texture addresser 0.93 busy at 3.6-4.3 TB/s).
@@ -2520,7 +2546,7 @@ fe_status launch_spmv(int64_t n, const int64_t *rowptr, const int32_t *colind, c
                       double *y, int64_t nnz, hipStream_t s)
 {
     if (n == 0) return FE_OK;
-    const SpmvPlan pl = csr_launch_form(plan_for(n, nnz), n, nnz, colind, val);
+    const SpmvPlan pl = csr_plan(n, nnz, colind, val);
     const int g = grid_rows(n, pl);
     FE_PLAN_DISPATCH(pl, (spmv_kernel<kMode, kRpb, double><<<dim3(g), dim3(rows_block(kMode)), 0, s>>>(n, nnz,
                                              rowptr, colind, val, x, y)));
@@ -2930,8 +2956,7 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
             plans[i] = launch_form(SpmvPlan{7, 1, jobs[i].sa->dim == 3 ? 27 : 9, 2}, jobs[i].n);
         else
             plans[i] = jobs[i].sa ? aligned_form(struct_plan(*jobs[i].sa), jobs[i].val)
-                                  : csr_launch_form(plan_for(jobs[i].n, jobs[i].nnz), jobs[i].n, jobs[i].nnz,
-                                                    jobs[i].colind, jobs[i].val);
+                                  : csr_plan(jobs[i].n, jobs[i].nnz, jobs[i].colind, jobs[i].val);
         if (jobs[i].n > 0) order.push_back(i);
     }
     std::vector<SmallPlan> small(njobs);
@@ -3570,7 +3595,7 @@ fe_status refine_solve_batch(int nprob, const fe_csr *Ahi, const fe_csr *Alo, co
     for (int it = 0; it <= max_outer && !active.empty(); it++) {
         for (int i : active) {
             const int64_t n = nr[i];
-            const SpmvPlan pl = csr_launch_form(plan_for(n, Ahi[i].nnz), n, Ahi[i].nnz, Ahi[i].colind, Ahi[i].values);
+            const SpmvPlan pl = csr_plan(n, Ahi[i].nnz, Ahi[i].colind, Ahi[i].values);
             const int gr = grid_rows(n, pl);
             const PcgWs w = carve(pws[i], n);
             FE_PLAN_DISPATCH(pl, (resid_vec_kernel<kMode, kRpb><<<dim3(gr), dim3(rows_block(kMode)), 0, s>>>(
@@ -3648,7 +3673,7 @@ fe_status refine_solve(const fe_csr *Ahi, const fe_csr *Alo, const float *values
     double *r = reinterpret_cast<double *>(base + inner_bytes);
     double *d = reinterpret_cast<double *>(base + inner_bytes + align256(size_t(n) * sizeof(double)));
     PcgWs w = carve(pws, n);
-    const SpmvPlan pl = csr_launch_form(plan_for(n, Ahi->nnz), n, Ahi->nnz, Ahi->colind, Ahi->values);
+    const SpmvPlan pl = csr_plan(n, Ahi->nnz, Ahi->colind, Ahi->values);
     const int gr = grid_rows(n, pl);
     const int ge = grid_elems(n);
     info->status = FE_ENOTCONV;

@@ -438,3 +438,40 @@ def test_small_systems_in_one_workgroup(dim, n, k, prob, faces):
     st, _ = F.pcg_solve_batch([A.csr, B.csr], [A.rhs, B.rhs], [x2, xb], 1e-12, 5000, bws)
     torch.cuda.synchronize()
     assert st == F.FE_OK and torch.equal(x1, x2)
+
+
+@pytest.mark.parametrize("dim,n,k,prob", [(2, [40, 33], 1, "poisson"), (2, [19, 14], 2, "poisson"),
+                                          (3, [9, 8, 7], 1, "poisson"), (3, [5, 6, 4], 2, "poisson"),
+                                          (3, [4, 3, 4], 2, "elasticity"), (3, [2, 3, 2], 4, "poisson")])
+@pytest.mark.parametrize("shift", [0, 8])
+def test_cached_matrices_take_the_wave_level_plan(dim, n, k, prob, shift):
+    """A CSR matrix that stays in cache is launched with the wave-level plan of
+    its row length, without a word in the reported plan; a plan that is set
+    (here the reported block tiles) is taken as it is.  Both products are the
+    oracle's, also with values off 16-byte boundaries."""
+    pair = Pair(dim, n, k, prob, seed=74)
+    A = pair.gpu_assembly()
+    S = pair.system
+    say(f"[cached csr] dim {dim} n {n} k {k} rows {A.n_rows} nnz {A.nnz} shift {shift}")
+    x = np.random.Generator(np.random.PCG64(75)).standard_normal(A.n_rows)
+    yo = O.spmv(S.rowptr, S.colind, S.values, x)
+    scale = O.spmv(S.rowptr, S.colind, np.abs(S.values), np.abs(x))
+    buf = torch.empty(A.nnz + 2, dtype=torch.float64, device="cuda")
+    vals = buf[shift // 8: shift // 8 + A.nnz]
+    vals.copy_(A.values[: A.nnz])
+    csr = F.Csr(A.n_rows, A.nnz, A.rowptr.data_ptr(), A.colind.data_ptr(), vals.data_ptr(), A.rhs.data_ptr(),
+                A.dinv.data_ptr())
+    xd = torch.from_numpy(x).cuda()
+    F.spmv_tuning_reset()
+    try:
+        mode, rpw, _ = F.spmv_plan_of(A.n_rows, A.nnz)
+        assert mode == 9
+        for plan in (None, (mode, rpw)):
+            if plan:
+                F.spmv_plan_set(A.n_rows, A.nnz, *plan)
+            y = torch.full_like(xd, float("nan"))
+            F.spmv(csr, xd, y)
+            torch.cuda.synchronize()
+            assert np.all(np.abs(y.cpu().numpy() - yo) <= 1e-12 * scale + 1e-300)
+    finally:
+        F.spmv_tuning_reset()
