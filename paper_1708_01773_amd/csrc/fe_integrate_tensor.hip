@@ -43,6 +43,15 @@ struct TensorShape {
     // Cells per workgroup.  Small systems fill their workgroup with cells: Q1
     // elasticity with seven 0.48 ms, three 0.52, one in 64 threads 0.72.
     static constexpr int CB = BS / LN;
+    // Least workgroups a cell's passes are split over.  Part p takes passes p,
+    // p + parts, ..., so neighbouring tiles are stored at about the same time,
+    // by workgroups of one XCD, and the cache lines that two pieces of a row
+    // share are completed before they are evicted.  Q4 elasticity (1.1 MB a
+    // cell): 5.5 ms with one part, 4.9 with three, 4.4 with five (4.7 when a
+    // part takes consecutive passes), 4.8 with fifteen, as every part repeats
+    // the geometry; below Q4 that costs more than it gives (Q3 2.6 / 2.8 with
+    // three, Q2 2.0 / 2.2).
+    static constexpr int PARTS = PROB == 1 && K1 == 5 ? 5 : 1;
     static constexpr int MINW = K1 == 5 ? 2 : (K1 == 3 ? 4 : 3);  // waves per SIMD: as many as the LDS lets run
     static constexpr int NG = PROB == 1 ? 17 : 7;  // doubles per point (odd: distinct banks)
     static_assert(NPAIR % PG == 0 && CB >= 1 && LP == NC * T, "thread layout");
@@ -65,12 +74,14 @@ __device__ __forceinline__ double source_value_t(const ProblemArgs &p, const dou
 // is staged in LDS and stored along the rows of the matrix, as the pair's
 // block and as its mirror; on a2 = b2 only the upper triangle is taken, so the
 // element matrix is symmetric to the last bit.
-// What bounds it: the stores (Q4 elasticity 15.6 GB in 4.4 to 5.5 ms, by where
-// the buffer lies: 2.8 to 3.5 TB/s, in row pieces of 600 bytes; non-temporal
-// stores 6.5 ms), below Q3 also the LDS round trips of the sums.  Measured
+// What bounds it: the sums and their LDS round trips (without the stores Q4
+// elasticity 3.4 ms, Q3 2.2, Q2 1.7, Poisson Q2 0.23), at Q4 then the stores of
+// the mirror (15.6 GB in 4.4 ms, 3.5 TB/s; without the mirror's 6.2 GB 3.6 ms),
+// whose row pieces of 600 bytes begin and end inside cache lines; non-temporal
+// stores made that worse (6.5 ms).  Measured
 // (contraction on the matrix cores, for Q1 elasticity on the vector unit / this
 // kernel, ms): elasticity Q1 60^3 3.47 / 0.48, Q2 48^3 2.34 / 1.96, Q3 32^3
-// 3.29 / 2.54, Q4 24^3 8.99 / 5.52; Poisson Q2 48^3 0.72 / 0.27, Q3 40^3 1.63 /
+// 3.29 / 2.58, Q4 24^3 8.99 / 4.40; Poisson Q2 48^3 0.72 / 0.27, Q3 40^3 1.63 /
 // 0.68, Q4 30^3 4.21 / 1.16.
 template <int K1, int PROB>
 __device__ __forceinline__ void k3_tensor_body(const MeshArgs &m, const ProblemArgs &p, const RefTables &rt,
@@ -206,9 +217,8 @@ __device__ __forceinline__ void k3_tensor_body(const MeshArgs &m, const ProblemA
         dd[q] = da * db;
     }
     const double lam = p.lambda, mu = p.mu;
-    const int first = part * S::NPASS / parts, last = (part + 1) * S::NPASS / parts;
 #pragma unroll 1
-    for (int pass = first; pass < last; pass++) {
+    for (int pass = part; pass < S::NPASS; pass += parts) {
         int a2 = 0, b2 = pass * PG + pg;  // pair number -> (a2, b2), a2 <= b2
 #pragma unroll
         for (int r = 0; r < K1 - 1; r++)
@@ -365,7 +375,7 @@ struct TensorBlocks {
         // few cells: the passes of a workgroup are split over several, up to
         // four workgroups per CU
         const int64_t groups = (ncells + S::CB - 1) / S::CB;
-        parts = int32_t(std::min<int64_t>(S::NPASS, std::max<int64_t>(1, 1024 / std::max<int64_t>(1, groups))));
+        parts = int32_t(std::min<int64_t>(S::NPASS, std::max<int64_t>(S::PARTS, 1024 / std::max<int64_t>(1, groups))));
         blocks = groups * parts;
         return FE_OK;
     }
