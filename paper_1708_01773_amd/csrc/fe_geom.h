@@ -4,9 +4,23 @@
 // and the facet kernels of the discontinuous Galerkin assembly.
 #pragma once
 
+#include <cmath>
+
 #include "fe_internal.h"
 
 namespace fe {
+
+// Component c of the source at x.
+__device__ __forceinline__ double source_value(const ProblemArgs &p, int dim, const double *x, int c)
+{
+    if (p.source_kind == FE_SOURCE_CONST) return p.source[c];
+    if (p.source_kind == FE_SOURCE_SINPROD) {
+        double s = 1.0;
+        for (int r = 0; r < dim; r++) s *= sin(M_PI * x[r]);
+        return p.source[c] * dim * (M_PI * M_PI) * s;
+    }
+    return 0.0;
+}
 
 template <int DIM>
 __device__ __forceinline__ void load_vertices(const MeshArgs &m, int64_t cell, double X[][3])

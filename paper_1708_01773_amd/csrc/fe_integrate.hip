@@ -33,20 +33,6 @@ ElemLayout elem_layout(const SpaceArgs &sa, int precision)
 }
 
 // ---------------------------------------------------------------------------
-// Device helpers
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double source_value(const ProblemArgs &p, int dim, const double *x, int c)
-{
-    if (p.source_kind == FE_SOURCE_CONST) return p.source[c];
-    if (p.source_kind == FE_SOURCE_SINPROD) {
-        double s = 1.0;
-        for (int r = 0; r < dim; r++) s *= sin(M_PI * x[r]);
-        return p.source[c] * dim * (M_PI * M_PI) * s;
-    }
-    return 0.0;
-}
-
-// ---------------------------------------------------------------------------
 // Q1 scalar kernel: one thread per cell, element matrix in registers (the 36
 // upper-triangle entries in 3D), written in the blocked layout
 // E[(c/64)][a*8+b][c%64] so that a wave's stores of one entry are 512
@@ -200,173 +186,6 @@ __global__ __launch_bounds__(256) void k3_q1_batch_kernel(const AsmJob *__restri
 }
 
 // ---------------------------------------------------------------------------
-// Generic tiled kernel (2D, any order, Poisson or elasticity, FP64): one
-// workgroup computes a TILE x TILE block of one cell's element matrix.
-// Quadrature points are processed in slabs of QS: the slab's geometry and the
-// physical gradients of the tile's row and column shape functions are staged
-// in LDS, then every thread accumulates an MT x MT register micro-tile.
-// ---------------------------------------------------------------------------
-template <int DIM, int PROB, int MT>
-__global__ __launch_bounds__(256) void k3_tiled_kernel(SpaceArgs s, MeshArgs m, ProblemArgs p, RefTables rt,
-                                                        int tiles, double *__restrict__ E, double *__restrict__ F)
-{
-    constexpr int TILE = 16 * MT;
-    constexpr int QS = 8;
-    constexpr int NV = 1 << DIM;
-    constexpr int NC = PROB == 1 ? DIM : 1;
-    const int k = s.k, k1 = k + 1, nn = s.nn, nloc = s.nloc;
-    const int nq = DIM == 3 ? k1 * k1 * k1 : k1 * k1;
-    const int64_t bid = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t cell = bid / (tiles * tiles);
-    const int tile = int(bid % (tiles * tiles));
-    const int r0 = (tile / tiles) * TILE, c0 = (tile % tiles) * TILE;
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-
-    __shared__ double sX[NV][3];
-    __shared__ double sW[QS], sWd[QS], sXq[QS][3], sJi[QS][9];
-    __shared__ double sGr[QS][TILE / NC + 2][DIM];
-    __shared__ double sGc[QS][TILE / NC + 2][DIM];
-    __shared__ int sBad;
-
-    if (tid < NV) {
-        double Xv[NV][3];
-        load_vertices<DIM>(m, cell, Xv);
-        sX[tid][0] = Xv[tid][0];
-        sX[tid][1] = Xv[tid][1];
-        sX[tid][2] = Xv[tid][2];
-    }
-    if (tid == 0) sBad = 0;
-    const double coef = m.coef ? m.coef[cell] : 1.0;
-    const int rn0 = r0 / NC, cn0 = c0 / NC;
-    const int rn1 = min((r0 + TILE - 1) / NC, nn - 1), cn1 = min((c0 + TILE - 1) / NC, nn - 1);
-    const int nrn = rn1 - rn0 + 1, ncn = cn1 - cn0 + 1;
-    const bool do_load = (c0 == 0);
-    __syncthreads();
-
-    double acc[MT][MT];
-#pragma unroll
-    for (int i = 0; i < MT; i++)
-#pragma unroll
-        for (int j = 0; j < MT; j++) acc[i][j] = 0.0;
-    double facc = 0.0;
-
-    for (int qs0 = 0; qs0 < nq; qs0 += QS) {
-        if (tid < QS && qs0 + tid < nq) {
-            const int q = qs0 + tid;
-            const int q0 = q % k1, q1 = (q / k1) % k1, q2 = q / (k1 * k1);
-            const double xi[3] = {rt.gx[q0], rt.gx[q1], DIM == 3 ? rt.gx[q2] : 0.0};
-            const double w = rt.gw[q0] * rt.gw[q1] * (DIM == 3 ? rt.gw[q2] : 1.0);
-            double Xl[NV][3];
-            for (int v = 0; v < NV; v++)
-                for (int r = 0; r < 3; r++) Xl[v][r] = sX[v][r];
-            double J[9], Ji[9], xq[3];
-            const double det = geometry<DIM>(Xl, xi, J, Ji, xq);
-            if (!(det > 0.0)) sBad = 1;
-            sWd[tid] = w * fabs(det);
-            sW[tid] = w * fabs(det) * coef;
-            for (int t = 0; t < 9; t++) sJi[tid][t] = Ji[t];
-            for (int r = 0; r < 3; r++) sXq[tid][r] = xq[r];
-        }
-        __syncthreads();
-        // physical gradients of the row and column nodes at the slab's points
-        for (int idx = tid; idx < QS * (nrn + ncn); idx += blockDim.x) {
-            const int q = idx / (nrn + ncn);
-            const int rem = idx % (nrn + ncn);
-            const bool is_row = rem < nrn;
-            const int node = is_row ? rn0 + rem : cn0 + (rem - nrn);
-            const int qq = qs0 + q;
-            double g[DIM];
-            if (qq < nq) {
-                const int q0 = qq % k1, q1 = (qq / k1) % k1, q2 = qq / (k1 * k1);
-                const int a0 = node % k1, a1 = (node / k1) % k1, a2 = node / (k1 * k1);
-                double gr[3];
-                const double L0 = rt.L[a0 * k1 + q0], L1 = rt.L[a1 * k1 + q1];
-                const double D0 = rt.D[a0 * k1 + q0], D1 = rt.D[a1 * k1 + q1];
-                if (DIM == 3) {
-                    const double L2 = rt.L[a2 * k1 + q2], D2 = rt.D[a2 * k1 + q2];
-                    gr[0] = D0 * L1 * L2;
-                    gr[1] = L0 * D1 * L2;
-                    gr[2] = L0 * L1 * D2;
-                } else {
-                    gr[0] = D0 * L1;
-                    gr[1] = L0 * D1;
-                    gr[2] = 0.0;
-                }
-                for (int i = 0; i < DIM; i++) {
-                    double v = 0.0;
-                    for (int sd = 0; sd < DIM; sd++) v += sJi[q][sd * DIM + i] * gr[sd];
-                    g[i] = v;
-                }
-            } else {
-                for (int i = 0; i < DIM; i++) g[i] = 0.0;
-            }
-            if (is_row)
-                for (int i = 0; i < DIM; i++) sGr[q][rem][i] = g[i];
-            else
-                for (int i = 0; i < DIM; i++) sGc[q][rem - nrn][i] = g[i];
-        }
-        __syncthreads();
-        const int qn = min(QS, nq - qs0);
-        for (int q = 0; q < qn; q++) {
-            const double wq = sW[q];
-            double ga[MT][DIM], gb[MT][DIM];
-#pragma unroll
-            for (int i = 0; i < MT; i++) {
-                const int row = min(r0 + ty + 16 * i, nloc - 1);
-                const int col = min(c0 + tx + 16 * i, nloc - 1);
-#pragma unroll
-                for (int d = 0; d < DIM; d++) {
-                    ga[i][d] = sGr[q][row / NC - rn0][d];
-                    gb[i][d] = sGc[q][col / NC - cn0][d];
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < MT; i++)
-#pragma unroll
-                for (int j = 0; j < MT; j++) {
-                    double dot = 0.0;
-#pragma unroll
-                    for (int d = 0; d < DIM; d++) dot += ga[i][d] * gb[j][d];
-                    if (PROB == 0) {
-                        acc[i][j] += wq * dot;
-                    } else {
-                        const int ci = (r0 + ty + 16 * i) % NC, cj = (c0 + tx + 16 * j) % NC;
-                        double v = p.lambda * ga[i][ci] * gb[j][cj] + p.mu * ga[i][cj] * gb[j][ci];
-                        if (ci == cj) v += p.mu * dot;
-                        acc[i][j] += wq * v;
-                    }
-                }
-        }
-        if (do_load && tid < TILE && r0 + tid < nloc) {
-            const int row = r0 + tid, a = row / NC, c = row % NC;
-            const int a0 = a % k1, a1 = (a / k1) % k1, a2 = a / (k1 * k1);
-            for (int q = 0; q < qn; q++) {
-                const int qq = qs0 + q;
-                const int q0 = qq % k1, q1 = (qq / k1) % k1, q2 = qq / (k1 * k1);
-                double phi = rt.L[a0 * k1 + q0] * rt.L[a1 * k1 + q1];
-                if (DIM == 3) phi *= rt.L[a2 * k1 + q2];
-                const double xq[3] = {sXq[q][0], sXq[q][1], sXq[q][2]};
-                facc += sWd[q] * source_value(p, DIM, xq, c) * phi;
-            }
-        }
-        __syncthreads();
-    }
-    if (tid == 0 && sBad) atomicOr(m.status, 1);
-    double *Ec = E + cell * int64_t(nloc) * nloc;
-#pragma unroll
-    for (int i = 0; i < MT; i++) {
-        const int row = r0 + ty + 16 * i;
-        if (row >= nloc) continue;
-#pragma unroll
-        for (int j = 0; j < MT; j++) {
-            const int col = c0 + tx + 16 * j;
-            if (col < nloc) Ec[int64_t(row) * nloc + col] = acc[i][j];
-        }
-    }
-    if (do_load && tid < TILE && r0 + tid < nloc) F[cell * nloc + r0 + tid] = facc;
-}
-
-// ---------------------------------------------------------------------------
 // Dirichlet lifting for non-zero (affine) data: F_a -= sum_{b fixed} A_ab u_D(b)
 // on every cell that has fixed DOFs (one wave per cell).
 // ---------------------------------------------------------------------------
@@ -404,34 +223,6 @@ __global__ __launch_bounds__(64) void k3_lift_kernel(SpaceArgs s, MeshArgs m, Pr
 // ---------------------------------------------------------------------------
 // Launch
 // ---------------------------------------------------------------------------
-template <int DIM, int PROB>
-static fe_status launch_tiled(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
-                              double *E, double *F, hipStream_t s)
-{
-    const int nloc = sa.nloc;
-    int mt = (nloc + 15) / 16;
-    if (mt == 3) mt = 4;  // at most 50 rows (2D Q4 elasticity)
-    const int tile = 16 * mt;
-    const int tiles = (nloc + tile - 1) / tile;
-    const int64_t grid = sa.ncells * tiles * tiles;
-    if (grid == 0) return FE_OK;
-#define FE_TILED_CASE(MTV)                                                                                          \
-    case MTV:                                                                                                       \
-        hipLaunchKernelGGL((k3_tiled_kernel<DIM, PROB, MTV>), dim3(grid), dim3(256), 0, s, sa, ma, pa, rt, tiles, E, \
-                           F);                                                                                      \
-        break;
-    switch (mt) {
-        FE_TILED_CASE(1)
-        FE_TILED_CASE(2)
-        FE_TILED_CASE(4)
-        default:
-            return set_error(FE_EINVAL, "unsupported element size");
-    }
-#undef FE_TILED_CASE
-    FE_HIP(hipGetLastError());
-    return FE_OK;
-}
-
 fe_status launch_integrate(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
                            const ElemLayout &el, void *ws, hipStream_t s)
 {
@@ -464,7 +255,7 @@ fe_status launch_integrate(const SpaceArgs &sa, const MeshArgs &ma, const Proble
     } else if (pa.precision != FE_FP64) {
         return set_error(FE_EINVAL, "reduced-precision integration needs 3D hexahedra (any order) or scalar Q1");
     } else {
-        st = pa.problem == 1 ? launch_tiled<2, 1>(sa, ma, pa, rt, E, F, s) : launch_tiled<2, 0>(sa, ma, pa, rt, E, F, s);
+        st = launch_integrate_plane(sa, ma, pa, rt, E, F, s);
     }
     return st;
 }

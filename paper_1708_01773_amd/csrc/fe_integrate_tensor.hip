@@ -1,5 +1,5 @@
-// fe_integrate_tensor.hip -- K3 in FP64 on hexahedra of order 2..4 (and Q1
-// elasticity): element matrices by sum factorization (Sect. 3.7 eq. fematrix;
+// fe_integrate_tensor.hip -- K3 in FP64 on quadrilaterals and hexahedra of order
+// 2..4 (and Q1 elasticity): element matrices by sum factorization (Sect. 3.7 eq. fematrix;
 // the Poisson element loop of Sect. 8.5 for a tensor-product basis).
 //
 // With a = (a0, a1, a2), q = (q0, q1, q2), phi_a = prod_d phi_{a_d}(xi_d) and
@@ -14,11 +14,12 @@
 //   A(a0, b0; a1, b1)     = sum_q0 V_xy(q0) T(a0, b0, q0)
 // with T a product of values or derivatives: at Q4 some 30 operations per
 // entry and component pair where the contraction over the 125 points has 125.
-// The FP64 matrix instructions run at the rate of the vector unit (64 cycles
+// In 2D the first sum falls away.  The FP64 matrix instructions run at the rate of the vector unit (64 cycles
 // for a 16 x 16 x 4 product), so they gain nothing for the longer sum.
 #include <algorithm>
 #include <cmath>
 
+#include "fe_geom.h"
 #include "fe_internal.h"
 
 namespace fe {
@@ -56,16 +57,6 @@ struct TensorShape {
     static constexpr int NG = PROB == 1 ? 17 : 7;  // doubles per point (odd: distinct banks)
     static_assert(NPAIR % PG == 0 && CB >= 1 && LP == NC * T, "thread layout");
 };
-
-__device__ __forceinline__ double source_value_t(const ProblemArgs &p, const double *x, int c)
-{
-    if (p.source_kind == FE_SOURCE_CONST) return p.source[c];
-    if (p.source_kind == FE_SOURCE_SINPROD) {
-        const double s = sin(M_PI * x[0]) * sin(M_PI * x[1]) * sin(M_PI * x[2]);
-        return p.source[c] * 3.0 * (M_PI * M_PI) * s;
-    }
-    return 0.0;
-}
 
 // One workgroup = CB cells, or a part of their passes over the plane pairs.
 // One thread per pair, components (i, j) and (q0, q1) in the first sum,
@@ -176,7 +167,7 @@ __device__ __forceinline__ void k3_tensor_body(const MeshArgs &m, const ProblemA
 #pragma unroll
             for (int t = 0; t < 9; t++) o[7 + t] = Ji[t];
         }
-        for (int c = 0; c < NC; c++) sF[e * NC + c] = wd * source_value_t(p, xq, c);
+        for (int c = 0; c < NC; c++) sF[e * NC + c] = wd * source_value(p, 3, xq, c);
     }
     __syncthreads();
     // load vector, one direction after the other
@@ -348,6 +339,130 @@ __global__ __launch_bounds__((TensorShape<K1, PROB>::BS), (TensorShape<K1, PROB>
     k3_tensor_body<K1, PROB>(J.m, J.p, J.rt, J.s.ncells, J.parts, static_cast<double *>(J.E), J.F, lb);
 }
 
+// 2D: one workgroup = CB cells, one thread per cell, components (i, j) and
+// (a1, b1), which sums over q1 for one q0 after the other, the K1^2 entries
+// (a0, b0) in registers.  The matrices of the cells are put together in LDS,
+// the lower triangle as the mirror of the upper, and leave as one contiguous
+// range.  What bounds it: instructions and the LDS round trips (Q2 2.8 TB/s,
+// Q4 elasticity 5.3).  Against one workgroup per cell with an outer product
+// over slabs of points, us: Poisson Q2 400x300 809 -> 28, elasticity Q1 400x300
+// 629 -> 32, Q4 150x150 3035 -> 213; one Q4 elasticity cell 52 -> 9.4.
+template <int K1, int PROB>
+struct PlaneShape {
+    static constexpr int NC = PROB == 1 ? 2 : 1;
+    static constexpr int NN = K1 * K1, NLOC = NN * NC;
+    static constexpr int LN = NC * NC * NN;  // threads of a cell
+    static constexpr int BS = 256, CB = BS / LN;
+    static constexpr int NG = PROB == 1 ? 9 : 3;  // doubles per point (odd: distinct banks)
+};
+
+template <int K1, int PROB>
+__global__ __launch_bounds__((PlaneShape<K1, PROB>::BS)) void k3_plane_kernel(MeshArgs m, ProblemArgs p, RefTables rt,
+                                                                               int64_t ncells, double *__restrict__ E,
+                                                                               double *__restrict__ F)
+{
+    using S = PlaneShape<K1, PROB>;
+    constexpr int NC = S::NC, NN = S::NN, NLOC = S::NLOC, CB = S::CB, BS = S::BS, NG = S::NG;
+    __shared__ double sL[NN], sD[NN];
+    // per point: w k Ji Ji^T (00, 01, 11; times mu for elasticity); elasticity also w k and J^-1
+    __shared__ double sQ[CB][NN][NG];
+    __shared__ double sE[CB * NLOC * NLOC];
+    __shared__ double sF[CB][NN * NC];
+    const int tid = threadIdx.x;
+    const int64_t c0 = xcd_block(blockIdx.x, gridDim.x) * CB;
+    const int ncb = ncells - c0 < CB ? int(ncells - c0) : CB;
+    for (int e = tid; e < NN; e += BS) {
+        sL[e] = rt.L[e];
+        sD[e] = rt.D[e];
+    }
+    for (int e = tid; e < ncb * NN; e += BS) {
+        const int ci = e / NN, q = e - ci * NN, q0 = q % K1, q1 = q / K1;
+        const double xi[3] = {rt.gx[q0], rt.gx[q1], 0.0};
+        double X[4][3], J[9], Ji[9], xq[3];
+        load_vertices<2>(m, c0 + ci, X);
+        const double det = geometry<2>(X, xi, J, Ji, xq);
+        if (!(det > 0.0)) atomicOr(m.status, 1);
+        const double wd = rt.gw[q0] * rt.gw[q1] * fabs(det);
+        const double w = wd * (m.coef ? m.coef[c0 + ci] : 1.0);
+        const double wm = PROB == 1 ? p.mu * w : w;
+        double *__restrict__ o = sQ[ci][q];
+        o[0] = wm * fma(Ji[1], Ji[1], Ji[0] * Ji[0]);
+        o[1] = wm * fma(Ji[1], Ji[3], Ji[0] * Ji[2]);
+        o[2] = wm * fma(Ji[3], Ji[3], Ji[2] * Ji[2]);
+        if (PROB == 1) {
+            o[3] = w;
+#pragma unroll
+            for (int t = 0; t < 4; t++) o[4 + t] = Ji[t];
+        }
+        for (int c = 0; c < NC; c++) sF[ci][q * NC + c] = wd * source_value(p, 2, xq, c);
+    }
+    __syncthreads();
+    for (int e = tid; e < ncb * NLOC; e += BS) {
+        const int ci = e / NLOC, row = e - ci * NLOC, a = row / NC, c = row - a * NC, a0 = a % K1, a1 = a / K1;
+        double f1 = 0.0;
+        for (int q1 = 0; q1 < K1; q1++) {
+            double f0 = 0.0;
+#pragma unroll
+            for (int q0 = 0; q0 < K1; q0++) f0 = fma(sL[a0 * K1 + q0], sF[ci][(q1 * K1 + q0) * NC + c], f0);
+            f1 = fma(sL[a1 * K1 + q1], f0, f1);
+        }
+        F[c0 * NLOC + e] = f1;
+    }
+    const int ci = tid / S::LN, ln = tid - ci * S::LN;
+    if (ci < ncb) {
+        const int b1 = ln % K1, a1 = ln / K1 % K1, ij = ln / NN, i = ij / NC, j = ij - i * NC;
+        const double lam = p.lambda, mu = p.mu;
+        double out[K1][K1];
+#pragma unroll
+        for (int a = 0; a < K1; a++)
+#pragma unroll
+            for (int b = 0; b < K1; b++) out[a][b] = 0.0;
+#pragma unroll 1
+        for (int q0 = 0; q0 < K1; q0++) {
+            double Vdd = 0.0, Vdv = 0.0, Vvd = 0.0, Vvv = 0.0;
+#pragma unroll
+            for (int q1 = 0; q1 < K1; q1++) {
+                const double la = sL[a1 * K1 + q1], da = sD[a1 * K1 + q1], lb = sL[b1 * K1 + q1], db = sD[b1 * K1 + q1];
+                const double *__restrict__ o = sQ[ci][q1 * K1 + q0];
+                double D[4] = {o[0], o[1], o[1], o[2]};  // r s
+                if (PROB == 1) {
+                    const double wl = lam * o[3], wm = mu * o[3];
+#pragma unroll
+                    for (int r = 0; r < 2; r++)
+#pragma unroll
+                        for (int t = 0; t < 2; t++)
+                            D[2 * r + t] = fma(wl * o[4 + 2 * r + i], o[4 + 2 * t + j],
+                                               fma(wm * o[4 + 2 * r + j], o[4 + 2 * t + i], i == j ? D[2 * r + t] : 0.0));
+                }
+                Vdd = fma(D[0], la * lb, Vdd);
+                Vdv = fma(D[1], la * db, Vdv);
+                Vvd = fma(D[2], da * lb, Vvd);
+                Vvv = fma(D[3], da * db, Vvv);
+            }
+#pragma unroll
+            for (int b = 0; b < K1; b++) {
+                const double lb = rt.L[b * K1 + q0], db = rt.D[b * K1 + q0];
+                const double yd = fma(Vdd, db, Vdv * lb), yv = fma(Vvd, db, Vvv * lb);
+#pragma unroll
+                for (int a = 0; a < K1; a++)
+                    out[a][b] = fma(rt.D[a * K1 + q0], yd, fma(rt.L[a * K1 + q0], yv, out[a][b]));
+            }
+        }
+        double *__restrict__ t = sE + ci * (NLOC * NLOC);
+#pragma unroll
+        for (int a = 0; a < K1; a++)
+#pragma unroll
+            for (int b = 0; b < K1; b++) {
+                const int I = (a1 * K1 + a) * NC + i, J = (b1 * K1 + b) * NC + j;
+                if (I <= J) t[I * NLOC + J] = out[a][b];
+                if (I < J) t[J * NLOC + I] = out[a][b];
+            }
+    }
+    __syncthreads();
+    double *__restrict__ Ec = E + c0 * (NLOC * NLOC);
+    for (int e = tid; e < ncb * (NLOC * NLOC); e += BS) Ec[e] = sE[e];
+}
+
 // Calls body.template operator()<K1, PROB>() for (order, problem).
 template <class Body>
 static fe_status with_tensor(int k, bool el, Body body)
@@ -423,6 +538,33 @@ struct TensorBatch {
         return FE_OK;
     }
 };
+
+template <int K1, int PROB>
+static fe_status launch_plane(const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt, int64_t ncells, double *E,
+                              double *F, hipStream_t s)
+{
+    constexpr int CB = PlaneShape<K1, PROB>::CB;
+    hipLaunchKernelGGL((k3_plane_kernel<K1, PROB>), dim3((ncells + CB - 1) / CB), dim3((PlaneShape<K1, PROB>::BS)), 0, s,
+                       ma, pa, rt, ncells, E, F);
+    FE_HIP(hipGetLastError());
+    return FE_OK;
+}
+
+fe_status launch_integrate_plane(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
+                                 double *E, double *F, hipStream_t s)
+{
+    if (sa.ncells == 0) return FE_OK;
+    switch (sa.k * 2 + (pa.problem == FE_ELASTICITY ? 1 : 0)) {
+        case 3: return launch_plane<2, 1>(ma, pa, rt, sa.ncells, E, F, s);
+        case 4: return launch_plane<3, 0>(ma, pa, rt, sa.ncells, E, F, s);
+        case 5: return launch_plane<3, 1>(ma, pa, rt, sa.ncells, E, F, s);
+        case 6: return launch_plane<4, 0>(ma, pa, rt, sa.ncells, E, F, s);
+        case 7: return launch_plane<4, 1>(ma, pa, rt, sa.ncells, E, F, s);
+        case 8: return launch_plane<5, 0>(ma, pa, rt, sa.ncells, E, F, s);
+        case 9: return launch_plane<5, 1>(ma, pa, rt, sa.ncells, E, F, s);
+        default: return set_error(FE_EINVAL, "unsupported element size");
+    }
+}
 
 fe_status launch_integrate_tensor(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
                                   double *E, double *F, hipStream_t s)

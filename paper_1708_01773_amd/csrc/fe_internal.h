@@ -167,6 +167,9 @@ inline bool tensor_integrated(const SpaceArgs &sa, const ProblemArgs &pa)
 }
 fe_status launch_integrate_tensor(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
                                   double *E, double *F, hipStream_t s);
+// FP64 quadrilaterals of order >= 2 and 2D Q1 elasticity
+fe_status launch_integrate_plane(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const RefTables &rt,
+                                 double *E, double *F, hipStream_t s);
 fe_status launch_lift(const SpaceArgs &sa, const MeshArgs &ma, const ProblemArgs &pa, const int32_t *cell_dofs,
                       const ElemLayout &el, void *ws, hipStream_t s);
 

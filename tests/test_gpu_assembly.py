@@ -156,3 +156,21 @@ def test_sum_factorized_element_matrices(n, k, prob):
     for c, E in zip(cells, Es):
         assert rel(E, pair.oracle_element(c)) <= MATRIX_RTOL
         assert np.array_equal(E, E.T)
+
+
+# cells per workgroup of the 2D kernel: 28, 16, 10 (Poisson orders 2-4), 16, 7,
+# 4, 2 (elasticity orders 1-4); one cell, one less and a few more than a workgroup
+@pytest.mark.parametrize("k,prob,per", [(2, "poisson", 28), (3, "poisson", 16), (4, "poisson", 10),
+                                        (1, "elasticity", 16), (2, "elasticity", 7), (3, "elasticity", 4),
+                                        (4, "elasticity", 2)])
+def test_sum_factorized_plane_element_matrices(k, prob, per):
+    for n in ([1, 1], [per - 1, 1], [1, per + 1], [per + 3, 2]):
+        say(f"[plane] n={n} k={k} {prob}")
+        pair = Pair(2, n, k, prob, seed=84, source_kind=2, source=(0.5, 2.0))
+        A = pair.gpu_assembly()
+        cells = list(range(pair.P.ncells))
+        Es, Fs = element_matrices(pair, A, cells)
+        for c, E in zip(cells, Es):
+            assert rel(E, pair.oracle_element(c)) <= MATRIX_RTOL
+            assert np.array_equal(E, E.T)
+        assert rel(A.rhs[: A.n_rows].cpu().numpy(), pair.system.rhs) <= MATRIX_RTOL
