@@ -618,12 +618,22 @@ __global__ __launch_bounds__(256) void k5_entries_batch_kernel(const AsmJob *__r
 static bool by_runs(const SpaceArgs &sa) { return sa.ncomp == 3 && sa.k >= 2; }
 
 // Blocks of the cell-major scatter, a wave per node, nodes interleaved over a
-// grid that fills the chip: the most, measured (run by run, Q4 24^3 / Q3 32^3
-// FP64: 3000 blocks 6.63 / 4.26 ms, 5000 5.94 / 3.83, 8192 6.54 / 4.13; entry by
-// entry, scalar Q2 48^3: 2048 blocks 917 us, 8192 836).
+// grid that fills the chip.  Measured on large systems (run by run, Q4 24^3 /
+// Q3 32^3 FP64: 3000 blocks 6.63 / 4.26 ms, 5000 5.94 / 3.83, 8192 6.54 / 4.13;
+// entry by entry, scalar Q2 48^3: 2048 blocks 917 us, 8192 836).  Below, a last
+// round in which few waves have a node left would cost up to a third: every
+// wave takes the same number of nodes (scalar Q2 20x22x21 91 -> 76 us, Q3 20^3
+// 254 -> 236; elasticity Q2 18^3 183 -> 164, 26^3 485 -> 455, Q3 16^3 543 ->
+// 487), or one each (elasticity Q2 14x15x16 107 -> 78, Q4 8^3 244 -> 203).  Not
+// so Q4 run by run (12^3: 795 -> 952): its few heavy nodes want the uneven grid.
 static int64_t entries_grid(const SpaceArgs &sa)
 {
-    return std::min<int64_t>((sa.n_rows / sa.ncomp + 3) / 4, by_runs(sa) ? 5000 : 8192);
+    const int64_t nb = (sa.n_rows / sa.ncomp + 3) / 4;
+    const int64_t most = by_runs(sa) ? 5000 : 8192;
+    if (by_runs(sa) && nb <= 2 * most) return nb;
+    if (by_runs(sa) && sa.k == 4) return most;
+    const int64_t rounds = (nb + most - 1) / most;
+    return (nb + rounds - 1) / rounds;
 }
 
 fe_status launch_scatter(const SpaceArgs &sa, const ElemLayout &el, const void *ws, double *values, double *rhs,
