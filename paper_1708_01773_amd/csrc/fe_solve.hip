@@ -2190,6 +2190,7 @@ constexpr int kSmallThreads = 1024;
 constexpr int kSmallElems = 4;  // elements of each vector per thread
 constexpr int kSmallRegs = 16;  // matrix entries per thread held in registers
 constexpr int64_t kSmallMaxRows = kSmallThreads * kSmallElems;
+constexpr int64_t kSmallStreamed = 56 * 1024;  // most entries whose values come from L2
 constexpr int64_t kSmallLds = 156 * 1024;  // of the 160 KB of a CU; the rest for the static part
 
 __host__ __device__ constexpr int64_t align16(int64_t b) { return (b + 15) / 16 * 16; }
@@ -2914,13 +2915,15 @@ static SmallPlan small_plan(const PcgJob &jb)
     const int64_t vb = jb.fp32 ? 4 : 8;
     const int64_t all = small_bytes(jb.n, jb.nnz, vb), some = small_bytes(jb.n, jb.nnz, 0);
     if (all <= kSmallLds) sp.resident = 1;
-    else if (jb.sym || some > kSmallLds) return sp;
+    else if (jb.sym || some > kSmallLds || jb.nnz > kSmallStreamed) return sp;
     sp.kind = jb.sym ? kSmallSym : (jb.sa ? kSmallStruct : kSmallCsr);
     sp.lds = int32_t(sp.resident ? all : some);
     // lanes per row: enough that every thread has a row or part of one, and
-    // that a lane's share of a row is short
+    // that a lane's share of a row is short, shorter where values come from L2
+    // (shares of 24 / 12 / 6 entries: Q1 12^3 11.5 / 7.4 / 8.1 us, Q2 5^3 10.5 /
+    // 9.7 / 10.3, 2D Q2 20^2 9.2 / 7.8 / 8.5)
     const double avg = double(jb.nnz) / double(jb.n);
-    while (sp.lanes < 64 && (2 * sp.lanes * jb.n <= kSmallThreads || avg > 24.0 * sp.lanes)) sp.lanes *= 2;
+    while (sp.lanes < 64 && (2 * sp.lanes * jb.n <= kSmallThreads || avg > (sp.resident ? 24.0 : 12.0) * sp.lanes)) sp.lanes *= 2;
     sp.regs = sp.resident && sp.lanes * jb.n <= kSmallThreads;
     return sp;
 }
