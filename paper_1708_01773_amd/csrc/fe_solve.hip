@@ -1600,11 +1600,12 @@ static std::map<int, SpmvPlan> g_stuned;  // evaluated-pattern plans measured by
 // The plan of an evaluated-pattern system: the autotuned one of its class,
 // else short rows (at most 32 entries, instantiated lengths) two lanes per
 // row, longer rows eight rows per wave step.
-static SpmvPlan struct_plan_of_class(const SpaceArgs &sa)
+static SpmvPlan struct_plan_of_class(const SpaceArgs &sa, bool *tuned = nullptr)
 {
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_stuned.find(struct_class(sa));
+        if (tuned) *tuned = it != g_stuned.end();
         if (it != g_stuned.end()) return it->second;
     }
     int L = sa.ncomp;
@@ -1656,8 +1657,28 @@ static SpmvPlan launch_form(SpmvPlan pl, int64_t n)
     return pl;
 }
 
-// The plan an evaluated-pattern system is launched with.
-static SpmvPlan struct_plan(const SpaceArgs &sa) { return launch_form(struct_plan_of_class(sa), sa.n_rows); }
+// The plan an evaluated-pattern system is launched with: that of its class,
+// but for scalar systems of orders >= 2, where no plan was tuned, lanes per row
+// (the same sums to the last bit) in place of the block-staged traversal
+//  - at order 2, where the values fit the 256 MB memory-side cache and not the
+//    L2s: its short rows wait for the staged box more than for the values.
+//    Measured (block-staged / lanes per row, us per CG iteration, values): 26^3
+//    63 MB 38.4 / 34.5, 30^3 99 MB 45.5 / 43.8, 33^3 133 MB 58.1 / 51.5, 36^3
+//    174 MB 64.7 / 62.7; but 24^3 49 MB 29.2 / 31.7, 40^3 241 MB 75.0 / 81.6; Q3
+//    14^3 61 MB 32.2 / 36.3, 18^3 136 MB 55.2 / 56.5;
+//  - from order 3, where there is less than a chunk for each CU: Q3 8^3 20.7 /
+//    20.1, the product alone 10.5 / 9.0, Q4 6^3 27.2 / 25.4 and 16.5 / 13.2; Q3
+//    10^3 (381 chunks) 21.5 / 22.6.
+static SpmvPlan struct_plan(const SpaceArgs &sa)
+{
+    bool tuned = false;
+    const SpmvPlan pl = struct_plan_of_class(sa, &tuned);
+    if (!tuned && pl.mode == 6 && sa.ncomp == 1) {
+        const int64_t mb = 8 * sa.nnz >> 20;
+        if (sa.k == 2 ? mb >= 52 && mb < 200 : sa.n_rows < 256 * kXbRows) return SpmvPlan{2, 1, 8, 8};
+    }
+    return launch_form(pl, sa.n_rows);
+}
 
 // Modes 4 and 5 stage the values with 16-byte loads from 16-byte boundaries
 // of the array; values not 16-byte aligned take mode 3, the same summation
@@ -2907,7 +2928,10 @@ static void launch_rows(int which, const Group &g, const PcgProb *probs, hipStre
 // The one-workgroup plan of a system, or none.  The rule is LDS: p, q, row
 // starts and 16-bit columns have to fit (the symmetric storage also needs its
 // values there, being read out of row order).  Values that do not fit come
-// from L2.
+// from L2, at the rate one CU reads, up to 56 K of them (us per iteration, one
+// workgroup / three kernels: 2D Q1 60^2, 30625 entries 7.5 / 14.3, Q1 12^3, 29791
+// 7.4 / 14.2; but Q2 6^3, 59319 16.4 / 15.0): beside the larger systems of a batch
+// these iterations come on top.
 static SmallPlan small_plan(const PcgJob &jb)
 {
     SmallPlan sp{};
