@@ -62,7 +62,9 @@ __host__ __device__ __forceinline__ int64_t dg_prefix(const DgArgs &d, int64_t K
     return dg_prefix_n(d.dim, d.n[0], d.n[1], d.n[2], K);
 }
 
-// Facet neighbours of K and their column slots.  Facet f = 2 r + side
+// Facet neighbours of K and their column slots (the loops unrolled, so that the
+// arrays stay in registers: placed in LDS by the compiler they cost a read of
+// the dispatch packet, 12 us a launch).  Facet f = 2 r + side
 // (side 1: x_r grows); nb[f] = -1 on the boundary.  Slots number the cells
 // of K's row block in ascending id order: lower neighbours (far axis first),
 // K itself, upper neighbours.
@@ -71,6 +73,7 @@ __host__ __device__ __forceinline__ void dg_cell_faces(const DgArgs &d, int64_t 
 {
     const int64_t c[3] = {K % d.n[0], (K / d.n[0]) % d.n[1], d.dim == 3 ? K / (int64_t(d.n[0]) * d.n[1]) : 0};
     int s = 0;
+#pragma unroll
     for (int r = 2; r >= 0; r--) {
         if (r >= d.dim) continue;
         const bool has = c[r] > 0;
@@ -78,7 +81,9 @@ __host__ __device__ __forceinline__ void dg_cell_faces(const DgArgs &d, int64_t 
         slot[2 * r] = has ? s++ : -1;
     }
     self = s++;
-    for (int r = 0; r < d.dim; r++) {
+#pragma unroll
+    for (int r = 0; r < 3; r++) {
+        if (r >= d.dim) continue;
         const bool has = c[r] < d.n[r] - 1;
         nb[2 * r + 1] = has ? K + d.st[r] : -1;
         slot[2 * r + 1] = has ? s++ : -1;
@@ -131,7 +136,7 @@ struct DgShape {
     // 3D Q2: three cells (243 of 256 threads) beat one in 128 threads (896 us
     // against 857) and two in 192 (848 against 815)
     static constexpr int BS = NT > 256 ? 640 : (DIM == 3 && KO >= 2 ? 256 : 64);
-    static constexpr int CB = BS / NT;  // cells per workgroup
+    static constexpr int CB = BS / NT;  // most cells per workgroup
     // waves per SIMD asked of the register allocator: 3D Q2 takes 128 registers
     // instead of 136 and a fourth wave (857 -> 815 us at 32^3 with the element
     // matrices; a fifth spills, 1055)
@@ -297,7 +302,7 @@ template <int DIM, int KO>
 __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) void dg_cell_kernel(
     DgArgs d, MeshArgs m, ProblemArgs p, ElemLayout el, const double *__restrict__ E, const double *__restrict__ F,
     const int64_t *__restrict__ rowptr, double *__restrict__ values, double *__restrict__ rhs,
-    double *__restrict__ dinv)
+    double *__restrict__ dinv, int cells)
 {
     using S = DgShape<DIM, KO>;
     constexpr int K1 = S::K1, NN = S::NN, NF = S::NF, NP = S::NP, NFACE = S::NFACE, BS = S::BS, CB = S::CB;
@@ -308,12 +313,13 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
     __shared__ __attribute__((aligned(16))) double sS[CB][NFACE * NP * 8];
     __shared__ double sV[CB][1 + NFACE][NV][3];  // vertices of K (slot 0) and of the neighbour across facet f (1 + f)
     __shared__ double sPr[2][K1 * K1 * K1];      // phi_t phi_u and phi_t phi_u' at a 1D Gauss point, [(t K1 + u) K1 + q]
+    __shared__ double sL[K1 * K1], sD[K1 * K1], sG[2][K1];  // 1D tables: read by lane, so not from the arguments
     __shared__ double sSig[CB][NFACE];
     __shared__ int sSlot[CB][NFACE], sSelf[CB], sNc[CB];
 
-    const int64_t Kb = xcd_block(blockIdx.x, gridDim.x) * CB;
+    const int64_t Kb = xcd_block(blockIdx.x, gridDim.x) * cells;
     const int tid = threadIdx.x;
-    const int ncb = d.ncells - Kb < CB ? int(d.ncells - Kb) : CB;  // cells of this workgroup
+    const int ncb = d.ncells - Kb < cells ? int(d.ncells - Kb) : cells;  // cells of this workgroup
     if (tid < ncb) {
         int64_t nb[6];
         int slot[6], self, nc;
@@ -338,10 +344,13 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
         sV[ci][sl][v][1] = m.y[vid];
         sV[ci][sl][v][2] = DIM == 3 ? m.z[vid] : 0.0;
     }
-    for (int e = tid; e < K1 * K1 * K1; e += BS) {
-        const int t = e / (K1 * K1), u = e / K1 % K1, q = e % K1;
-        sPr[0][e] = d.L[t * K1 + q] * d.L[u * K1 + q];
-        sPr[1][e] = d.L[t * K1 + q] * d.D[u * K1 + q];
+    if (tid < K1 * K1) {
+        sL[tid] = d.L[tid];
+        sD[tid] = d.D[tid];
+    }
+    if (tid < K1) {
+        sG[0][tid] = d.gx[tid];
+        sG[1][tid] = d.gw[tid];
     }
     // the diagonal blocks start from the element matrices
     for (int e = tid; e < ncb * (NN * NN); e += BS) {
@@ -351,8 +360,8 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
     const int rc = tid / NN, rb = tid - rc * NN;  // row of the workgroup that this thread holds the rhs of
     double racc = rc < ncb ? F[(Kb + rc) * NN + rb] : 0.0;
     DgPair P;
-    const int ci = tid / NT;
-    const bool on = ci < ncb;
+    const int ci = CB == 1 ? 0 : tid / NT;  // one cell: what depends on it stays uniform
+    const bool on = CB == 1 ? tid < NT : ci < ncb;
     {
         const int pr = min(tid - ci * NT, NT - 1);
         P.t = pr / NF;
@@ -367,6 +376,11 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
     }
     __syncthreads();
 
+    for (int e = tid; e < K1 * K1 * K1; e += BS) {
+        const int t = e / (K1 * K1), u = e / K1 % K1, q = e % K1;
+        sPr[0][e] = sL[t * K1 + q] * sL[u * K1 + q];
+        sPr[1][e] = sL[t * K1 + q] * sD[u * K1 + q];
+    }
     // 1. the facet normal from the cell below the facet (K on its upper facets
     // and on the boundary), then J^-1 n there and on the other side
     for (int i = tid; i < ncb * (NFACE * NP); i += BS) {
@@ -384,7 +398,7 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
             const double er = mine == (side == 1) ? 1.0 : 0.0;  // reference coordinate along r
             double xi[3];
 #pragma unroll
-            for (int sx = 0; sx < 3; sx++) xi[sx] = sx == r ? er : (sx == t0 ? d.gx[q0] : (sx == t1 ? d.gx[q1] : 0.0));
+            for (int sx = 0; sx < 3; sx++) xi[sx] = sx == r ? er : (sx == t0 ? sG[0][q0] : (sx == t1 ? sG[0][q1] : 0.0));
             double X[NV][3], J[9], Ji[9], xq[3];
 #pragma unroll
             for (int v = 0; v < NV; v++)
@@ -406,7 +420,7 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
                 const double sgn = side ? 1.0 : -1.0;
 #pragma unroll
                 for (int c = 0; c < DIM; c++) n[c] = sgn * (n[c] / dS);
-                w = (d.gw[q0] * (DIM == 3 ? d.gw[q1] : 1.0)) * dS;
+                w = (sG[1][q0] * (DIM == 3 ? sG[1][q1] : 1.0)) * dS;
                 o[0] = w;
             }
 #pragma unroll
@@ -449,10 +463,10 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
             double sr = 0.0;
             for (int q = 0; q < NP; q++) {
                 const int i0 = bt0 * K1 + q % K1, i1 = bt1 * K1 + q / K1;
-                const double l0 = d.L[i0], l1 = DIM == 3 ? d.L[i1] : 1.0;
+                const double l0 = sL[i0], l1 = DIM == 3 ? sL[i1] : 1.0;
                 const double *__restrict__ v = sS[rc] + (f * NP + q) * 8;
-                double dn = v[1] * (de * l0 * l1) + v[2] * (le * d.D[i0] * l1);
-                if (DIM == 3) dn += v[3] * (le * l0 * d.D[i1]);
+                double dn = v[1] * (de * l0 * l1) + v[2] * (le * sD[i0] * l1);
+                if (DIM == 3) dn += v[3] * (le * l0 * sD[i1]);
                 double t = -d.tau * dn;
                 if (br == (side ? KO : 0)) t += sig * (v[0] * (l0 * l1));
                 sr += v[7] * t;
@@ -462,7 +476,7 @@ __global__ __launch_bounds__((DgShape<DIM, KO>::BS), (DgShape<DIM, KO>::MINW)) v
     }
     if (rc < ncb) rhs[(Kb + rc) * NN + rb] = racc;
 
-    const int cs = on ? ci : 0;
+    const int cs = CB > 1 && on ? ci : 0;
     const int64_t row0 = rowptr[(Kb + cs) * NN];
     const int rlen = sNc[cs] * NN;
     if (on) dg_axis<DIM, KO, 0>(d, P, sS[ci], sSig[ci], sSlot[ci], sDiag[ci], values + row0, rlen);
@@ -562,9 +576,16 @@ fe_status launch_dg_facets(int dim, const int32_t *n, int k, double gamma, doubl
     if (d.ncells == 0) return FE_OK;
     const double *E = static_cast<const double *>(ws);
     const double *F = reinterpret_cast<const double *>(static_cast<const char *>(ws) + el.f_offset);
-#define FE_DGK(D, KO)                                                                                  \
-    hipLaunchKernelGGL((dg_cell_kernel<D, KO>), dim3((d.ncells + DgShape<D, KO>::CB - 1) / DgShape<D, KO>::CB),        \
-                       dim3((DgShape<D, KO>::BS)), 0, s, d, ma, pa, el, E, F, rowptr, values, rhs, dinv)
+    // Few cells: a workgroup takes fewer of them, so that four workgroups a CU
+    // share the chain of phases (with the element matrices, 3D Q2 6x7x5 22.7 ->
+    // 19.9 us)
+#define FE_DGK(D, KO)                                                                                          \
+    {                                                                                                          \
+        const int cells = int(std::min<int64_t>(DgShape<D, KO>::CB, (d.ncells + 1023) / 1024));                \
+        hipLaunchKernelGGL((dg_cell_kernel<D, KO>), dim3((d.ncells + cells - 1) / cells),                      \
+                           dim3((DgShape<D, KO>::BS)), 0, s, d, ma, pa, el, E, F, rowptr, values, rhs, dinv,   \
+                           cells);                                                                             \
+    }
     if (dim == 3) {
         switch (k) {
             case 1: FE_DGK(3, 1); break;

@@ -212,3 +212,17 @@ def test_dg_cells_beside_the_workgroup_size(dim, k, per):
             assert rel(A.values[: A.nnz].cpu().numpy(), D.values) <= MATRIX_RTOL
             assert rel(A.rhs[: A.n_rows].cpu().numpy(), D.rhs) <= MATRIX_RTOL
             assert rel(A.dinv[: A.n_rows].cpu().numpy(), 1.0 / np.diag(D.dense())) <= MATRIX_RTOL
+
+
+# more than 1024 full workgroups of the facet kernel (fewer cells share less), and a ragged last one
+@pytest.mark.parametrize("dim,n,k", [(2, [128, 131], 1), (2, [85, 86], 2), (2, [64, 65], 3), (2, [45, 47], 4),
+                                     (3, [16, 16, 17], 1), (3, [14, 15, 15], 2)])
+def test_dg_cells_of_full_workgroups(dim, n, k):
+    say(f"[dg cells] dim={dim} n={n} k={k}")
+    v = structured_vertices(dim, n, jitter=0.2, seed=96)
+    mesh, coeff, A = gpu_dg(dim, n, k, v, penalty(k), 1.0)
+    D = O.DGSystem(O.Problem(dim, n, k, source_kind=1, source=(1.0,), dirichlet_kind=1, dirichlet_affine=AFF), v,
+                   gamma=penalty(k), tau=1.0)
+    assert D.ok
+    assert rel(A.values[: A.nnz].cpu().numpy(), D.values) <= MATRIX_RTOL
+    assert rel(A.rhs[: A.n_rows].cpu().numpy(), D.rhs) <= MATRIX_RTOL
