@@ -573,6 +573,9 @@ fe_status fe_pcg_solve_sym(fe_mesh mesh, int32_t order, const fe_coeff *coeff, c
  * and makes the fastest the plan of every matrix of the same row-length class
  * (half octaves of nnz / n_rows) in this process.  The plan fixes each row's
  * summation order: results are bitwise reproducible for a fixed plan table.
+ * A system of at most 4096 rows whose pattern fits the LDS of a CU is solved
+ * by one workgroup, without a plan, unless a plan of its class was tuned or
+ * set; then it is solved with that plan like any other.
  *   ws: device, fe_spmv_autotune_query bytes.  tried: host, up to max_tried
  *   entries (us = mean launch time in microseconds); chosen: host.
  *   Synchronizes.  fe_spmv_tuning_reset forgets every tuned plan. */

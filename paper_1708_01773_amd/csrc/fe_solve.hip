@@ -270,10 +270,11 @@ static SpmvPlan plan_for(int64_t n, int64_t nnz, bool *tuned = nullptr)
 // 262 MB 83.2 / 88.4.  The plan depends on the matrix alone, so a matrix is
 // summed alike alone and in a batch.
 constexpr int64_t kCsrCached = int64_t(200) << 20;  // bytes of columns and FP64 values
-static SpmvPlan csr_plan(int64_t n, int64_t nnz, const int32_t *colind, const void *val)
+static SpmvPlan csr_plan(int64_t n, int64_t nnz, const int32_t *colind, const void *val, bool *planned = nullptr)
 {
     bool tuned = false;
     const SpmvPlan pl = plan_for(n, nnz, &tuned);
+    if (planned) *planned = tuned;
     if (pl.mode == 9 && !tuned && 12 * nnz <= kCsrCached) return stream_plan(n > 0 ? double(nnz) / double(n) : 1.0);
     return csr_launch_form(pl, n, nnz, colind, val);
 }
@@ -1669,10 +1670,11 @@ static SpmvPlan launch_form(SpmvPlan pl, int64_t n)
 //  - from order 3, where there is less than a chunk for each CU: Q3 8^3 20.7 /
 //    20.1, the product alone 10.5 / 9.0, Q4 6^3 27.2 / 25.4 and 16.5 / 13.2; Q3
 //    10^3 (381 chunks) 21.5 / 22.6.
-static SpmvPlan struct_plan(const SpaceArgs &sa)
+static SpmvPlan struct_plan(const SpaceArgs &sa, bool *planned = nullptr)
 {
     bool tuned = false;
     const SpmvPlan pl = struct_plan_of_class(sa, &tuned);
+    if (planned) *planned = tuned;
     if (!tuned && pl.mode == 6 && sa.ncomp == 1) {
         const int64_t mb = 8 * sa.nnz >> 20;
         if (sa.k == 2 ? mb >= 52 && mb < 200 : sa.n_rows < 256 * kXbRows) return SpmvPlan{2, 1, 8, 8};
@@ -2932,10 +2934,12 @@ static void launch_rows(int which, const Group &g, const PcgProb *probs, hipStre
 // workgroup / three kernels: 2D Q1 60^2, 30625 entries 7.5 / 14.3, Q1 12^3, 29791
 // 7.4 / 14.2; but Q2 6^3, 59319 16.4 / 15.0): beside the larger systems of a batch
 // these iterations come on top.
-static SmallPlan small_plan(const PcgJob &jb)
+// planned: a plan of the system's class was tuned or set.  It fixes the order
+// in which the rows are summed, so such a system runs on it.
+static SmallPlan small_plan(const PcgJob &jb, bool planned)
 {
     SmallPlan sp{};
-    if (jb.dg || jb.n < 1 || jb.n > kSmallMaxRows || jb.nnz < 1 || jb.nnz > kSmallLds / 2) return sp;
+    if (planned || jb.dg || jb.n < 1 || jb.n > kSmallMaxRows || jb.nnz < 1 || jb.nnz > kSmallLds / 2) return sp;
     const int64_t vb = jb.fp32 ? 4 : 8;
     const int64_t all = small_bytes(jb.n, jb.nnz, vb), some = small_bytes(jb.n, jb.nnz, 0);
     if (all <= kSmallLds) sp.resident = 1;
@@ -2974,7 +2978,9 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
 {
     std::vector<int> order;
     std::vector<SpmvPlan> plans(njobs);
+    std::vector<SmallPlan> small(njobs);
     for (int i = 0; i < njobs; i++) {
+        bool planned = false;
         if (jobs[i].dg)  // DG: the cell-block traversal
             plans[i] = SpmvPlan{10, jobs[i].sa->dim, jobs[i].sa->nn, 0};
         else if (jobs[i].sa && jobs[i].fp32 && !jobs[i].sym)  // FP32 values: the block-staged traversal
@@ -2982,12 +2988,11 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         else if (jobs[i].sym)
             plans[i] = launch_form(SpmvPlan{7, 1, jobs[i].sa->dim == 3 ? 27 : 9, 2}, jobs[i].n);
         else
-            plans[i] = jobs[i].sa ? aligned_form(struct_plan(*jobs[i].sa), jobs[i].val)
-                                  : csr_plan(jobs[i].n, jobs[i].nnz, jobs[i].colind, jobs[i].val);
+            plans[i] = jobs[i].sa ? aligned_form(struct_plan(*jobs[i].sa, &planned), jobs[i].val)
+                                  : csr_plan(jobs[i].n, jobs[i].nnz, jobs[i].colind, jobs[i].val, &planned);
+        small[i] = small_plan(jobs[i], planned);
         if (jobs[i].n > 0) order.push_back(i);
     }
-    std::vector<SmallPlan> small(njobs);
-    for (int i = 0; i < njobs; i++) small[i] = small_plan(jobs[i]);
     auto key = [&](int i) {
         return (((plans[i].mode * 1024 + plans[i].rpb) * 4 + plans[i].nc) * 2 + (jobs[i].fp32 ? 1 : 0)) * 4 +
                (small[i].kind ? 1 + small[i].regs : 0);
