@@ -567,8 +567,9 @@ fe_status fe_pcg_solve_sym(fe_mesh mesh, int32_t order, const fe_coeff *coeff, c
 /* ------------------------------------------------------------------------ */
 /* A plan is how the CSR SpMV of fe_spmv / fe_pcg_solve / fe_pcg_solve_batch
  * walks the rows: mode 0 = wave-level CSR-stream with rows_per_wave rows
- * (1..32) per wave iteration, mode 1 = one wave per row.  Without tuning a
- * plan follows from the average row length nnz / n_rows; fe_spmv_autotune
+ * (1..32) per wave iteration, mode 1 = one wave per row, mode 9 = block tiles
+ * of rows_per_wave rows (4..256).  Without tuning a plan follows from n_rows
+ * and the average row length nnz / n_rows; fe_spmv_autotune
  * times every plan on a matrix (reps launches each, after a warm-up launch)
  * and makes the fastest the plan of every matrix of the same row-length class
  * (half octaves of nnz / n_rows) in this process.  The plan fixes each row's
@@ -638,10 +639,10 @@ fe_status fe_integrate_autotune(fe_mesh mesh, int32_t order, const fe_coeff *coe
                                 fe_k3_plan *chosen, fe_stream stream);
 fe_status fe_integrate_plan_of(fe_mesh mesh, int32_t order, const fe_coeff *coeff, fe_k3_plan *plan);
 
-/* The plan a matrix of n_rows rows and nnz entries gets now, and its class.
- * Where no plan of the class was tuned or set, a matrix of at most 200 MiB
- * (columns and FP64 values) is launched with the wave-level plan of its row
- * length instead of the block tiles reported here. */
+/* The plan a matrix of n_rows rows and nnz entries is launched with now, and
+ * its class: fe_spmv_plan_set with it leaves the products of fe_spmv as they
+ * are, to the last bit.  (Block tiles need colind and values 16-byte aligned;
+ * other matrices take the wave-level plan of their row length.) */
 fe_status fe_spmv_plan_of(int64_t n_rows, int64_t nnz, fe_spmv_plan *plan, int32_t *row_class);
 /* Makes `plan` (mode and rows_per_wave of one of the CSR plans fe_spmv_autotune
  * times; us is ignored) the plan of the row-length class of a matrix of n_rows

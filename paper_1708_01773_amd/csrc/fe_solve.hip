@@ -219,11 +219,27 @@ static std::map<int, SpmvPlan> g_tuned;
 // two in [4, 256] with R avg <= kTileRowsTarget entries (three passes; the
 // fastest tile sizes of the autotuner on the 128^3 Q1 and the Q2-Q4
 // elasticity matrices, 27 to 611 entries per row, lie at 3000-9000 entries).
+// A matrix of less than kTilesFew such tiles (eight for each CU) takes half the
+// rows per tile while half a tile still fills most of a pass: it stays in cache,
+// and an iteration is bound by the passes of the few tiles each CU has.
+// Measured per CG iteration (us, the larger / the smaller tiles; in a batch of
+// copies that together exceed the cache, the same): 25 entries a row, 4 MB 16.9 /
+// 14.7, 270 / 272; 27 (shuffled quadratic tetrahedra), 18 MB 22.2 / 20.1, 346 /
+// 350; 41 (cubic tetrahedra), 7 MB 32.7 / 21.1, 358 / 298; 52, 4 MB 19.6 / 16.5,
+// 240 / 247; 103, 21 MB 24.1 / 19.3, 213 / 223; 148, 17 MB 28.4 / 19.9, 200 / 197;
+// 162, 68 MB 45.8 / 36.9, 194 / 183; 292, 80 MB 50.5 / 37.5, 200 / 197.  A quarter
+// of the rows costs the batches 18-37%.  From kTilesFew on the smaller tiles gain
+// nothing (25 entries a row, 185 MB 65.1 / 67.1; 77, 182 MB 64.0 / 66.2).
+// The wave-level plans are faster still for one such matrix (148: 17.2; 292: 29.5)
+// but 1.1 to 1.9 times slower in a batch, and a batch sums a matrix as it is
+// summed alone, so the plan cannot depend on which it is.
 constexpr double kTileRowsTarget = 6144.0;
-static SpmvPlan heuristic_plan(double avg)
+constexpr int64_t kTilesFew = 2048;
+static SpmvPlan heuristic_plan(int64_t n, double avg)
 {
     int R = 256;
     while (R > 4 && R * avg > kTileRowsTarget) R /= 2;
+    if (R > 4 && R * avg >= 0.5 * kTileRowsTarget && (n + R - 1) / R < kTilesFew) R /= 2;
     SpmvPlan pl{};
     pl.mode = 9;
     pl.rpb = R;
@@ -255,28 +271,13 @@ static SpmvPlan plan_for(int64_t n, int64_t nnz, bool *tuned = nullptr)
         if (tuned) *tuned = it != g_tuned.end();
         if (it != g_tuned.end()) return it->second;
     }
-    return heuristic_plan(n > 0 ? double(nnz) / double(n) : 1.0);
+    return heuristic_plan(n, n > 0 ? double(nnz) / double(n) : 1.0);
 }
 
-// The plan a CSR matrix is launched with: that of its class, but the
-// wave-level plan of its row length where no plan was tuned and the matrix
-// stays in the 256 MB memory-side cache.  There an iteration is bound by the
-// latency of a block's first pass, and waves of their own, without block
-// barriers, shorten it.  Measured per CG iteration (block tiles / wave-level,
-// us, by entries per row): 25, 9 MB 17.4 / 15.5, 133 MB 51.7 / 41.6; 60, 41 MB
-// 27.0 / 25.2, 181 MB 63.8 / 57.0; 101, 15 MB 24.2 / 17.9; 170, 53 MB 34.4 /
-// 27.1, 182 MB 65.1 / 51.5; 310, 196 MB 74.6 / 45.6; 9, 87 MB 43.2 / 41.4.
-// Beyond it the tiles' wide loads win for long rows: 174, 372 MB 119 / 130; 61,
-// 262 MB 83.2 / 88.4.  The plan depends on the matrix alone, so a matrix is
-// summed alike alone and in a batch.
-constexpr int64_t kCsrCached = int64_t(200) << 20;  // bytes of columns and FP64 values
+// The plan a CSR matrix is launched with; planned: tuned or set for its class.
 static SpmvPlan csr_plan(int64_t n, int64_t nnz, const int32_t *colind, const void *val, bool *planned = nullptr)
 {
-    bool tuned = false;
-    const SpmvPlan pl = plan_for(n, nnz, &tuned);
-    if (planned) *planned = tuned;
-    if (pl.mode == 9 && !tuned && 12 * nnz <= kCsrCached) return stream_plan(n > 0 ? double(nnz) / double(n) : 1.0);
-    return csr_launch_form(pl, n, nnz, colind, val);
+    return csr_launch_form(plan_for(n, nnz, planned), n, nnz, colind, val);
 }
 
 // ---------------------------------------------------------------------------

@@ -61,3 +61,44 @@ def test_small_systems_take_the_plan_of_their_class(dim, n, k, prob, how):
             assert rel(x1.cpu().numpy(), x0.cpu().numpy()) <= 1e-8
     finally:
         F.spmv_tuning_reset()
+
+
+def _abs_product(A, x):
+    c = F.csr_struct(A.n_rows, A.nnz, A.rowptr, A.colind, A.values[: A.nnz].abs(), A.rhs, A.dinv)
+    y = torch.empty_like(x)
+    F.spmv(c, x.abs(), y)
+    return y
+
+
+# The reported plan is the launched one: setting it leaves the product as it
+# is.  Rows of 9 to 290 entries; tiles of 1536 to 6144 entries; in 2D Q2, 2042
+# and 2054 tiles of 256 rows (below 2048 half the rows are taken), one tile and
+# less than one.  The product is that of one wave per row up to rounding.
+@pytest.mark.parametrize("dim,n,k,prob,rows", [(2, [100, 90], 1, "poisson", 256), (2, [60, 50], 2, "poisson", 128),
+                                               (2, [362, 362], 2, "poisson", 128), (2, [363, 363], 2, "poisson", 256),
+                                               (3, [12, 13, 11], 1, "poisson", 128), (3, [20, 19, 21], 1, "poisson", 64),
+                                               (3, [9, 8, 10], 2, "poisson", 32), (3, [6, 5, 7], 3, "poisson", 32), (3, [9, 8, 9], 3, "poisson", 16),
+                                               (3, [6, 5, 5], 2, "elasticity", 16), (3, [4, 5, 4], 3, "elasticity", 8),
+                                               (2, [3, 3], 2, "poisson", None), (2, [2, 2], 1, "poisson", None)])
+def test_reported_csr_plan_is_the_launched_one(dim, n, k, prob, rows):
+    pair = Pair(dim, n, k, prob, seed=92)
+    A = pair.gpu_assembly()
+    say(f"[csr plan] dim {dim} n {n} k {k} {prob} rows {A.n_rows} nnz {A.nnz}")
+    x = torch.from_numpy(np.random.Generator(np.random.PCG64(93)).standard_normal(A.n_rows)).cuda()
+    y0, y1, y2 = (torch.full_like(x, float("nan")) for _ in range(3))
+    F.spmv_tuning_reset()
+    try:
+        mode, rpw, _ = F.spmv_plan_of(A.n_rows, A.nnz)
+        assert mode == 9 and rpw == (rows or rpw)
+        F.spmv(A.csr, x, y0)
+        F.spmv_plan_set(A.n_rows, A.nnz, mode, rpw)
+        F.spmv(A.csr, x, y1)
+        F.spmv_plan_set(A.n_rows, A.nnz, 1, 1)
+        F.spmv(A.csr, x, y2)
+        scale = _abs_product(A, x)
+        torch.cuda.synchronize()
+    finally:
+        F.spmv_tuning_reset()
+    assert torch.equal(y0, y1)
+    # a row of m entries, summed in two orders: each within m eps of the sum of magnitudes (m < 700)
+    assert bool(torch.all((y0 - y2).abs() <= 2 * 700 * 2.0 ** -53 * scale))
