@@ -603,6 +603,9 @@ fe_status fe_spmv_tuning_reset(void);
  * timed on A assembled on (mesh, order, coeff); the fastest
  * becomes the plan of every mesh system with the same longest row and
  * component count.  ws: fe_spmv_autotune_query(A->n_rows) bytes.
+ * fe_spmv_plan_of_mesh reports the plan the system is launched with now (which
+ * without tuning also depends on its size: setting it leaves the products of
+ * fe_spmv_mesh as they are, to the last bit) and its class.
  * fe_spmv_plan_set_mesh makes `plan` (mode and rows_per_wave of one of the
  * plans the autotuner would time; us is ignored) the plan of that class
  * without timing; FE_EINVAL for any other plan. */

@@ -1659,28 +1659,49 @@ static SpmvPlan launch_form(SpmvPlan pl, int64_t n)
     return pl;
 }
 
-// The plan an evaluated-pattern system is launched with: that of its class,
-// but for scalar systems of orders >= 2, where no plan was tuned, lanes per row
-// (the same sums to the last bit) in place of the block-staged traversal
-//  - at order 2, where the values fit the 256 MB memory-side cache and not the
-//    L2s: its short rows wait for the staged box more than for the values.
-//    Measured (block-staged / lanes per row, us per CG iteration, values): 26^3
-//    63 MB 38.4 / 34.5, 30^3 99 MB 45.5 / 43.8, 33^3 133 MB 58.1 / 51.5, 36^3
-//    174 MB 64.7 / 62.7; but 24^3 49 MB 29.2 / 31.7, 40^3 241 MB 75.0 / 81.6; Q3
-//    14^3 61 MB 32.2 / 36.3, 18^3 136 MB 55.2 / 56.5;
-//  - from order 3, where there is less than a chunk for each CU: Q3 8^3 20.7 /
-//    20.1, the product alone 10.5 / 9.0, Q4 6^3 27.2 / 25.4 and 16.5 / 13.2; Q3
-//    10^3 (381 chunks) 21.5 / 22.6.
-static SpmvPlan struct_plan(const SpaceArgs &sa, bool *planned = nullptr)
+static int grid_rows(int64_t n, const SpmvPlan &pl, const XbShape &xb = XbShape{});
+
+// The plan of an evaluated-pattern system, as launched and as reported (up to
+// launch_form): that of its class, but for scalar systems of orders >= 2, where
+// no plan was tuned, lanes per row (the same products to the last bit) in place
+// of the block-staged traversal
+//  - at order 2, where the values stay in the 256 MB memory-side cache and a
+//    block has more than two chunks: their barriers and staging, one chunk after
+//    the other, then weigh more than the loads (chunks are at most 64 rows, blocks
+//    as many as partial slots, one for 128 rows but at least 1024).  Measured
+//    (block-staged / lanes per row, us per CG iteration; chunks, blocks): 24^3
+//    28.4 / 30.9 (1692, 1024), 5x60x60 32.1 / 32.6 (2023, 1024); 25^3 33.2 / 31.9
+//    (2499, 1024), 26^3 37.8 / 33.6 (2601, 1040), 6x64x64 42.1 / 38.1 (3302,
+//    1392), 100x100x4 53.3 / 47.3 (4900, 2168), 33^3 57.3 / 50.7 (5525, 2152),
+//    36^3 63.5 / 61.6; 19 further bricks of 60 to 120 MB 0.98 to 1.07.  From
+//    memory the loads decide: 40^3 (229 MB) 73.1 / 77.8, 50^3 151.3 / 182.3;
+//  - from order 3, where there is less than a chunk for each CU: Q3 8^3 20.2 /
+//    19.4, Q4 5^3 26.3 / 24.7, 6^3 26.5 / 25.1, 9x5x6 27.8 / 26.8; Q3 10^3 (435
+//    chunks) 21.0 / 21.8, Q4 8^3 (496) 31.4 / 32.1.
+// In a batch that exceeds the cache the block-staged traversal is the faster one
+// at every size (Q2 26^3 x 8 185 / 226, Q3 8^3 x 40 137 / 196), but a system's
+// partial sums, so its iterates, depend on the traversal, and a batch gives the
+// iterates of the system alone: the plan follows from the system, not the use.
+static SpmvPlan struct_plan_reported(const SpaceArgs &sa, bool *planned = nullptr)
 {
     bool tuned = false;
     const SpmvPlan pl = struct_plan_of_class(sa, &tuned);
     if (planned) *planned = tuned;
     if (!tuned && pl.mode == 6 && sa.ncomp == 1) {
-        const int64_t mb = 8 * sa.nnz >> 20;
-        if (sa.k == 2 ? mb >= 52 && mb < 200 : sa.n_rows < 256 * kXbRows) return SpmvPlan{2, 1, 8, 8};
+        constexpr int64_t kCached = int64_t(200) << 20;  // bytes of values
+        bool rows = sa.n_rows < 256 * kXbRows;
+        if (sa.k == 2) {
+            const XbShape xb = xb_shape(sa, pl.rpb);
+            rows = 8 * sa.nnz < kCached && xb.nchunks > 2 * grid_rows(sa.n_rows, pl, xb);
+        }
+        if (rows) return SpmvPlan{2, 1, 8, 8};
     }
-    return launch_form(pl, sa.n_rows);
+    return pl;
+}
+
+static SpmvPlan struct_plan(const SpaceArgs &sa, bool *planned = nullptr)
+{
+    return launch_form(struct_plan_reported(sa, planned), sa.n_rows);
 }
 
 // Modes 4 and 5 stage the values with 16-byte loads from 16-byte boundaries
@@ -2531,7 +2552,7 @@ __global__ __launch_bounds__(kBlock) void resid_finish_kernel(const PcgProb *__r
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-static int grid_rows(int64_t n, const SpmvPlan &pl, const XbShape &xb = XbShape{})
+static int grid_rows(int64_t n, const SpmvPlan &pl, const XbShape &xb)
 {
     if (pl.mode == 6) {  // a block per chunk, at most one per partial slot; a multiple of 8 (XCD-contiguous chunks)
         const int64_t cap = part_slots(n) / 8 * 8;
@@ -2838,7 +2859,7 @@ fe_status spmv_plan_set_struct(const SpaceArgs &sa, const fe_spmv_plan &plan)
 
 void spmv_plan_of_struct(const SpaceArgs &sa, fe_spmv_plan *plan, int32_t *cls)
 {
-    const SpmvPlan pl = struct_plan_of_class(sa);
+    const SpmvPlan pl = struct_plan_reported(sa);
     if (plan) *plan = fe_spmv_plan{pl.mode, pl.rpb, 0.0};
     if (cls) *cls = struct_class(sa);
 }

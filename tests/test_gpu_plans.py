@@ -102,3 +102,42 @@ def test_reported_csr_plan_is_the_launched_one(dim, n, k, prob, rows):
     assert torch.equal(y0, y1)
     # a row of m entries, summed in two orders: each within m eps of the sum of magnitudes (m < 700)
     assert bool(torch.all((y0 - y2).abs() <= 2 * 700 * 2.0 ** -53 * scale))
+
+
+# The same for the evaluated pattern.  Scalar order 2: two chunks a block (24^3,
+# 5x60x60) and more (25^3, 6x64x64), values below and past what stays cached (38^3,
+# 39^3); orders 3 and 4 below and past a chunk for each CU; vector and 2D classes.
+# Plans (2, 8) and (6, 8) give the same products to the last bit.
+@pytest.mark.parametrize("dim,n,k,prob,plan", [(3, [24, 24, 24], 2, "poisson", (6, 8)), (3, [25, 25, 25], 2, "poisson", (2, 8)),
+                                               (3, [5, 60, 60], 2, "poisson", (6, 8)), (3, [6, 64, 64], 2, "poisson", (2, 8)),
+                                               (3, [38, 38, 38], 2, "poisson", (2, 8)), (3, [39, 39, 39], 2, "poisson", (6, 8)),
+                                               (3, [8, 8, 8], 3, "poisson", (2, 8)), (3, [9, 9, 9], 3, "poisson", (6, 8)),
+                                               (3, [6, 6, 6], 4, "poisson", (2, 8)), (3, [7, 7, 7], 4, "poisson", (6, 8)),
+                                               (3, [5, 6, 7], 2, "elasticity", (6, 4)), (2, [40, 30], 3, "poisson", (2, 8)),
+                                               (3, [9, 8, 7], 1, "poisson", (4, 27))])
+def test_reported_mesh_plan_is_the_launched_one(dim, n, k, prob, plan):
+    pair = Pair(dim, n, k, prob, jitter=0.1, seed=94)
+    A = pair.gpu_assembly()
+    say(f"[mesh plan] dim {dim} n {n} k {k} {prob} rows {A.n_rows} nnz {A.nnz}")
+    x = torch.from_numpy(np.random.Generator(np.random.PCG64(95)).standard_normal(A.n_rows)).cuda()
+    ys = []
+    F.spmv_tuning_reset()
+    try:
+        rep = F.spmv_plan_of_mesh(pair.mesh, k, pair.coeff)[:2]
+        assert rep == plan
+        plans = [None, rep] + ([(2, 8), (6, 8)] if plan[1] == 8 else [])
+        for p in plans:
+            if p:
+                F.spmv_plan_set_mesh(pair.mesh, k, pair.coeff, *p)
+                assert F.spmv_plan_of_mesh(pair.mesh, k, pair.coeff)[:2] == p
+            y = torch.full_like(x, float("nan"))
+            F.spmv_mesh(pair.mesh, k, pair.coeff, A.csr, x, y)
+            ys.append(y)
+        yc = torch.empty_like(x)
+        F.spmv(A.csr, x, yc)
+        scale = _abs_product(A, x)
+        torch.cuda.synchronize()
+    finally:
+        F.spmv_tuning_reset()
+    assert all(torch.equal(y, ys[0]) for y in ys[1:])
+    assert bool(torch.all((ys[0] - yc).abs() <= 2 * 800 * 2.0 ** -53 * scale))  # rows of at most 729 entries
