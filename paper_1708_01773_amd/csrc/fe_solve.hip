@@ -3106,15 +3106,41 @@ fe_status engine_init(EngineSet &E, hipStream_t s)
     return FE_OK;
 }
 
+// The one-workgroup kernel by value type and form (REGS).
+static auto small_kernel(bool fp32, bool regs)
+{
+    if (regs) return fp32 ? pcg_small_kernel<float, true> : pcg_small_kernel<double, true>;
+    return fp32 ? pcg_small_kernel<float, false> : pcg_small_kernel<double, false>;
+}
+
+// Raises the dynamic LDS these kernels may be launched with to the most a
+// system takes, once per device.  The limit belongs to the process: set for
+// each launch to what that launch needs, one thread could lower it between
+// another's set and launch.
+static fe_status allow_small_lds()
+{
+    static std::mutex mu;
+    static std::vector<char> done;
+    int dev = 0;
+    FE_HIP(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(mu);
+    if (int(done.size()) <= dev) done.resize(dev + 1, 0);
+    if (done[dev]) return FE_OK;
+    for (int f = 0; f < 4; f++)
+        FE_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(small_kernel(f & 1, f & 2)),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallLds)));
+    done[dev] = 1;
+    return FE_OK;
+}
+
 // iters iterations of the one-workgroup systems still running.
 static fe_status engine_small(const EngineSet &E, int iters, hipStream_t q)
 {
     for (const Group &g : E.groups) {
         if (!g.small) continue;
-        void (*const f)(const PcgProb *, int) = g.small == 2 ? (g.fp32 ? pcg_small_kernel<float, true> : pcg_small_kernel<double, true>)
-                                                             : (g.fp32 ? pcg_small_kernel<float, false> : pcg_small_kernel<double, false>);
-        if (g.small_lds > 64 * 1024)
-            FE_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(f), hipFuncAttributeMaxDynamicSharedMemorySize, g.small_lds));
+        const fe_status st = allow_small_lds();
+        if (st != FE_OK) return st;
+        const auto f = small_kernel(g.fp32, g.small == 2);
         f<<<dim3(g.count), dim3(kSmallThreads), g.small_lds, q>>>(E.d_probs + g.first, iters);
     }
     return FE_OK;
