@@ -2225,7 +2225,10 @@ __global__ __launch_bounds__(kBlock) void pcg_dir_kernel(const PcgProb *__restri
 // the kernel boundaries.  A system that gives every thread at most one row (or
 // a lane's share of one) of at most 16 entries holds its matrix in registers
 // (REGS), so that a product reads nothing but the gathered p from LDS.  What bounds it is LDS and barrier
-// latency, or the values from L2 at the rate one CU reads.  Scalars, stop test and state
+// latency, or the values from L2 at the rate one CU reads.  A row far longer than the
+// average (more than kSmallLong entries a lane; no finite element matrix has one) would be
+// a chain of its own: it is summed by a whole wave (4000 rows, one of them dense, us per
+// iteration, three kernels / by its lanes / by a wave: 152 / 172 / 7.8).  Scalars, stop test and state
 // are those of the three kernels, so a launch may take any number of
 // iterations and the next go on from the state.
 // The matrix comes from the CSR arrays, from the values in CSR order with the
@@ -2234,6 +2237,7 @@ __global__ __launch_bounds__(kBlock) void pcg_dir_kernel(const PcgProb *__restri
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallElems = 4;  // elements of each vector per thread
 constexpr int kSmallRegs = 16;  // matrix entries per thread held in registers
+constexpr int kSmallLong = 128; // most entries of a row per lane of its lane group
 constexpr int64_t kSmallMaxRows = kSmallThreads * kSmallElems;
 constexpr int64_t kSmallStreamed = 56 * 1024;  // most entries whose values come from L2
 constexpr int64_t kSmallLds = 156 * 1024;  // of the 160 KB of a CU; the rest for the static part
@@ -2410,6 +2414,15 @@ __global__ __launch_bounds__(kSmallThreads) void pcg_small_kernel(const PcgProb 
             rcol[u] = t < e ? scol[t] : uint16_t(myrow);
         }
     }
+    // rows longer than this are summed by whole waves, in a pass of their own
+    int cut = INT32_MAX;
+    if constexpr (!REGS) {
+        if (tid == 0) longest = 0;
+        __syncthreads();
+        for (int row = tid; row < n; row += kSmallThreads) atomicMax(&longest, int(sstart[row + 1] - sstart[row]));
+        __syncthreads();
+        if (longest > kSmallLong * LW) cut = kSmallLong * LW;
+    }
     int stop = 0, status = FE_OK;
     for (int it = 0; it < iters && !stop; it++) {
         const int flip = it & 1;
@@ -2419,9 +2432,15 @@ __global__ __launch_bounds__(kSmallThreads) void pcg_small_kernel(const PcgProb 
             for (int r0 = 0; r0 < n; r0 += rpp) {
                 const int row = r0 + tid / LW;
                 double a = 0.0;
-                if (row < n) {
+                bool mine = row < n;
+                if (mine) {
                     const int b = int(sstart[row]), e = int(sstart[row + 1]);
                     int t = b + sub;
+                    if constexpr (!REGS)
+                        if (e - b > cut) {
+                            mine = false;
+                            t = e;
+                        }
                     for (; t + 3 * LW < e; t += 4 * LW) {
                         double m[4], xx[4];
 #pragma unroll
@@ -2435,9 +2454,29 @@ __global__ __launch_bounds__(kSmallThreads) void pcg_small_kernel(const PcgProb 
                     for (; t < e; t += LW) a = fma(double(val[t]), sp[scol[t]], a);
                 }
                 for (int off = LW / 2; off > 0; off >>= 1) a += __shfl_xor(a, off);
-                if (row < n && sub == 0) {
+                if (mine && sub == 0) {
                     sq[row] = a;
                     v1[0] = fma(sp[row], a, v1[0]);
+                }
+            }
+            if (REGS || cut == INT32_MAX) return;
+            // the long rows of 64 at a time, by the wave that has them
+            const int lane = tid % 64;
+            for (int r0 = tid - lane; r0 < n; r0 += kSmallThreads) {
+                const int l = r0 + lane;
+                uint64_t rest = __ballot(l < n && int(sstart[min(l, n - 1) + 1] - sstart[min(l, n - 1)]) > cut);
+                while (rest) {
+                    const int row = r0 + __ffsll(static_cast<unsigned long long>(rest)) - 1;
+                    rest &= rest - 1;
+                    const int e = int(sstart[row + 1]);
+                    double a = 0.0;
+#pragma unroll 4
+                    for (int t = int(sstart[row]) + lane; t < e; t += 64) a = fma(double(val[t]), sp[scol[t]], a);
+                    a = wave_sum(a);
+                    if (lane == 0) {
+                        sq[row] = a;
+                        v1[0] = fma(sp[row], a, v1[0]);
+                    }
                 }
             }
         };
