@@ -114,6 +114,33 @@ struct SmallPlan {
     int32_t lds = 0;            // bytes of LDS
 };
 
+// Limits of the one-workgroup solver.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallElems = 4;  // elements of each vector per thread
+constexpr int kSmallRegs = 16;  // matrix entries per thread held in registers
+constexpr int kSmallLong = 128; // most entries of a row per lane of its lane group
+constexpr int64_t kSmallMaxRows = kSmallThreads * kSmallElems;
+constexpr int64_t kSmallStreamed = 56 * 1024;  // most entries whose values come from L2
+constexpr int64_t kSmallLds = 156 * 1024;  // of the 160 KB of a CU; the rest for the static part
+
+__host__ __device__ constexpr int64_t align16(int64_t b) { return (b + 15) / 16 * 16; }
+
+// p, q | row starts | columns | values (when resident)
+__host__ __device__ constexpr int64_t small_bytes(int64_t n, int64_t nnz, int64_t resident_value)
+{
+    return align16(16 * n) + align16(4 * (n + 1)) + align16(2 * nnz) + align16(resident_value * nnz);
+}
+
+// Whether the one-workgroup solver can hold a matrix of n rows and nnz values
+// of vb bytes; resident: its values too (else they come from L2).
+static bool small_fits(int64_t n, int64_t nnz, int64_t vb, bool &resident)
+{
+    resident = false;
+    if (n < 1 || n > kSmallMaxRows || nnz < 1 || nnz > kSmallLds / 2) return false;
+    resident = small_bytes(n, nnz, vb) <= kSmallLds;
+    return resident || (small_bytes(n, nnz, 0) <= kSmallLds && nnz <= kSmallStreamed);
+}
+
 // One problem of a (possibly batched) solve, as the kernels see it.
 struct PcgProb {
     int64_t n, nnz;
@@ -233,13 +260,19 @@ static std::map<int, SpmvPlan> g_tuned;
 // The wave-level plans are faster still for one such matrix (148: 17.2; 292: 29.5)
 // but 1.1 to 1.9 times slower in a batch, and a batch sums a matrix as it is
 // summed alone, so the plan cannot depend on which it is.
+// A matrix that the one-workgroup solver holds is iterated without a plan; its
+// products alone are spread over the chip in tiles of at most 16 rows (us out of
+// cache: 961 rows, 8281 entries 8.8 / 6.4, 729 rows, 29791 entries 18.2 / 6.8).
 constexpr double kTileRowsTarget = 6144.0;
 constexpr int64_t kTilesFew = 2048;
-static SpmvPlan heuristic_plan(int64_t n, double avg)
+static SpmvPlan heuristic_plan(int64_t n, int64_t nnz)
 {
+    const double avg = n > 0 ? double(nnz) / double(n) : 1.0;
     int R = 256;
     while (R > 4 && R * avg > kTileRowsTarget) R /= 2;
     if (R > 4 && R * avg >= 0.5 * kTileRowsTarget && (n + R - 1) / R < kTilesFew) R /= 2;
+    bool resident;
+    if (small_fits(n, nnz, 8, resident)) R = std::min(R, 16);
     SpmvPlan pl{};
     pl.mode = 9;
     pl.rpb = R;
@@ -271,7 +304,7 @@ static SpmvPlan plan_for(int64_t n, int64_t nnz, bool *tuned = nullptr)
         if (tuned) *tuned = it != g_tuned.end();
         if (it != g_tuned.end()) return it->second;
     }
-    return heuristic_plan(n, n > 0 ? double(nnz) / double(n) : 1.0);
+    return heuristic_plan(n, nnz);
 }
 
 // The plan a CSR matrix is launched with; planned: tuned or set for its class.
@@ -2234,22 +2267,6 @@ __global__ __launch_bounds__(kBlock) void pcg_dir_kernel(const PcgProb *__restri
 // The matrix comes from the CSR arrays, from the values in CSR order with the
 // columns evaluated, or from the symmetric storage of a Q1 scalar system.
 // ---------------------------------------------------------------------------
-constexpr int kSmallThreads = 1024;
-constexpr int kSmallElems = 4;  // elements of each vector per thread
-constexpr int kSmallRegs = 16;  // matrix entries per thread held in registers
-constexpr int kSmallLong = 128; // most entries of a row per lane of its lane group
-constexpr int64_t kSmallMaxRows = kSmallThreads * kSmallElems;
-constexpr int64_t kSmallStreamed = 56 * 1024;  // most entries whose values come from L2
-constexpr int64_t kSmallLds = 156 * 1024;  // of the 160 KB of a CU; the rest for the static part
-
-__host__ __device__ constexpr int64_t align16(int64_t b) { return (b + 15) / 16 * 16; }
-
-// p, q | row starts | columns | values (when resident)
-__host__ __device__ constexpr int64_t small_bytes(int64_t n, int64_t nnz, int64_t resident_value)
-{
-    return align16(16 * n) + align16(4 * (n + 1)) + align16(2 * nnz) + align16(resident_value * nnz);
-}
-
 // Sum over the wave, the same in every lane, without LDS: quads, then halves
 // and rows of 16 by mirrored moves, then the four rows through scalar
 // registers (a butterfly of lane exchanges through LDS has six dependent
@@ -3000,13 +3017,12 @@ static void launch_rows(int which, const Group &g, const PcgProb *probs, hipStre
 static SmallPlan small_plan(const PcgJob &jb, bool planned)
 {
     SmallPlan sp{};
-    if (planned || jb.dg || jb.n < 1 || jb.n > kSmallMaxRows || jb.nnz < 1 || jb.nnz > kSmallLds / 2) return sp;
     const int64_t vb = jb.fp32 ? 4 : 8;
-    const int64_t all = small_bytes(jb.n, jb.nnz, vb), some = small_bytes(jb.n, jb.nnz, 0);
-    if (all <= kSmallLds) sp.resident = 1;
-    else if (jb.sym || some > kSmallLds || jb.nnz > kSmallStreamed) return sp;
+    bool resident = false;
+    if (planned || jb.dg || !small_fits(jb.n, jb.nnz, vb, resident) || (jb.sym && !resident)) return sp;
+    sp.resident = resident;
     sp.kind = jb.sym ? kSmallSym : (jb.sa ? kSmallStruct : kSmallCsr);
-    sp.lds = int32_t(sp.resident ? all : some);
+    sp.lds = int32_t(small_bytes(jb.n, jb.nnz, resident ? vb : 0));
     // lanes per row: enough that every thread has a row or part of one, and
     // that a lane's share of a row is short, shorter where values come from L2
     // (shares of 24 / 12 / 6 entries: Q1 12^3 11.5 / 7.4 / 8.1 us, Q2 5^3 10.5 /
