@@ -3366,6 +3366,11 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
                 FE_HIP(hipGraphLaunch(hold.e, s));
                 j += gchunk;
             } else {
+                // a solve of many iterations reads the counter less often: counter
+                // and event cost 3.5 us a chunk, an iteration run in vain (at most
+                // two chunks of a 64th of the solve) some 6 us.  10012 iterations
+                // of 136 us: 1375.5 ms in chunks of 8, 1371.2 now
+                if (!no_alloc) chunk = std::max(8, std::min(64, j / 64));
                 const int todo = std::min(chunk, maxit - j);
                 if ((st = engine_small(E, todo, s)) != FE_OK) return st;
                 for (int i = 0; i < todo; i++, j++) {
