@@ -390,14 +390,13 @@ __device__ __forceinline__ RowGeom row_geom_closed(const SpaceArgs &s, const Axi
 // x -- column node, component, the one or two cells -- in registers for the
 // whole node, and a run needs two table reads per lane instead of a decode and
 // six per entry.  Every first contribution of two runs of NC rows (three for
-// FP32 entries) is loaded before any is used; the others (runs through the row node's own line or
-// plane, entries of its own column) follow in ascending cell order.
+// FP32 entries) is loaded before any is used; the others (runs through the row
+// node's own line or plane, entries of its own column) follow in ascending cell
+// order.
 // What bounds it: HBM, E read once and the values written once, and the waves
 // in flight (107 registers: four per SIMD; six loads per row in flight need
 // 147 and are slower).  Every first contribution is loaded unconditionally.
-// Entry by entry, Q4 24^3 took 6.90 ms from FP64 entries, Q3 32^3 4.19 from
-// FP64 and 3.99 from FP32, Q2 48^3 2.80 and 2.82; now 5.94, 3.83, 3.51, 2.77
-// and 2.63 (Q4: 4.7 TB/s; a copy reaches 5.1).
+// Where it is taken, and what it gives, see by_runs.
 template <int NC, int GL, typename ET>
 __device__ __forceinline__ void node_runs(const SpaceArgs &s, const RowGeom &g, const RowTables &t,
                                           const ET *__restrict__ E, double *__restrict__ values,
@@ -612,26 +611,45 @@ __global__ __launch_bounds__(256) void k5_entries_batch_kernel(const AsmJob *__r
     k5_entries_body<NC, ET, RUNS>(J.s, static_cast<const ET *>(J.E), J.F, J.values, J.rhs, J.dinv, lb, nb);
 }
 
-// Whether a space's rows are scattered run by run (node_runs): 3D vector
-// problems of order >= 2.  Rows of Q1 elasticity (runs of 9 in 16 lanes) took
-// 667 us at 60^3 that way, 440 entry by entry.
-static bool by_runs(const SpaceArgs &sa) { return sa.ncomp == 3 && sa.k >= 2; }
+// Whether the rows of 3D vector problems of order >= 2 are scattered run by run
+// (node_runs) or entry by entry; the sums are the same to the last bit.  blocks:
+// those of a wave per node, in a batch the blocks of its launch.  Measured inside
+// assemblies, us, entry by entry / run by run (median of three, FP64; FP32 entries):
+//   Q4 24^3 6209 / 6004; 5123 / 4781, 12^3 894 / 836; 785 / 697, 8^3 286 / 273;
+//     261 / 230, 15x11x17 1312 / 1427; 1075 / 1087: run by run;
+//   Q3 32^3 3804 / 3971; 3478 / 3548, 16^3 544 / 575; 541 / 521, 23x17x21 1038 /
+//     1129; 1037 / 957, 9x10x14 180 / 199; 161 / 153: from FP32 entries only;
+//   Q2 48^3 2483 / 2818; 2453 / 2674, 24^3 348 / 422; 363 / 391, 33x41x29 927 /
+//     1033; 944 / 944, 18^3 155 / 186; 126 / 127: entry by entry;
+//   few nodes, whose time is the chain of one wave: Q2 12^3 47 / 42; 49 / 42, 8^3
+//     24 / 20; 24 / 20, Q3 6^3 42 / 37; 40 / 34, Q4 4^3 67 / 41; 62 / 37: run by run
+//     (a longer run of columns is one step of it instead of several).
+// Rows of Q1 elasticity (runs of 9 in 16 lanes) took 667 us at 60^3 run by run, 440
+// entry by entry.
+constexpr int64_t kFewNodeBlocks = 4096;
+static bool by_runs(const SpaceArgs &sa, int32_t elem_bytes, int64_t blocks)
+{
+    if (sa.ncomp != 3 || sa.k < 2) return false;
+    return sa.k == 4 || (sa.k == 3 && elem_bytes == 4) || blocks <= kFewNodeBlocks;
+}
 
 // Blocks of the cell-major scatter, a wave per node, nodes interleaved over a
-// grid that fills the chip.  Measured on large systems (run by run, Q4 24^3 /
-// Q3 32^3 FP64: 3000 blocks 6.63 / 4.26 ms, 5000 5.94 / 3.83, 8192 6.54 / 4.13;
-// entry by entry, scalar Q2 48^3: 2048 blocks 917 us, 8192 836).  Below, a last
-// round in which few waves have a node left would cost up to a third: every
-// wave takes the same number of nodes (scalar Q2 20x22x21 91 -> 76 us, Q3 20^3
-// 254 -> 236; elasticity Q2 18^3 183 -> 164, 26^3 485 -> 455, Q3 16^3 543 ->
-// 487), or one each (elasticity Q2 14x15x16 107 -> 78, Q4 8^3 244 -> 203).  Not
-// so Q4 run by run (12^3: 795 -> 952): its few heavy nodes want the uneven grid.
-static int64_t entries_grid(const SpaceArgs &sa)
+// grid that fills the chip.  Measured on large systems (run by run, Q4 24^3
+// FP64: 3000 blocks 6.63 ms, 5000 5.94, 8192 6.54; entry by entry, scalar Q2
+// 48^3: 2048 blocks 917 us, 8192 836).  Below, a last round in which few waves
+// have a node left would cost up to a third: every wave takes the same number of
+// nodes (scalar Q2 20x22x21 91 -> 76 us, Q3 20^3 254 -> 236; elasticity Q2 24^3
+// 381 -> 348), or one each (elasticity Q2 14x15x16 107 -> 78, Q4 8^3 244 -> 203).
+// Not so vector problems of order 4 (12^3: 795 -> 952) and, entry by entry, 3
+// (23x17x21 1038 -> 1118, 32^3 3804 -> 3866): their few heavy nodes want the
+// uneven grid.
+static int64_t entries_grid(const SpaceArgs &sa, int32_t elem_bytes)
 {
     const int64_t nb = (sa.n_rows / sa.ncomp + 3) / 4;
-    const int64_t most = by_runs(sa) ? 5000 : 8192;
-    if (by_runs(sa) && nb <= 2 * most) return nb;
-    if (by_runs(sa) && sa.k == 4) return most;
+    const bool runs = by_runs(sa, elem_bytes, nb);
+    const int64_t most = runs ? 5000 : 8192;
+    if (runs && nb <= 2 * most) return nb;
+    if (sa.ncomp == 3 && (sa.k == 4 || (sa.k == 3 && !runs))) return std::min(nb, most);
     const int64_t rounds = (nb + most - 1) / most;
     return (nb + rounds - 1) / rounds;
 }
@@ -657,7 +675,7 @@ fe_status launch_scatter(const SpaceArgs &sa, const ElemLayout &el, const void *
         }
 #undef FE_K5Q
     } else {
-        const int64_t grid = entries_grid(sa);
+        const int64_t grid = entries_grid(sa, el.elem_bytes);
 #define FE_K5E(NCV, T, R)                                                                                           \
     hipLaunchKernelGGL((k5_entries_kernel<NCV, T, R>), dim3(grid), dim3(256), 0, s, sa, static_cast<const T *>(ws), F, \
                        values, rhs, dinv)
@@ -667,7 +685,7 @@ fe_status launch_scatter(const SpaceArgs &sa, const ElemLayout &el, const void *
         } else if (sa.ncomp == 2) {
             if (el.elem_bytes == 8) FE_K5E(2, double, false);
             else FE_K5E(2, float, false);
-        } else if (by_runs(sa)) {
+        } else if (by_runs(sa, el.elem_bytes, (sa.n_rows / sa.ncomp + 3) / 4)) {
             if (el.elem_bytes == 8) FE_K5E(3, double, true);
             else FE_K5E(3, float, true);
         } else {
@@ -685,7 +703,7 @@ int64_t scatter_blocks(const SpaceArgs &sa, const ElemLayout &el)
 {
     if (sa.n_rows == 0) return 0;
     if (el.cb > 1) return (q1_chunks(sa) + 3) / 4;
-    return entries_grid(sa);
+    return entries_grid(sa, el.elem_bytes);
 }
 
 fe_status launch_scatter_batch(const AsmJob &h, const ElemLayout &el, const AsmJob *jobs, const int32_t *boff,
@@ -714,7 +732,7 @@ fe_status launch_scatter_batch(const AsmJob &h, const ElemLayout &el, const AsmJ
         } else if (h.s.ncomp == 2) {
             if (el.elem_bytes == 8) FE_K5B(2, double, false);
             else FE_K5B(2, float, false);
-        } else if (by_runs(h.s)) {
+        } else if (by_runs(h.s, el.elem_bytes, grid)) {
             if (el.elem_bytes == 8) FE_K5B(3, double, true);
             else FE_K5B(3, float, true);
         } else {
