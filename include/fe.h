@@ -814,10 +814,10 @@ fe_status fe_server_destroy(fe_server server);
 /* ------------------------------------------------------------------------ */
 /* When enabled (process-wide), fe_integrate / fe_scatter record HIP events
  * around their kernels and the single-system solves (fe_pcg_solve,
- * fe_pcg_solve_mesh, fe_pcg_solve_sym; not those replayed from a graph)
- * around the SpMV launch of every 16th CG iteration before convergence, on
- * the call's own stream (an event pair costs a few microseconds of device
- * time).  fe_get_timing waits for the recorded events, returns the
+ * fe_pcg_solve_mesh, fe_pcg_solve_sym) around the SpMV launch of every 16th CG
+ * iteration before convergence, on the call's own stream (an event pair costs a
+ * few microseconds of device time).  A system solved by one workgroup has no
+ * SpMV launches to time.  fe_get_timing waits for the recorded events, returns the
  * accumulated kernel times (milliseconds) and counts of timed launches, and
  * clears them when reset != 0. */
 typedef struct {

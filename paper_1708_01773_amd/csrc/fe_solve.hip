@@ -93,7 +93,7 @@ struct PcgWs {
     double *p2;    // 2 x kGrid partials of r.z, r.r
     double *p3;    // 3 x ps partials of the initial r.z, r.r, b.b (and the final residual)
     int32_t ps;    // partial slots of the row kernels
-    double *hist;  // 2 x kHist (alpha, beta)
+    double *hist;  // kHist pairs (alpha, beta)
     double *r, *p, *q;
 };
 
@@ -2136,7 +2136,7 @@ __global__ __launch_bounds__(kBlock) void pcg_update_kernel(const PcgProb *__res
     const double alpha = st->rho[j & 1] / pq[0];
     if (lb == 0 && threadIdx.x == 0) {
         st->alpha = alpha;
-        if (j < kHist) P.w.hist[j] = alpha;
+        if (j < kHist) P.w.hist[2 * j] = alpha;
     }
     int64_t lo, hi;
     owned_elems(P.n, lb, nb, lo, hi);
@@ -2192,7 +2192,7 @@ __global__ __launch_bounds__(kBlock) void pcg_dir_kernel(const PcgProb *__restri
         st->rho[(j + 1) & 1] = t[0];
         st->rr = t[1];
         st->iter = j + 1;
-        if (j < kHist) P.w.hist[kHist + j] = beta;
+        if (j < kHist) P.w.hist[2 * j + 1] = beta;
         // stop_at, not done: the other blocks of this kernel still read the solve as running
         if (conv) {
             st->stop_at = j;
@@ -2538,8 +2538,8 @@ __global__ __launch_bounds__(kSmallThreads) void pcg_small_kernel(const PcgProb 
         rho = v2[0];
         rr = v2[1];
         if (tid == 0 && j < kHist) {
-            P.w.hist[j] = alpha;
-            P.w.hist[kHist + j] = beta;
+            P.w.hist[2 * j] = alpha;
+            P.w.hist[2 * j + 1] = beta;
         }
 #pragma unroll
         for (int u = 0; u < kElems; u++) {
@@ -2656,8 +2656,6 @@ fe_status launch_spmv(int64_t n, const int64_t *rowptr, const int32_t *colind, c
     return FE_OK;
 }
 
-// Smallest / largest eigenvalue of the symmetric tridiagonal (d, e) by
-// bisection on Sturm sequence counts.
 // Extremal eigenvalues of the symmetric tridiagonal matrix (d, e) by bisection
 // on the signs of its pivots: an eigenvalue lies below x if a pivot of
 // T - x is negative, none at or above x if all are.  Both ends are bisected
@@ -3239,9 +3237,9 @@ fe_status engine_states(EngineSet &E, hipStream_t s)
 }
 
 // True residuals of every problem of the set, then their states and infos.
-// pin: the state of a single system and its CG coefficients come straight
-// into pinned memory, with one wait.
-static fe_status engine_finish_to(EngineSet &E, hipStream_t s, StopSlots *pin)
+// pin: the state of a single system and its first nhist CG coefficient pairs
+// come straight into pinned memory, with one wait.
+static fe_status engine_finish_to(EngineSet &E, hipStream_t s, StopSlots *pin, int nhist = 0)
 {
     if (E.np == 0) return FE_OK;
     for (const Group &g : E.groups) launch_rows(2, g, E.d_probs, s);
@@ -3250,7 +3248,8 @@ static fe_status engine_finish_to(EngineSet &E, hipStream_t s, StopSlots *pin)
     if (pin && E.np == 1) {
         const PcgWs &w = E.hp[0].w;
         FE_HIP(hipMemcpyAsync(&pin->h->state, w.st, sizeof(PcgState), hipMemcpyDeviceToHost, s));
-        FE_HIP(hipMemcpyAsync(pin->h->hist, w.hist, sizeof(double) * 2 * kHist, hipMemcpyDeviceToHost, s));
+        if (nhist > 0)
+            FE_HIP(hipMemcpyAsync(pin->h->hist, w.hist, sizeof(double) * 2 * size_t(nhist), hipMemcpyDeviceToHost, s));
         FE_HIP(hipStreamSynchronize(s));
         E.hs[0] = pin->h->state;
     } else {
@@ -3347,6 +3346,8 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
             return set_error(FE_EDEVICE, "graph instantiation failed");
     }
     int j = 0, chunk = 8;
+    // coefficient pairs that j iterations may have left, if the solve wants them
+    auto pairs = [&](int n) { return spectrum ? std::min(n, kHist) : 0; };
     // one-workgroup systems alone: a launch of many iterations (some
     // milliseconds at most), the states read after each
     while (E.ge == 0) {
@@ -3354,7 +3355,7 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         if (todo > 0 && (st = engine_small(E, todo, s)) != FE_OK) return st;
         j += todo;
         FE_HIP(hipGetLastError());
-        if ((st = engine_finish_to(E, s, no_alloc ? nullptr : &slots)) != FE_OK) return st;
+        if ((st = engine_finish_to(E, s, no_alloc ? nullptr : &slots, pairs(j))) != FE_OK) return st;
         bool all = true;
         for (int t = 0; t < np; t++) all = all && engine_done(E, t);
         if (all || j >= maxit) break;
@@ -3399,7 +3400,7 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
             if (!more) break;
         }
     }
-    if (E.ge > 0 && (st = engine_finish_to(E, s, no_alloc ? nullptr : &slots)) != FE_OK) return st;
+    if (E.ge > 0 && (st = engine_finish_to(E, s, no_alloc ? nullptr : &slots, pairs(j))) != FE_OK) return st;
     for (size_t i = 0; i < marks.size(); i++) {
         if (mark_iter[i] < E.hs[0].iter) {
             timing_commit(marks[i].first, marks[i].second, kTimeSpmv);
@@ -3418,15 +3419,15 @@ static fe_status pcg_engine(std::vector<PcgJob> &jobs, void *table, bool use_gra
         fe_solve_info *info = E.jobs[0].info;
         const int m = std::min(E.hs[0].iter, kHist);
         if (m > 0) {
-            std::vector<double> hv(no_alloc ? 2 * kHist : 0);
+            std::vector<double> hv(no_alloc ? 2 * m : 0);
             if (no_alloc)
-                FE_HIP(hipMemcpy(hv.data(), E.hp[0].w.hist, sizeof(double) * 2 * kHist, hipMemcpyDeviceToHost));
+                FE_HIP(hipMemcpy(hv.data(), E.hp[0].w.hist, sizeof(double) * hv.size(), hipMemcpyDeviceToHost));
             const double *h = no_alloc ? hv.data() : slots.h->hist;
             std::vector<double> d(m), e(m > 1 ? m - 1 : 1);
             for (int i = 0; i < m; i++) {
-                const double a = h[i];
-                d[i] = 1.0 / a + (i > 0 ? h[kHist + i - 1] / h[i - 1] : 0.0);
-                if (i + 1 < m) e[i] = std::sqrt(h[kHist + i]) / a;
+                const double a = h[2 * i];
+                d[i] = 1.0 / a + (i > 0 ? h[2 * i - 1] / h[2 * i - 2] : 0.0);
+                if (i + 1 < m) e[i] = std::sqrt(h[2 * i + 1]) / a;
             }
             tridiag_extremes(d, e, info->lambda_min_est, info->lambda_max_est);
         }
