@@ -409,14 +409,14 @@ struct AxisClosed {
 // floor(a / k) for 0 <= a < 2^31 and an order k in 1..4, in integers (a shift,
 // or a multiplication by ceil(2^32 / 3)): exact, and uniform arguments stay
 // on the scalar unit, which a division through doubles does not.
-__device__ __forceinline__ int32_t div_order(int32_t a, int32_t k)
+__host__ __device__ __forceinline__ int32_t div_order(int32_t a, int32_t k)
 {
     const int32_t third = int32_t((uint64_t(uint32_t(a)) * 0x55555556u) >> 32);
     return k == 3 ? third : a >> (k >> 1);
 }
 
-__device__ __forceinline__ void axis_row(const AxisClosed &A, int32_t k, int32_t i, int32_t &w, int32_t &cl,
-                                         int32_t &P)
+__host__ __device__ __forceinline__ void axis_row(const AxisClosed &A, int32_t k, int32_t i, int32_t &w, int32_t &cl,
+                                                  int32_t &P)
 {
     if (A.N == 0) {  // the third axis of a 2D mesh
         w = 1;

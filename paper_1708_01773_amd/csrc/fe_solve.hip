@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "fe_internal.h"
+#include "fe_xblock.h"
 
 namespace fe {
 
@@ -95,13 +96,6 @@ struct PcgWs {
     int32_t ps;    // partial slots of the row kernels
     double *hist;  // kHist pairs (alpha, beta)
     double *r, *p, *q;
-};
-
-// How the block-staged traversal (plan mode 6) cuts a system into chunks.
-struct XbShape {
-    int32_t rc = 1, m = 1, pcs = 1, yb = 1;  // groups per line stretch, lines per chunk, stretches per line, y blocks
-    int32_t nchunks = 0;
-    int32_t lds = 0;  // bytes of the staged box
 };
 
 // How a small system is held by the one-workgroup solver (pcg_small_kernel).
@@ -1338,7 +1332,7 @@ __global__ __launch_bounds__(kQ1Block) void sym_fill_kernel(SpaceArgs s, const d
 //     arithmetic serve NC values each, in an order of its own.
 // Chunks are dealt XCD-contiguously (nb is a multiple of 8).
 constexpr int kXbRows = 64;   // most rows per chunk
-constexpr int kXbCap = 7536;  // most staged doubles: (2k+1)^2 runs of NC (nodes of a chunk + 2k), k <= 4
+constexpr int kXbCap = 7536;  // most staged doubles (the limit of xb_cut): (2k+1)^2 runs of NC (nodes of a chunk + 2k), k <= 4
 
 // The staged box of a chunk of one line: its kXbRows rows cover at most
 // (kXbRows - 1) / NC + 2 nodes of the line (a chunk may start inside a node's
@@ -1349,40 +1343,15 @@ constexpr int kXbCap = 7536;  // most staged doubles: (2k+1)^2 runs of NC (nodes
 constexpr int xblock_staged_max(int nc, int k) { return nc * ((kXbRows - 1) / nc + 2 + 2 * k) * (2 * k + 1) * (2 * k + 1); }
 static_assert(xblock_staged_max(1, 4) <= kXbCap && xblock_staged_max(2, 4) <= kXbCap &&
                   xblock_staged_max(3, 4) <= kXbCap,
-              "the staged x box of a mode-6 chunk exceeds its LDS buffer");
+              "the staged x box of a mode-6 chunk exceeds its LDS");
+static_assert(kQ1Block == kXbBlock, "the chunks are cut for the row kernels' blocks");
 
-constexpr int xb_lanes(int shape) { return shape == 8 ? 4 : 16; }
-constexpr int xb_group_rows(int shape, int nc) { return shape == 8 ? 1 : nc; }
-
-// The cut with the least work: every chunk streams up to G groups whatever it
-// holds (idle lanes cost what busy ones do) and stages its box, so short lines
-// of nodes are taken several to a chunk and long ones in equal stretches.
-static XbShape xb_shape(const SpaceArgs &sa, int shape)
+// The cut of a system, refused if its box does not fit.
+static fe_status xb_cut(const SpaceArgs &sa, int shape, XbShape &xb)
 {
-    const int nc = sa.ncomp, k = sa.k, G = kQ1Block / xb_lanes(shape), gr = xb_group_rows(shape, nc);
-    const int64_t f0 = sa.ax[0].f, f1 = sa.ax[1].f, f2 = sa.ax[2].f;
-    XbShape best{};
-    if (f0 == 0 || f1 == 0 || f2 == 0) return best;
-    const int64_t gpl = f0 * nc / gr;  // groups per line
-    double row = nc;                   // values per row, average over the vertex and interior nodes of an axis
-    for (int r = 0; r < sa.dim; r++) row *= double(2 * k + 1 + (k - 1) * (k + 1)) / k;
-    double cost = 0.0;
-    const int64_t p0 = (gpl + G - 1) / G;
-    for (int64_t pcs = p0; pcs < p0 + 4 && pcs <= gpl; pcs++) {
-        const int64_t rc = (gpl + pcs - 1) / pcs;
-        const int64_t m = std::max<int64_t>(1, std::min<int64_t>(f1, G / rc));
-        const int64_t yb = (f1 + m - 1) / m;
-        const int64_t nodes = std::min<int64_t>(f0, (rc * gr - 1) / nc + 2 + 2 * k);
-        const int64_t wy = std::min<int64_t>(f1, m + 2 * k), wz = sa.dim == 3 ? std::min<int64_t>(f2, 2 * k + 1) : 1;
-        const int64_t staged = nc * nodes * wy * wz;
-        const double c = double(yb * pcs) * (G * gr * row + 2.0 * double(staged));
-        if (best.nchunks == 0 || c < cost) {
-            cost = c;
-            best = XbShape{int32_t(rc), int32_t(m), int32_t((gpl + rc - 1) / rc), int32_t(yb), 0, int32_t(8 * staged)};
-            best.nchunks = int32_t(f2 * yb * best.pcs);
-        }
-    }
-    return best;
+    xb = xb_shape(sa, shape);
+    if (xb.lds > int32_t(sizeof(double)) * kXbCap) return set_error(FE_EINVAL, "the staged box of a chunk exceeds its LDS");
+    return FE_OK;
 }
 
 extern __shared__ double fe_xb_lds[];                                       // the staged box (XbShape::lds bytes)
@@ -1425,18 +1394,9 @@ __device__ __forceinline__ void for_rows_xblock(const SpaceArgs &s, const XbShap
     const int32_t xcd = int32_t(lb % 8), per = int32_t(nb / 8);
     const int32_t c_hi = int32_t(int64_t(xcd + 1) * xb.nchunks / 8);
     for (int32_t ch = int32_t(int64_t(xcd) * xb.nchunks / 8) + int32_t(lb / 8); ch < c_hi; ch += per) {
-        const int32_t q = ch / xb.pcs, pc = ch - q * xb.pcs;
-        const int32_t t2 = q / xb.yb, ya = (q - t2 * xb.yb) * m;   // plane and first line of the chunk
-        const int32_t ny = ya + m < f1 ? m : f1 - ya;               // lines of the chunk
-        const int32_t lr0 = pc * rc * GR;                           // its rows along a line: [lr0, lr1)
-        const int32_t lr1 = lr0 + rc * GR < rpl ? lr0 + rc * GR : rpl;
-        int32_t wa, cla, Pa, wb, clb, Pb, wya, cya, Pya, wyb, cyb, Pyb, w2, cl2, P2;
-        axis_row(A[0], k, A[0].lo + lr0 / NC, wa, cla, Pa);
-        axis_row(A[0], k, A[0].lo + (lr1 - 1) / NC, wb, clb, Pb);
-        axis_row(A[1], k, A[1].lo + ya, wya, cya, Pya);
-        axis_row(A[1], k, A[1].lo + ya + ny - 1, wyb, cyb, Pyb);
-        axis_row(A[2], k, A[2].lo + t2, w2, cl2, P2);
-        const int32_t run = NC * (clb + wb - cla), W1 = cyb + wyb - cya;
+        const XbBox B = xb_box(A, xb, k, NC, GR, f1, rpl, ch);
+        const int32_t t2 = B.t2, ya = B.ya, ny = B.ny, lr0 = B.lr0, lr1 = B.lr1, w2 = B.w2, cl2 = B.cl2, P2 = B.P2;
+        const int32_t cla = B.cla, cya = B.cya, run = B.run, W1 = B.W1;
         __syncthreads();  // the previous chunk's reads of sx are done
         {
             // element e of the box: run rr = e / run, (jy, jz) = rr mod, div W1; exact
@@ -2869,7 +2829,8 @@ fe_status spmv_autotune_struct(const SpaceArgs &sa, const double *values, int re
     fe_status st = FE_OK;
     for (size_t c = 0; c < cand.size() && st == FE_OK; c++) {
         const SpmvPlan pl = aligned_form(launch_form(cand[c], n), values);
-        const XbShape xb = pl.mode == 6 ? xb_shape(sa, pl.rpb) : XbShape{};
+        XbShape xb{};
+        if (pl.mode == 6 && (st = xb_cut(sa, pl.rpb, xb)) != FE_OK) break;
         const int g = grid_rows(n, pl, xb);
         for (int r = -1; r < reps; r++) {
             if (r == 0 && hipEventRecord(e0, s) != hipSuccess) st = set_error(FE_EDEVICE, "event record failed");
@@ -3107,7 +3068,10 @@ fe_status engine_build(EngineSet &E, const PcgJob *jobs, int njobs, void *table,
         P.maxit = jb.maxit;
         if (jb.sa) P.sa = *jb.sa;
         const SpmvPlan &pl = plans[order[t]];
-        if (pl.mode == 6) P.xb = xb_shape(*jb.sa, pl.rpb);
+        if (pl.mode == 6) {
+            const fe_status st = xb_cut(*jb.sa, pl.rpb, P.xb);
+            if (st != FE_OK) return st;
+        }
         P.turn = alternates(pl, (jb.sym ? int64_t(sym_slots(jb.sa->dim)) * sym_stride(jb.n) : jb.nnz) * (jb.fp32 ? 4 : 8));
         P.nbr = grid_rows(jb.n, pl, P.xb);
         P.nbe = grid_elems(jb.n);
@@ -3565,7 +3529,11 @@ fe_status launch_spmv_struct(const SpaceArgs &sa, const double *val, const doubl
 {
     if (sa.n_rows == 0) return FE_OK;
     const SpmvPlan pl = aligned_form(struct_plan(sa), val);
-    const XbShape xb = pl.mode == 6 ? xb_shape(sa, pl.rpb) : XbShape{};
+    XbShape xb{};
+    if (pl.mode == 6) {
+        const fe_status st = xb_cut(sa, pl.rpb, xb);
+        if (st != FE_OK) return st;
+    }
     const int g = grid_rows(sa.n_rows, pl, xb);
     FE_SPLAN_DISPATCH(pl, (spmv_struct_kernel<kMode, kRpb, kNc><<<dim3(g), dim3(rows_block(kMode)), xb.lds, s>>>(sa, xb, val, x, y)));
     FE_HIP(hipGetLastError());
