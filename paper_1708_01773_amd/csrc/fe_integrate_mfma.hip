@@ -902,7 +902,8 @@ fe_status launch_mfma_batch(const AsmJob &h, const AsmJob *jobs, const int32_t *
     switch (h.p.precision) {
         case FE_FP32: return with_shape(h.s.k, el, ppw, BatchLaunch<PolF32>{jobs, boff, njobs, grid, s});
         case FE_FP16: return with_cell16(h.s.k, el, Cell16Batch<PolF16>{jobs, boff, njobs, grid, s});
-        default: return with_cell16(h.s.k, el, Cell16Batch<PolBF16>{jobs, boff, njobs, grid, s});
+        case FE_BF16: return with_cell16(h.s.k, el, Cell16Batch<PolBF16>{jobs, boff, njobs, grid, s});
+        default: return set_error(FE_EINVAL, "no matrix-core kernel for this precision");  // FP64: launch_tensor_batch
     }
 }
 
