@@ -146,6 +146,7 @@ def cpu_baseline(wl, gpu_iters, ncells_full, nnz_full, n=64, cg_its=60):
     }
 
 
+# vector and matrix unit alike in FP64 and FP32, matrix unit in the 16-bit types
 PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "fp16": 2500.0, "bf16": 2500.0}
 E_BYTES = {"fp64": 8, "fp32": 4, "fp16": 4, "bf16": 4}  # element-matrix storage (FP32 for the reduced GEMMs)
 
@@ -195,7 +196,7 @@ def csr_roofline(A, F, torch, stream, reps=30):
 def c3_assembly(F, torch, reps=5, precisions=("fp64", "bf16", "fp16")):
     """3D elasticity on Q2 48^3, Q3 32^3, Q4 24^3 (jittered, f = (0,0,-1),
     clamped): assembly (K3 + K5) per precision with event-timed kernels, the
-    K3 fraction of the matrix-core peak on 18 nn^2 nq flops per cell and of HBM
+    K3 fraction of its unit's peak on the flops of k3_flops and of HBM
     on its element-matrix bytes, the K5 fraction of HBM on NE_ff (8 + 4) + 8 nnz
     + 8 n bytes (element entries and their positions read, values and rhs
     written); then the SpMV of the FP64 system through the block-staged
@@ -227,11 +228,13 @@ def c3_assembly(F, torch, reps=5, precisions=("fp64", "bf16", "fp16")):
             k3 = tm["integrate_ms"] / max(tm["integrate_calls"], 1) * 1e-3
             k5 = tm["scatter_ms"] / max(tm["scatter_calls"], 1) * 1e-3
             nloc = 3 * nn
-            fl = k3_flops(wl, ncells)
+            fl = k3_flops(wl, ncells, prec)
+            unit = k3_unit(wl, prec)
             e_bytes = ncells * (8 + nloc * nloc * E_BYTES[prec]) + (n + 1) ** dim * dim * 8
             k5_bytes = ne_ff(dim, n, k, 3) * (E_BYTES[prec] + 4) + 8 * A.nnz + 8 * A.n_rows
             r = {"elements_per_s": ncells / (k3 + k5), "k3_ms": k3 * 1e3, "k5_ms": k5 * 1e3,
-                 "k3_algorithmic_tflops": fl / k3 / 1e12, "k3_mfma_frac": fl / k3 / 1e12 / PEAK_TFLOPS[prec],
+                 "k3_algorithmic_tflops": fl / k3 / 1e12, "k3_unit": unit,
+                 "k3_unit_frac": fl / k3 / 1e12 / PEAK_TFLOPS[prec],
                  "k3_hbm_frac": e_bytes / k3 / 1e9 / HBM_PEAK_GBS, "k5_hbm_frac": k5_bytes / k5 / 1e9 / HBM_PEAK_GBS,
                  "k3_bytes": e_bytes, "k5_bytes": k5_bytes}
             if prec == "fp64":
@@ -249,7 +252,7 @@ def c3_assembly(F, torch, reps=5, precisions=("fp64", "bf16", "fp16")):
                     "own_bytes": own, "csr_plan": list(F.spmv_plan_of(A.n_rows, A.nnz)[:2])}
                 del x, y
             res[prec] = r
-            print(f"[bench] {key} {prec}: K3 {k3 * 1e3:.2f} ms ({r['k3_mfma_frac']:.2f} of MFMA, "
+            print(f"[bench] {key} {prec}: K3 {k3 * 1e3:.2f} ms ({r['k3_unit_frac']:.2f} of the {unit} unit, "
                   f"{r['k3_hbm_frac']:.2f} of HBM), K5 {k5 * 1e3:.2f} ms ({r['k5_hbm_frac']:.2f} of HBM)",
                   file=sys.stderr, flush=True)
             del A
@@ -259,13 +262,31 @@ def c3_assembly(F, torch, reps=5, precisions=("fp64", "bf16", "fp16")):
     return out
 
 
-def k3_flops(wl, ncells):
-    """Algorithmic flops of element integration: Poisson 2 nn^2 d nq, elasticity
-    18 nn^2 nq per cell (geometry excluded)."""
+def k3_flops(wl, ncells, precision="fp64"):
+    """Flops of element integration as its kernel computes it (geometry
+    excluded).  Reduced precisions and scalar Q1 contract over the quadrature
+    points: Poisson 2 nn^2 d nq, elasticity 18 nn^2 nq per cell.  FP64 of every
+    other space sums one direction after the other: per ordered pair of
+    components and, in 3D, pair of node planes a2 <= b2, with m = k + 1, the sum
+    over q2 (9 coefficients, 2 flops each, 6 where a coefficient is formed from
+    lambda, mu and J^-1), the one over q1 (18 flops) and the one over q0 (6 per
+    column node, 4 per entry); in 2D the sums over q1 (12, or 28) and q0."""
     d, k = wl["dim"], wl["k"]
+    el = wl["problem"] == "elasticity"
     nn = nq = (k + 1) ** d
-    per = 18 * nn * nn * nq if wl["problem"] == "elasticity" else 2 * nn * nn * d * nq
-    return per * ncells
+    if precision != "fp64" or (k == 1 and not el):
+        return (18 * nn * nn * nq if el else 2 * nn * nn * d * nq) * ncells
+    m = k + 1
+    if d == 3:
+        per = m * (m + 1) // 2 * (9 * (6 if el else 2) * m ** 3 + 18 * m ** 4 + 6 * m ** 4 + 4 * m ** 5)
+    else:
+        per = (28 if el else 12) * m ** 4 + 6 * m ** 4 + 4 * m ** 5
+    return per * (d * d if el else 1) * ncells
+
+
+def k3_unit(wl, precision):
+    """The unit the flops of k3_flops run on (its peak: PEAK_TFLOPS)."""
+    return "vector" if precision == "fp64" or wl["k"] == 1 else "matrix"
 
 
 def assemble_only(args, wl, A, ncells, F, torch):
@@ -283,13 +304,14 @@ def assemble_only(args, wl, A, ncells, F, torch):
     F.set_timing(False)
     k3 = tm["integrate_ms"] / max(tm["integrate_calls"], 1) * 1e-3
     k5 = tm["scatter_ms"] / max(tm["scatter_calls"], 1) * 1e-3
-    fl = k3_flops(wl, ncells)
+    fl = k3_flops(wl, ncells, wl["precision"])
     peak = PEAK_TFLOPS[wl["precision"]]
     out = {"metric": "hex elements assembled/s (assembly only)", "value": ncells * args.steps / total,
            "unit": "elements/s", "steps": args.steps, "ms_per_step": total / args.steps * 1e3,
            "dtype": wl["precision"], "config": {"workload": wl["text"], "cells": ncells, "order": wl["k"],
                                                 "dofs": A.n_rows, "nnz": A.nnz},
-           "k3": {"ms": k3 * 1e3, "algorithmic_tflops": fl / k3 / 1e12, "peak_tflops": peak,
+           "k3": {"ms": k3 * 1e3, "algorithmic_tflops": fl / k3 / 1e12, "unit": k3_unit(wl, wl["precision"]),
+                  "peak_tflops": peak,
                   "frac": fl / k3 / 1e12 / peak},
            "k5": {"ms": k5 * 1e3}}
     print(json.dumps(out), flush=True)
