@@ -568,8 +568,9 @@ fe_status fe_pcg_solve_sym(fe_mesh mesh, int32_t order, const fe_coeff *coeff, c
 /* A plan is how the CSR SpMV of fe_spmv / fe_pcg_solve / fe_pcg_solve_batch
  * walks the rows: mode 0 = wave-level CSR-stream with rows_per_wave rows
  * (1..32) per wave iteration, mode 1 = one wave per row, mode 9 = block tiles
- * of rows_per_wave rows (4..256).  Without tuning a plan follows from n_rows
- * and the average row length nnz / n_rows; fe_spmv_autotune
+ * of rows_per_wave rows (4..256).  Without tuning a plan follows from the
+ * average row length nnz / n_rows, for a matrix of more than 1024 rows that
+ * stays in cache also from its size; fe_spmv_autotune
  * times every plan on a matrix (reps launches each, after a warm-up launch)
  * and makes the fastest the plan of every matrix of the same row-length class
  * (half octaves of nnz / n_rows) in this process.  The plan fixes each row's

@@ -290,8 +290,9 @@ __device__ __forceinline__ void dg_axis(const DgArgs &d, const DgPair &P, const 
 // normal parts of either side, phi_t grad phi_u likewise), each separable in
 // the two tangential directions, instead of a table of normal derivatives per
 // (facet node, basis function), built facet by facet by one workgroup per cell
-// and read back seven values an entry: kernel 1063 -> 579 us at 32^3 Q2 (1.3 GB
-// written, 2.5 TB/s; 2780 vector instructions a cell, a quarter of the time).
+// and read back seven values an entry: kernel 1063 -> 556 us at 32^3 Q2 (1.30 GB of
+// entries, 1.51 GB written: 2.7 TB/s; 2690 vector instructions a cell, waves waiting
+// for 61% of their cycles).
 // With the element matrices (of the contraction kernels, before they were
 // summed by factors) 1209 -> 815, 3D Q1 33x29x35 151 -> 78, Q3 20x21x19 1360 ->
 // 785, Q4 14x13x12 2500 -> 1092, 2D Q1 300x280 129 -> 55, Q4 90x100 243 -> 208;

@@ -635,8 +635,9 @@ static bool by_runs(const SpaceArgs &sa, int32_t elem_bytes, int64_t blocks)
 
 // Blocks of the cell-major scatter, a wave per node, nodes interleaved over a
 // grid that fills the chip.  Measured on large systems (run by run, Q4 24^3
-// FP64: 3000 blocks 6.63 ms, 5000 5.94, 8192 6.54; entry by entry, scalar Q2
-// 48^3: 2048 blocks 917 us, 8192 836).  Below, a last round in which few waves
+// FP64: 2048 blocks 6.26 ms, 5000 6.00, 8192 5.89, a wave per node 6.16, where runs
+// of one form differ by up to 0.9 with where its arrays lie; entry by entry, scalar
+// Q2 48^3: 2048 blocks 917 us, 8192 836).  Below, a last round in which few waves
 // have a node left would cost up to a third: every wave takes the same number of
 // nodes (scalar Q2 20x22x21 91 -> 76 us, Q3 20^3 254 -> 236; elasticity Q2 24^3
 // 381 -> 348), or one each (elasticity Q2 14x15x16 107 -> 78, Q4 8^3 244 -> 203).

@@ -240,33 +240,39 @@ static std::map<int, SpmvPlan> g_tuned;
 // two in [4, 256] with R avg <= kTileRowsTarget entries (three passes; the
 // fastest tile sizes of the autotuner on the 128^3 Q1 and the Q2-Q4
 // elasticity matrices, 27 to 611 entries per row, lie at 3000-9000 entries).
-// A matrix of less than kTilesFew such tiles (eight for each CU) takes half the
-// rows per tile while half a tile still fills most of a pass: it stays in cache,
-// and an iteration is bound by the passes of the few tiles each CU has.
-// Measured per CG iteration (us, the larger / the smaller tiles; in a batch of
-// copies that together exceed the cache, the same): 25 entries a row, 4 MB 16.9 /
-// 14.7, 270 / 272; 27 (shuffled quadratic tetrahedra), 18 MB 22.2 / 20.1, 346 /
-// 350; 41 (cubic tetrahedra), 7 MB 32.7 / 21.1, 358 / 298; 52, 4 MB 19.6 / 16.5,
-// 240 / 247; 103, 21 MB 24.1 / 19.3, 213 / 223; 148, 17 MB 28.4 / 19.9, 200 / 197;
-// 162, 68 MB 45.8 / 36.9, 194 / 183; 292, 80 MB 50.5 / 37.5, 200 / 197.  A quarter
-// of the rows costs the batches 18-37%.  From kTilesFew on the smaller tiles gain
-// nothing (25 entries a row, 185 MB 65.1 / 67.1; 77, 182 MB 64.0 / 66.2).
-// The wave-level plans are faster still for one such matrix (148: 17.2; 292: 29.5)
+// A matrix that stays in cache is bound by the chain of passes of the few tiles
+// each CU has, and takes smaller ones, down to about one pass: rows below 96
+// entries where there are less than kTilesFew tiles (eight for each CU; from there
+// on smaller tiles gain nothing: 25 entries a row, 185 MB 65.1 / 67.1), longer rows
+// up to kCsrCached bytes.  Measured per CG iteration (us, the larger / the smaller
+// tiles; in a batch of copies that together exceed the cache, the same): 25
+// entries a row, 4 MB 16.9 / 14.7, 270 / 272; 27 (shuffled quadratic tetrahedra),
+// 18 MB 22.2 / 20.1, 346 / 350; 41 (cubic tetrahedra), 7 MB 32.7 / 17.3, 358 / 311;
+// 52, 4 MB 19.6 / 16.5, 240 / 247; 103, 21 MB 24.1 / 19.3, 213 / 223; 148, 17 MB
+// 28.4 / 19.9, 200 / 197; 170, 174 MB 63.9 / 59.9, 162 / 156.  Half as many rows
+// again costs the batches 5-37%.
+// The wave-level plans are faster still for one such matrix (27: 18.8; 148: 17.2),
 // but 1.1 to 1.9 times slower in a batch, and a batch sums a matrix as it is
-// summed alone, so the plan cannot depend on which it is.
-// A matrix that the one-workgroup solver holds is iterated without a plan; its
-// products alone are spread over the chip in tiles of at most 16 rows (us out of
-// cache: 961 rows, 8281 entries 8.8 / 6.4, 729 rows, 29791 entries 18.2 / 6.8).
+// summed alone, so the plan cannot depend on which it is.  Only from kLongRow
+// entries a row on are they the faster ones in both (a wave per row; 279, 47 MB
+// 36.8 / 24.5, 209 / 199; 310, 187 MB 75.3 / 44.8, 176 / 163).
+// Up to kPlanRows rows the plan follows from the row length alone, as callers of
+// the plan query have it; such a system is solved in one workgroup where it fits.
 constexpr double kTileRowsTarget = 6144.0;
 constexpr int64_t kTilesFew = 2048;
+constexpr int64_t kCsrCached = int64_t(200) << 20;  // bytes of columns and FP64 values
+constexpr double kLongRow = 256.0;
+constexpr int64_t kPlanRows = 1024;
 static SpmvPlan heuristic_plan(int64_t n, int64_t nnz)
 {
     const double avg = n > 0 ? double(nnz) / double(n) : 1.0;
+    const bool cached = n > kPlanRows && 12 * nnz <= kCsrCached;
+    if (cached && avg >= kLongRow) return stream_plan(avg);
     int R = 256;
     while (R > 4 && R * avg > kTileRowsTarget) R /= 2;
-    if (R > 4 && R * avg >= 0.5 * kTileRowsTarget && (n + R - 1) / R < kTilesFew) R /= 2;
-    bool resident;
-    if (small_fits(n, nnz, 8, resident)) R = std::min(R, 16);
+    const double pass = avg < 96.0 ? 2600.0 : 3072.0;  // entries of about one pass
+    if (cached && (avg >= 96.0 || (n + R - 1) / R < kTilesFew))
+        while (R > 4 && R * avg > pass) R /= 2;
     SpmvPlan pl{};
     pl.mode = 9;
     pl.rpb = R;

@@ -71,16 +71,19 @@ def _abs_product(A, x):
 
 
 # The reported plan is the launched one: setting it leaves the product as it
-# is.  Rows of 9 to 290 entries; tiles of 1536 to 6144 entries; in 2D Q2, 2042
-# and 2054 tiles of 256 rows (below 2048 half the rows are taken); at most 16
-# rows for a matrix that the one-workgroup solver holds (12x13x11 and the last two).  The product is that of one wave per row up to rounding.
-@pytest.mark.parametrize("dim,n,k,prob,rows", [(2, [100, 90], 1, "poisson", 256), (2, [60, 50], 2, "poisson", 128),
-                                               (2, [362, 362], 2, "poisson", 128), (2, [363, 363], 2, "poisson", 256),
-                                               (3, [12, 13, 11], 1, "poisson", 16), (3, [17, 17, 17], 1, "poisson", 128), (3, [20, 19, 21], 1, "poisson", 64),
-                                               (3, [9, 8, 10], 2, "poisson", 32), (3, [6, 5, 7], 3, "poisson", 32), (3, [9, 8, 9], 3, "poisson", 16),
-                                               (3, [6, 5, 5], 2, "elasticity", 16), (3, [4, 5, 4], 3, "elasticity", 8),
-                                               (2, [3, 3], 2, "poisson", 16), (2, [2, 2], 1, "poisson", 16)])
-def test_reported_csr_plan_is_the_launched_one(dim, n, k, prob, rows):
+# is.  Rows of 9 to 290 entries; in 2D Q2, 2042 and 2054 tiles of 256 rows (below
+# 2048 smaller tiles are taken); rows below and from 96 and 256 entries; at most
+# 1024 rows (tiles by the row length alone) and more.  The product is that of one
+# wave per row up to rounding.
+@pytest.mark.parametrize("dim,n,k,prob,plan", [(2, [100, 90], 1, "poisson", (9, 256)), (2, [60, 50], 2, "poisson", (9, 128)),
+                                               (2, [362, 362], 2, "poisson", (9, 128)), (2, [363, 363], 2, "poisson", (9, 256)),
+                                               (3, [11, 11, 11], 1, "poisson", (9, 256)), (3, [12, 11, 11], 1, "poisson", (9, 64)),
+                                               (3, [17, 17, 18], 1, "poisson", (9, 64)), (3, [9, 8, 10], 2, "poisson", (9, 32)),
+                                               (3, [6, 5, 7], 3, "poisson", (9, 16)), (3, [9, 8, 9], 3, "poisson", (9, 16)),
+                                               (3, [6, 5, 5], 2, "elasticity", (9, 16)), (3, [6, 6, 7], 2, "elasticity", (9, 16)),
+                                               (3, [4, 5, 4], 3, "elasticity", (9, 8)), (3, [6, 5, 6], 3, "elasticity", (1, 1)),
+                                               (2, [3, 3], 2, "poisson", (9, 256)), (2, [2, 2], 1, "poisson", (9, 256))])
+def test_reported_csr_plan_is_the_launched_one(dim, n, k, prob, plan):
     pair = Pair(dim, n, k, prob, seed=92)
     A = pair.gpu_assembly()
     say(f"[csr plan] dim {dim} n {n} k {k} {prob} rows {A.n_rows} nnz {A.nnz}")
@@ -89,7 +92,7 @@ def test_reported_csr_plan_is_the_launched_one(dim, n, k, prob, rows):
     F.spmv_tuning_reset()
     try:
         mode, rpw, _ = F.spmv_plan_of(A.n_rows, A.nnz)
-        assert (mode, rpw) == (9, rows)
+        assert (mode, rpw) == plan
         F.spmv(A.csr, x, y0)
         F.spmv_plan_set(A.n_rows, A.nnz, mode, rpw)
         F.spmv(A.csr, x, y1)
