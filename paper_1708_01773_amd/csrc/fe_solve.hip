@@ -250,7 +250,10 @@ static std::map<int, SpmvPlan> g_tuned;
 // 18 MB 22.2 / 20.1, 346 / 350; 41 (cubic tetrahedra), 7 MB 32.7 / 17.3, 358 / 311;
 // 52, 4 MB 19.6 / 16.5, 240 / 247; 103, 21 MB 24.1 / 19.3, 213 / 223; 148, 17 MB
 // 28.4 / 19.9, 200 / 197; 170, 174 MB 63.9 / 59.9, 162 / 156.  Half as many rows
-// again costs the batches 5-37%.
+// again costs the batches 5-37%.  Where not every CU has a tile, the line is a
+// little lower (39, cubic tetrahedra of 6440 rows, 64 / 32 rows: 19.9 / 16.0, in a
+// batch 303 / 329, with 128 rows 355), not above it (75, 45 MB, 32 / 16 rows: 26.9 /
+// 27.4, 195 / 204).
 // The wave-level plans are faster still for one such matrix (27: 18.8; 148: 17.2),
 // but 1.1 to 1.9 times slower in a batch, and a batch sums a matrix as it is
 // summed alone, so the plan cannot depend on which it is.  Only from kLongRow
@@ -260,6 +263,7 @@ static std::map<int, SpmvPlan> g_tuned;
 // the plan query have it; such a system is solved in one workgroup where it fits.
 constexpr double kTileRowsTarget = 6144.0;
 constexpr int64_t kTilesFew = 2048;
+constexpr int64_t kTilesIdle = 256;  // fewer tiles than CUs
 constexpr int64_t kCsrCached = int64_t(200) << 20;  // bytes of columns and FP64 values
 constexpr double kLongRow = 256.0;
 constexpr int64_t kPlanRows = 1024;
@@ -270,9 +274,11 @@ static SpmvPlan heuristic_plan(int64_t n, int64_t nnz)
     if (cached && avg >= kLongRow) return stream_plan(avg);
     int R = 256;
     while (R > 4 && R * avg > kTileRowsTarget) R /= 2;
-    const double pass = avg < 96.0 ? 2600.0 : 3072.0;  // entries of about one pass
+    auto pass = [&] {  // entries of about one pass
+        return avg >= 96.0 ? 3072.0 : (n + R - 1) / R < kTilesIdle ? 2400.0 : 2600.0;
+    };
     if (cached && (avg >= 96.0 || (n + R - 1) / R < kTilesFew))
-        while (R > 4 && R * avg > pass) R /= 2;
+        while (R > 4 && R * avg > pass()) R /= 2;
     SpmvPlan pl{};
     pl.mode = 9;
     pl.rpb = R;

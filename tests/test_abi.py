@@ -192,3 +192,18 @@ def test_simplex_entry_points_validate_on_host():
     assert L.fe_simplex_query(None, None, None, None, None) == F.FE_EINVAL
     assert L.fe_simplex_pattern(None, None, None) == F.FE_EINVAL
     assert L.fe_simplex_assemble(None, None, None) == F.FE_EINVAL
+
+
+def test_untuned_plans_in_cache_on_host():
+    """The lines of the default CSR plan above 1024 rows: entries of a tile, tiles for 256 CUs, and 200 MiB."""
+    def plan(n, avg):
+        return F.spmv_plan_of(n, int(n * avg))[:2]
+
+    assert plan(6440, 37) == (9, 64) and plan(6440, 38) == (9, 32)  # 101 tiles of 64 rows
+    assert plan(16384, 40) == (9, 64) and plan(16320, 40) == (9, 32)  # 256 and 255
+    assert plan(16384, 41) == (9, 32)
+    assert plan(52728, 75) == (9, 32)
+    assert plan(262000, 17) == (9, 128) and plan(524289, 17) == (9, 256)  # 2048 tiles
+    assert plan(20000, 95) == (9, 16) and plan(20000, 97) == (9, 16)
+    assert plan(20000, 255) == (9, 8) and plan(20000, 256) == (1, 1)
+    assert plan(68000, 256) == (1, 1) and plan(69000, 256) == (9, 16)  # 200 MiB: 68266 rows
